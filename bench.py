@@ -91,6 +91,9 @@ def kernel_bytes(ns, nn, nb, npx, lay):
         # inverse and r, z, p, x out
         "asm_fold": 152.0 * lay["fold_entries"] + 24.0 * nn * 4 + 144.0 * (2 * nb - nn) + 144.0 * nn + 28.0 * nn
                     + 288.0 * nn + 4 * 24.0 * nn,
+        # a whole linear solve and the node update in one launch: blocks and
+        # inverses once, r, z in, x, node state and tables out, index-map reset
+        "pcg_solve": 144.0 * nb + 288.0 * nn + 3 * 24.0 * nn + 152.0 * nn + 8.0 * npx,
         # diagonal blocks and gradient in; FP64 inverses and r, z, p, x out
         "pcg_init": 144.0 * nn + 24.0 * nn + 288.0 * nn + 4 * 24.0 * nn,
         # upper blocks once (each is used for a row and, transposed, a column),
@@ -125,6 +128,13 @@ def launches_per_frame(G, P, fused):
                      0 if P > 0 else G, G], dtype=float)
 
 
+def whole_solves(per_frame_us):
+    """Whether every linear solve ran as one launch (slot 3, which it shares
+    with the fused steps, without products before or between them)."""
+    us = dict(zip(KERNELS, per_frame_us))
+    return us["pcg_step"] > 0 and us["pcg_spmv"] == 0 and us["pcg_update"] == 0
+
+
 def stage_roofline(per_frame_us, launches, kb, replay, scale=1.0, streams=1):
     """Achieved GB/s of every replayed kernel (algorithmic bytes x scale / mean
     time per launch) and the roofline entry of the kernel with the largest
@@ -132,13 +142,16 @@ def stage_roofline(per_frame_us, launches, kb, replay, scale=1.0, streams=1):
     import numpy as np
     rates = {k: scale * kb[k] / (us * 1e-6) / 1e9 for k, us in replay.items() if us > 0}
     share = {k: per_frame_us[i] for i, k in enumerate(KERNELS) if k in replay and launches[i] > 0}
+    if "pcg_solve" in replay:
+        share = {k: v for k, v in share.items() if k not in ("pcg_step", "pcg_spmv", "pcg_update")}
+        share["pcg_solve"] = per_frame_us[KERNELS.index("pcg_step")]
     name = max(share, key=share.get)
     achieved = rates[name]
     traffic = measured_traffic(name, streams)
     roof = {"bound": "hbm", "kernel": name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
             "alg_bytes_per_launch": scale * kb[name], "avg_launch_us": round(float(replay[name]), 3),
-            "launches_per_frame": int(launches[KERNELS.index(name)])}
+            "launches_per_frame": int(launches[KERNELS.index("asm_fold" if name == "pcg_solve" else name)])}
     if traffic is not None:
         # the bytes the kernel moves beyond L2 (counters) per launch time, beside the algorithmic rate
         roof["traffic_gbs"] = round(traffic / (replay[name] * 1e-6) / 1e9, 1)
@@ -283,7 +296,7 @@ def run_plain_fifo(sts, frames, trace):
 
 # the sources compiled into the frame-solve kernels (a change to any of them
 # invalidates the committed HBM-traffic counts)
-SOLVE_SOURCES = ("frame.hip", "assemble.hip", "solve.hip", "swgn_frame.h", "swgn_impl.h", "swgn_launch.h")
+SOLVE_SOURCES = ("frame.hip", "assemble.hip", "solve.hip", "pcg.hip", "swgn_pcg.h", "swgn_frame.h", "swgn_impl.h", "swgn_launch.h")
 
 
 def kernel_source_hash():
@@ -533,6 +546,9 @@ def main():
     kb = kernel_bytes(ns, nn, nb, scene.cam.width * scene.cam.height, lay)
     px = swgn.Batch(hip_stream=hip_stream)
     replay = replay_us(px, [tst], Pi)
+    whole = whole_solves(per_frame_us)
+    if whole:        # (it moves the nodes, so it is timed in the frame, not replayed)
+        replay["pcg_solve"] = float(per_frame_us[KERNELS.index("pcg_step")]) / G
     px.close()
     tst.close()
     roofline, rates = stage_roofline(per_frame_us, launches, kb, replay)
@@ -621,7 +637,7 @@ def main():
                    "pcg_iters": p.pcg_iters, "mode": "plain"},
         "latency_ms": {"p50": round(1000 * percentile(lat, 0.5), 4),
                        "p99": round(1000 * percentile(lat, 0.99), 4)},
-        "pcg_schedule": "fused" if fused else "split",
+        "pcg_schedule": "whole" if whole else ("fused" if fused else "split"),
         "kernel_us_per_frame": {k: round(float(v), 2) for k, v in zip(KERNELS, per_frame_us)},
         "kernel_us_per_launch": {k: round(v, 3) for k, v in replay.items()},
         "roofline": roofline,
@@ -695,6 +711,9 @@ def run_batched(swgn, torch, scenes, depths, stream_of, hip_stream, args, copy_g
     Pi = max(sc.params.pcg_iters for sc in scenes)
     G = max(sc.params.gn_iters for sc in scenes)
     b_replay = replay_us(tb, sts, Pi, reps=50)
+    b_whole = whole_solves(btot)
+    if b_whole:
+        b_replay["pcg_solve"] = float(btot[KERNELS.index("pcg_step")]) / breps / G
     tb.close()
     kb = {}
     for t, sc in zip(sts, scenes):
@@ -723,7 +742,7 @@ def run_batched(swgn, torch, scenes, depths, stream_of, hip_stream, args, copy_g
             "kernel_us_per_batch_frame": {k: round(float(v), 2) for k, v in zip(KERNELS, btot / breps)},
             "kernel_us_per_launch": {k: round(v, 3) for k, v in b_replay.items()},
             "kernel_gbs": b_rates, "roofline": b_roof, "identical_to_solo": bool(same),
-            "pcg_schedule": "fused" if b_fused else "split",
+            "pcg_schedule": "whole" if b_whole else ("fused" if b_fused else "split"),
             "launch_variant": {k: ("xcd" if orders[STAGE_ID[k]] & 1 else "linear") +
                                ("+wide" if orders[STAGE_ID[k]] & 2 else "")
                                for k in KERNELS if k not in ("depth_prep", "node_update")

@@ -129,9 +129,9 @@ typedef struct sw_frame_stats {
     float stage_us[12];        /* with stage_timing: microseconds per kernel, summed
                                   over the frame: [0] depth preprocessing, [1] warp +
                                   index map, [2] correspondence + Jacobians +
-                                  segment Gram matrices, [3] fused PCG steps
-                                  (the last of an iteration also moves the
-                                  nodes), [4] block-Jacobi + PCG start (0: it
+                                  segment Gram matrices, [3] whole linear
+                                  solves and fused PCG steps (the last of an
+                                  iteration also moves the nodes), [4] block-Jacobi + PCG start (0: it
                                   runs inside the assembly), [5] PCG products,
                                   [6] PCG finishes, [7] node update of streams
                                   without PCG iterations, [8] assembly of the
@@ -185,7 +185,12 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos_xyz,
  * segment layout, all on the device. The node order defines the node
  * indices. n_nodes in [9, 32768]; surfels must be set (SW_ESTATE otherwise).
  * A repeated call reuses the device memory of the stream's previous node set
- * and so first waits for all work on the device (as freeing it would). */
+ * and so first waits for all work on the device (as freeing it would).
+ * Linear solves run as one launch per Gauss-Newton iteration whose workgroups
+ * wait for each other; where another process holds the device so that they
+ * cannot all run, they give up after SWGN_PCG_WAIT_US microseconds
+ * (environment, read here; default 100000) and the frame is solved again one
+ * launch per PCG iteration, with the same results. */
 sw_status sw_set_node_graph(sw_stream s, int32_t n_nodes, const float* node_pos_xyz,
                             const float* node_se3, int32_t on_device);
 
@@ -331,9 +336,12 @@ typedef struct sw_batch_s* sw_batch;
  * sw_set_node_graph on a member, captures anew). Results are identical to
  * the launch-by-launch path. Not combinable with SW_BATCH_TIMING (EINVAL);
  * streams that capture an iteration (debug_iter) run launch by launch.
- * SW_BATCH_PCG_SPLIT or SW_BATCH_PCG_FUSED (not both) fix the PCG schedule,
- * which is otherwise chosen per batch shape (the autotuner's choice, else
- * fused steps up to 8192 nodes in all); both give identical results. */
+ * SW_BATCH_PCG_SPLIT or SW_BATCH_PCG_FUSED (not both) fix the PCG schedule.
+ * Otherwise a linear solve is one launch for all streams whose node sets it
+ * can hold (while the device has room for its workgroups beside those of
+ * other executors' solves), and the rest run step by step in the schedule
+ * chosen per batch shape (the autotuner's choice, else fused steps up to 8192
+ * nodes in all); all give identical results. */
 sw_status sw_create_batch(void* hip_stream, int32_t flags, sw_batch* out);
 
 /* Destroy an executor (NULL is a no-op). Streams are not affected. */

@@ -14,7 +14,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <cstdlib>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -87,6 +89,59 @@ Executor::~Executor() {
     if (own_stream && st) (void)hipStreamDestroy(st);
 }
 
+// Waves of the whole-solve kernel leased on each device.
+constexpr int kMaxDevices = 64;
+static std::atomic<int> g_pcg_leased[kMaxDevices];
+
+// waves that a whole linear solve of stream s takes, in workgroups of so many; 0: it cannot take one
+static int whole_solve_waves(const Executor& ex, sw_stream s, int waves) {
+    if (s->pcg_sets(waves) == 0 || s->h.pcg_iters == 0) return 0;
+    const int n = pcg_tiles(s->h, waves) * waves;
+    return n <= ex.pcg_resident ? n : 0;
+}
+
+PcgLease::PcgLease(Executor& ex, const std::vector<sw_stream>& ss) : ex_(ex) {
+    ex.pcg_lease = 0;
+    if (ex.pcg_mode != kPcgAuto || ex.pcg_resident == 0) return;
+    // workgroups of 4 waves while every SIMD then has one wave at most (a wave
+    // alone on its SIMD is not slowed by another); beyond, of 8
+    auto total = [&](int waves, int& most) {
+        int all = 0;
+        most = 0;
+        for (sw_stream s : ss) {
+            const int n = whole_solve_waves(ex, s, waves);
+            most = std::max(most, n);
+            all += n;
+        }
+        return all;
+    };
+    int most = 0;
+    int all = total(4, most);
+    ex.pcg_waves = 4;
+    if (all > ex.pcg_resident / 2 || most == 0) {
+        all = total(8, most);
+        ex.pcg_waves = 8;
+    }
+    if (most == 0) return;
+    std::atomic<int>& leased = g_pcg_leased[ex.device];
+    int now = leased.load();
+    for (;;) {
+        const int n = std::min(all, ex.pcg_resident - now);
+        if (n < most) return;
+        if (leased.compare_exchange_weak(now, now + n)) {
+            ex.pcg_lease = n;
+            return;
+        }
+    }
+}
+
+void PcgLease::release() {
+    if (ex_.pcg_lease == 0) return;
+    (void)hipStreamSynchronize(ex_.st);
+    g_pcg_leased[ex_.device].fetch_sub(ex_.pcg_lease);
+    ex_.pcg_lease = 0;
+}
+
 void Executor::init(void* hip_stream) {
     if (hip_stream) {
         st = static_cast<hipStream_t>(hip_stream);
@@ -94,6 +149,11 @@ void Executor::init(void* hip_stream) {
         SWGN_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
         own_stream = true;
     }
+    SWGN_HIP(hipGetDevice(&device));
+    int cus = 0;
+    SWGN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+    if (device < kMaxDevices)
+        pcg_resident = std::min(4 * pcg_resident_workgroups(4, cus), 8 * pcg_resident_workgroups(8, cus));
     SWGN_HIP(hipMalloc(reinterpret_cast<void**>(&stats_dev), (size_t)kStatsOutBytes * kMaxBatch));
     SWGN_HIP(hipHostMalloc(&stats_host, (size_t)kStatsOutBytes * kMaxBatch, hipHostMallocDefault));
 }
@@ -253,6 +313,16 @@ void publish_desc(sw_stream s) {
     *s->h_pinned = s->h;
     SWGN_HIP(hipMemcpyAsync(s->d_desc, s->h_pinned, sizeof(FrameDesc), hipMemcpyHostToDevice, s->exec.st));
     SWGN_HIP(hipStreamSynchronize(s->exec.st));
+}
+
+// Longest wait of a whole solve's workgroup for the others, in 10 ns:
+// SWGN_PCG_WAIT_US microseconds (negative: gives up at once), else kPcgWait.
+long long pcg_wait_limit() {
+    const char* e = std::getenv("SWGN_PCG_WAIT_US");
+    char* end = nullptr;
+    const long long us = e ? std::strtoll(e, &end, 10) : 0;
+    if (!e || end == e) return kPcgWait;
+    return us < 0 ? -1 : std::min(us, 10000000LL) * 100;
 }
 
 // Segments, packs and the block fold's entries (once per node set, on the
@@ -636,6 +706,34 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     int* ell_col = G.alloc<int>((size_t)nn * h.ell_w);
     launch_ell(nn, h.ell_w, frow_ptr, fblk, fcol, ell_blk, ell_col, st);
     h.ell_blk = ell_blk; h.ell_col = ell_col;
+    // the whole-solve kernel's local columns and exchange words
+    s->pcg_sets4 = s->pcg_sets8 = 0;
+    if (h.ell_w <= kPcgMaxSlots) {
+        int* need = tmp.alloc<int>(2);
+        launch_fill_i32(need, 2, 0, st);
+        uint16_t* loc[2];
+        int *halo[2], *halo_n[2];
+        for (int q = 0; q < 2; ++q) {
+            const int waves = q ? 8 : 4;
+            const size_t tiles = (size_t)pcg_tiles(h, waves);
+            loc[q] = G.alloc<uint16_t>((size_t)nn * h.ell_w);
+            halo[q] = G.alloc<int>(tiles * pcg_halo(waves));
+            halo_n[q] = G.alloc<int>(tiles);
+            launch_pcg_local(waves, nn, h.ell_w, ell_blk, ell_col, loc[q], halo[q], halo_n[q], need + q, st);
+        }
+        int got[2];
+        SWGN_HIP(hipMemcpyAsync(got, need, sizeof(got), hipMemcpyDeviceToHost, st));
+        SWGN_HIP(hipStreamSynchronize(st));
+        if (got[0] <= pcg_halo(4)) s->pcg_sets4 = 1 + cdiv(got[0], pcg_rows(4));
+        if (got[1] <= pcg_halo(8)) s->pcg_sets8 = 1 + cdiv(got[1], pcg_rows(8));
+        h.loc4 = loc[0]; h.halo4 = halo[0]; h.halo_n4 = halo_n[0];
+        h.loc8 = loc[1]; h.halo8 = halo[1]; h.halo_n8 = halo_n[1];
+        if (s->pcg_sets4 > 0 || s->pcg_sets8 > 0) {
+            h.xpart = G.alloc<unsigned long long>(2 * kPcgCopies * pcg_part_words(h));
+            h.xuv = G.alloc<unsigned long long>(2 * (size_t)nn * 12);
+        }
+    }
+    h.pcg_wait = pcg_wait_limit();
     int* slot_u = G.alloc<int>(h.nb);
     int* slot_t = G.alloc<int>(h.nb);
     launch_fill_i32(slot_t, h.nb, -1, st);
@@ -697,9 +795,13 @@ void run_stage(Executor& ex, int stage, const std::vector<sw_stream>& ss, const 
     int64_t rows = 0;
     for (int i = 0; i < b.n; ++i)
         if (its[i] >= 0) rows += ss[i]->h.nn;
-    const int variant = ex.variant_of(stage, rows);
+    const int variant =
+        stage == kStPcgSolve ? (ex.pcg_waves == 8 ? kVarWide : 0) : ex.variant_of(stage, rows);
     b.order = (variant & kVarXcd) ? kOrderXcd : kOrderLinear;
     b.wide = (variant & kVarWide) ? 1 : 0;
+    if (stage == kStPcgSolve)
+        for (int i = 0; i < b.n; ++i)
+            if (its[i] >= 0) b.sets = std::max(b.sets, ss[i]->pcg_sets(ex.pcg_waves));
     int off = 0;
     for (int i = 0; i < b.n; ++i) {
         const FrameDesc& h = ss[i]->h;
@@ -728,6 +830,7 @@ void run_stage(Executor& ex, int stage, const std::vector<sw_stream>& ss, const 
             launch_frame_stage(stage, b, depth, ex.st);
             break;
         case kStAsmSeg: case kStAsmFold: launch_asm_stage(stage, b, ex.st); break;
+        case kStPcgSolve: launch_pcg_solve(b, ex.st); break;
         default: launch_solve_stage(stage, b, ex.stats_dev, ex.st); break;
     }
     if (timing) {
@@ -783,9 +886,6 @@ void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std
                        std::vector<int>& ev, std::vector<char>& captured) {
     hipStream_t st = ex.st;
     const int n = (int)ss.size();
-    int pmax = 0;
-    for (int i = 0; i < n; ++i)
-        if (its[i] >= 0) pmax = std::max(pmax, ss[i]->h.pcg_iters);
     auto capturing = [&](int i) { return its[i] >= 0 && its[i] == ss[i]->cfg.debug_iter; };
     run_stage(ex, kStWarp, ss, its, 0, nullptr, timing, ev);
     for (int i = 0; i < n; ++i) {
@@ -806,19 +906,42 @@ void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std
         SWGN_HIP(hipMemcpyAsync(s->dbg_g, h.g, sizeof(float) * 6 * h.nn, hipMemcpyDeviceToDevice, st));
     }
     // (the fold also starts PCG: block-Jacobi inverses, r_0, z_0, x = 0)
+    // whole solves, as many streams per launch as the lease has waves for
+    std::vector<int> steps = its;             // streams left to solve step by step
+    for (int i = 0; i < n && ex.pcg_lease > 0;) {
+        std::vector<int> now(n, -1);
+        int waves = 0;
+        bool any = false;
+        for (; i < n; ++i) {
+            const int w = its[i] >= 0 ? whole_solve_waves(ex, ss[i], ex.pcg_waves) : 0;
+            if (w == 0) continue;
+            // (with the whole device leased, workgroups start in order as others
+            // end: the first stream that is not done always gets all of its own)
+            if (waves + w > ex.pcg_lease && ex.pcg_lease < ex.pcg_resident) break;
+            waves += w;
+            any = true;
+            now[i] = its[i];
+            steps[i] = -1;
+        }
+        if (any) run_stage(ex, kStPcgSolve, ss, now, 0, nullptr, timing, ev, true);
+    }
+    int pmax = 0;
     int64_t rows = 0;
     for (int i = 0; i < n; ++i)
-        if (its[i] >= 0) rows += ss[i]->h.nn;
+        if (steps[i] >= 0) {
+            pmax = std::max(pmax, ss[i]->h.pcg_iters);
+            rows += ss[i]->h.nn;
+        }
     const bool fused = ex.pcg_mode == kPcgFused ||
                        (ex.pcg_mode == kPcgAuto && (ex.variant_of(kStSpmv, rows) & kVarFused) != 0);
-    if (pmax > 0) run_stage(ex, kStSpmv, ss, its, 0, nullptr, timing, ev);
+    if (pmax > 0) run_stage(ex, kStSpmv, ss, steps, 0, nullptr, timing, ev);
     for (int pit = 1; pit <= pmax; ++pit) {
         if (fused) {
             // finish of pit - 1 and, for streams with more iterations, products of pit
-            run_stage(ex, kStPcgStep, ss, its, pit, nullptr, timing, ev, true);
+            run_stage(ex, kStPcgStep, ss, steps, pit, nullptr, timing, ev, true);
         } else {
-            run_stage(ex, kStUpdate, ss, its, pit - 1, nullptr, timing, ev, true);
-            if (pit < pmax) run_stage(ex, kStSpmv, ss, its, pit, nullptr, timing, ev);
+            run_stage(ex, kStUpdate, ss, steps, pit - 1, nullptr, timing, ev, true);
+            if (pit < pmax) run_stage(ex, kStSpmv, ss, steps, pit, nullptr, timing, ev);
         }
     }
     run_stage(ex, kStNodeUpdate, ss, its, 0, nullptr, timing, ev);
@@ -841,19 +964,20 @@ void enqueue_collect(Executor& ex, const std::vector<sw_stream>& ss) {
 }
 
 sw_status collect_frames(Executor& ex, const std::vector<sw_stream>& ss, const float* stage_us,
-                         sw_frame_stats* stats, sw_status* status) {
+                         sw_frame_stats* stats, sw_status* status, std::vector<char>* stalled) {
     enqueue_collect(ex, ss);
     SWGN_HIP(hipGetLastError());
-    return finish_frames(ex, ss, stage_us, stats, status);
+    return finish_frames(ex, ss, stage_us, stats, status, stalled);
 }
 
 sw_status finish_frames(Executor& ex, const std::vector<sw_stream>& ss, const float* stage_us,
-                        sw_frame_stats* stats, sw_status* status) {
+                        sw_frame_stats* stats, sw_status* status, std::vector<char>* stalled) {
     hipStream_t st = ex.st;
     const int n = (int)ss.size();
     SWGN_HIP(hipStreamSynchronize(st));
     sw_status rc = SW_OK;
     bool restored = false;
+    if (stalled) stalled->assign(n, 0);
     for (int i = 0; i < n; ++i) {
         sw_stream s = ss[i];
         const FrameDesc& h = s->h;
@@ -900,6 +1024,7 @@ sw_status finish_frames(Executor& ex, const std::vector<sw_stream>& ss, const fl
             status[i] = SW_ENUMERIC;
             rc = SW_ENUMERIC;
             restored = true;
+            if (stalled && flags[1] != 0) (*stalled)[i] = 1;
         }
     }
     if (restored) SWGN_HIP(hipStreamSynchronize(st));
@@ -920,6 +1045,7 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         gmax = std::max(gmax, ss[i]->cfg.gn_iters);
         any_capture |= ss[i]->cfg.debug_iter >= 0 && ss[i]->cfg.debug_iter < ss[i]->cfg.gn_iters;
     }
+    PcgLease lease(ex, ss);
     enqueue_depth(ex, ss, depths, on_device, timing, ev);
     enqueue_rigid(ex, ss, timing, ev);
     std::vector<char> captured(n, 0);
@@ -938,6 +1064,7 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         std::vector<std::pair<sw_stream, uint64_t>> key;
         for (sw_stream s : ss) key.emplace_back(s, s->generation);
         key.emplace_back(nullptr, ex.tune_epoch);
+        key.emplace_back(nullptr, (uint64_t)ex.pcg_lease * 16 + (uint64_t)ex.pcg_waves);
         if (!ex.graph_exec || key != ex.graph_key) {
             ex.drop_graph();
             hipGraph_t g = nullptr;
@@ -972,9 +1099,36 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
             stage_us[stage_slot(ev[a])] += 1000.f * ms;
         }
     }
-    const sw_status rc = finish_frames(ex, ss, timing ? stage_us : nullptr, stats, status);
+    std::vector<char> stalled;
+    sw_status rc = finish_frames(ex, ss, timing ? stage_us : nullptr, stats, status, &stalled);
+    lease.release();
     for (int i = 0; i < n; ++i)
         if (captured[i]) ss[i]->captured = true;
+    if (std::find(stalled.begin(), stalled.end(), 1) != stalled.end()) {
+        // a whole solve gave up waiting for its workgroups (another process
+        // holds the chip): those frames again, step by step, as every later
+        // frame of this executor
+        ex.pcg_resident = 0;
+        std::vector<sw_stream> again;
+        std::vector<const float*> again_depth;
+        std::vector<int> at;
+        for (int i = 0; i < n; ++i)
+            if (stalled[i]) {
+                again.push_back(ss[i]);
+                again_depth.push_back(depths[i]);
+                at.push_back(i);
+            }
+        std::vector<sw_frame_stats> st2(again.size());
+        std::vector<sw_status> rc2(again.size(), SW_OK);
+        (void)solve_frames(ex, again, again_depth.data(), on_device, timing, stats ? st2.data() : nullptr, rc2.data());
+        rc = SW_OK;
+        for (size_t q = 0; q < at.size(); ++q) {
+            if (stats) stats[at[q]] = st2[q];
+            status[at[q]] = rc2[q];
+        }
+        for (int i = 0; i < n; ++i)
+            if (status[i] != SW_OK) rc = status[i];
+    }
     return rc;
 }
 

@@ -85,12 +85,36 @@ struct Executor {
     // replay of a batch's iterations as one HIP graph
     bool graphs = false;
     int pcg_mode = 0;                     // kPcgAuto, kPcgSplit, kPcgFused
+    // whole linear solves in one launch (pcg.hip): how many waves of it the
+    // device holds at once (0: never used), and how many of them a launch of
+    // the call being enqueued may take (its lease), in workgroups of how many
+    int device = 0;
+    int pcg_resident = 0;
+    int pcg_lease = 0;
+    int pcg_waves = 4;
     hipGraphExec_t graph_exec = nullptr;
     std::vector<std::pair<sw_stream, uint64_t>> graph_key;   // (stream, generation) it was captured for
     ~Executor();
     void init(void* hip_stream);
     hipEvent_t event(size_t i);
     void drop_graph();
+};
+
+// The right to have n waves of the whole-solve kernel resident on a device, held while launches that need them may run: its workgroups wait for
+// each other, so all that are in flight in this process together must fit
+// the chip. Takes what the streams can use, at least their largest solve, or
+// nothing (their linear solves then run step by step, with equal results).
+class PcgLease {
+public:
+    PcgLease(Executor& ex, const std::vector<sw_stream>& ss);
+    ~PcgLease() { release(); }
+    PcgLease(const PcgLease&) = delete;
+    PcgLease& operator=(const PcgLease&) = delete;
+    // waits for the executor's stream and gives the workgroups back
+    void release();
+
+private:
+    Executor& ex_;
 };
 
 inline sw_status fail(std::string& err, sw_status code, const std::string& msg) {
@@ -112,6 +136,10 @@ sw_status guarded(std::string& err, F&& f) {
 }
 
 size_t carve_workspace(FrameDesc& h, char* base);
+
+// longest wait of a whole solve's workgroup for the others before the frame
+// is solved again step by step (100 ms, in 10 ns)
+constexpr long long kPcgWait = 10000000;
 
 }  // namespace rt
 }  // namespace swgn
@@ -153,6 +181,10 @@ struct sw_stream_s {
     float *apos3 = nullptr, *anrm3 = nullptr, *arad = nullptr, *aconf = nullptr;
     bool surfels_set = false;
     bool graph_set = false;
+    // sets of local nodes the whole-solve kernel needs with workgroups of 4
+    // and 8 waves (0: the node set does not fit it)
+    int pcg_sets4 = 0, pcg_sets8 = 0;
+    int pcg_sets(int waves) const { return waves == 4 ? pcg_sets4 : pcg_sets8; }
     sw_server server = nullptr;           // set while attached to a serving loop
 
     // descriptor: host copy, pinned staging copy and the device copy kernels read
@@ -195,9 +227,11 @@ void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std
                        std::vector<int>& ev, std::vector<char>& captured);
 void enqueue_collect(Executor& ex, const std::vector<sw_stream>& ss);
 sw_status collect_frames(Executor& ex, const std::vector<sw_stream>& ss, const float* stage_us,
-                         sw_frame_stats* stats, sw_status* status);
+                         sw_frame_stats* stats, sw_status* status, std::vector<char>* stalled = nullptr);
+// stalled (or null): streams whose frame has to be solved again because a
+// whole solve gave up waiting (their node state is the frame's start's)
 sw_status finish_frames(Executor& ex, const std::vector<sw_stream>& ss, const float* stage_us,
-                        sw_frame_stats* stats, sw_status* status);
+                        sw_frame_stats* stats, sw_status* status, std::vector<char>* stalled = nullptr);
 uint64_t shape_bucket(const std::vector<sw_stream>& ss);
 void server_quiesce(sw_server sv, sw_stream s);
 void server_forget(sw_server sv, sw_stream s);

@@ -155,8 +155,10 @@ void sw_server_s::run() {
     std::vector<int> its;
     std::vector<char> captured;
     std::vector<int> ev;
+    std::vector<Ticket*> again;      // frames to be solved anew (a whole solve gave up waiting)
     for (;;) {
         std::vector<Ticket*> admitted;
+        admitted.swap(again);
         {
             std::unique_lock<std::mutex> lk(mu);
             cv_work.wait(lk, [&] { return stop || !pending.empty() || !active.empty(); });
@@ -216,6 +218,7 @@ void sw_server_s::run() {
                 its.push_back(a.it < a.t->s->cfg.gn_iters ? a.it : -1);
             }
             captured.assign(ss.size(), 0);
+            PcgLease lease(exec, ss);
             enqueue_iteration(exec, ss, its, false, ev, captured);
             for (size_t i = 0; i < active.size(); ++i) {
                 if (captured[i]) active[i].t->s->captured = true;
@@ -231,11 +234,23 @@ void sw_server_s::run() {
             if (!fs.empty()) {
                 std::vector<sw_frame_stats> st(fs.size());
                 std::vector<sw_status> status(fs.size());
-                collect_frames(exec, fs, nullptr, st.data(), status.data());
+                std::vector<char> stalled;
+                collect_frames(exec, fs, nullptr, st.data(), status.data(), &stalled);
+                std::vector<Ticket*> ended;
                 for (size_t i = 0; i < fs.size(); ++i) {
+                    if (stalled[i]) {
+                        // from the start again, step by step, as every later frame here
+                        exec.pcg_resident = 0;
+                        again.push_back(finished[i]);
+                        for (Active& a : active)
+                            if (a.t == finished[i]) a.it = 0;
+                        continue;
+                    }
                     finished[i]->stats = st[i];
                     finished[i]->status = status[i];
+                    ended.push_back(finished[i]);
                 }
+                finished.swap(ended);
             } else {
                 SWGN_HIP(hipStreamSynchronize(exec.st));
             }
@@ -246,6 +261,7 @@ void sw_server_s::run() {
         if (rc != SW_OK) {
             worker_err = step_err;
             // a runtime failure ends every frame in flight with that status
+            again.clear();
             for (Active& a : active) {
                 a.t->status = rc;
                 a.t->done = true;

@@ -6,6 +6,7 @@
 // FP32 key with a fixed operation order and ties to the lower index; sorts
 // compare full (key, value) pairs that are unique; the only atomics are
 // integer OR / ADD whose results do not depend on order.
+#include "swgn_frame.h"
 #include "swgn_impl.h"
 #include "swgn_launch.h"
 #include "swgn_setup.h"
@@ -610,6 +611,82 @@ __global__ void k_ell(int nn, int ell_w, const int* __restrict__ frow_ptr, const
     ell_col[t] = in ? fcol[f] : 0;
 }
 
+// The whole-solve kernel's view of the rows: per workgroup of 8 WAVES rows
+// the foreign nodes its slots touch, ascending (at most kHalo are kept),
+// and per slot the column's place among the workgroup's local nodes
+// (its own rows first, then the foreign ones; kLocal: the slot is not in use). One workgroup per tile: the
+// columns are marked in a bitmap over the nodes, a column's place is its rank.
+// need becomes the largest number of foreign nodes, or 2^20 when they or the
+// slots from 16 on of 8 rows are more than the kernel holds.
+template <int WAVES>
+__global__ void __launch_bounds__(256) k_pcg_local(int nn, int ell_w, const uint32_t* __restrict__ ell_blk,
+                                                   const int* __restrict__ ell_col, uint16_t* __restrict__ loc,
+                                                   int* __restrict__ halo, int* __restrict__ halo_n,
+                                                   int* __restrict__ need) {
+    constexpr int kRows = pcg_rows(WAVES), kLocal = pcg_local(WAVES), kHalo = pcg_halo(WAVES);
+    constexpr int kWords = 1024;                        // 32768 nodes
+    __shared__ uint32_t bits[kWords];
+    __shared__ int before[kWords];
+    __shared__ int sums[256];
+    const int row0 = blockIdx.x * kRows, row1 = min(nn, row0 + kRows);
+    const int nslots = (row1 - row0) * ell_w;
+    const size_t slot0 = (size_t)row0 * ell_w;
+    const int words = (nn + 31) / 32;
+    for (int w = threadIdx.x; w < kWords; w += 256) bits[w] = 0;
+    __syncthreads();
+    for (int t = threadIdx.x; t < nslots; t += 256) {
+        const int c = ell_col[slot0 + t];
+        if (ell_blk[slot0 + t] != 0xffffffffu && (c < row0 || c >= row1)) atomicOr(&bits[c >> 5], 1u << (c & 31));
+    }
+    __syncthreads();
+    // exclusive prefix of the words' counts, four consecutive words per thread
+    const int w0 = 4 * threadIdx.x;
+    int own = 0;
+    for (int q = 0; q < 4; ++q) own += __popc(bits[w0 + q]);
+    sums[threadIdx.x] = own;
+    __syncthreads();
+    for (int d = 1; d < 256; d <<= 1) {
+        const int v = (int)threadIdx.x >= d ? sums[threadIdx.x - d] : 0;
+        __syncthreads();
+        sums[threadIdx.x] += v;
+        __syncthreads();
+    }
+    int run = sums[threadIdx.x] - own;
+    for (int q = 0; q < 4; ++q) {
+        before[w0 + q] = run;
+        run += __popc(bits[w0 + q]);
+    }
+    __syncthreads();
+    const int total = sums[255];
+    if (threadIdx.x == 0) {
+        halo_n[blockIdx.x] = min(total, kHalo);
+        atomicMax(need, total > kHalo ? 1 << 20 : total);
+    }
+    if (threadIdx.x < WAVES) {
+        int nfar = 0;
+        for (int j = 0; j < 8; ++j) {
+            const int row = row0 + 8 * threadIdx.x + j;
+            for (int f = 16; row < row1 && f < ell_w; ++f)
+                nfar += ell_blk[(size_t)row * ell_w + f] != 0xffffffffu ? 1 : 0;
+        }
+        if (nfar > kPcgFar) atomicMax(need, 1 << 20);
+    }
+    for (int w = threadIdx.x; w < words; w += 256) {
+        int rank = before[w];
+        for (uint32_t m = bits[w]; m != 0u; m &= m - 1u, ++rank)
+            if (rank < kHalo) halo[(size_t)blockIdx.x * kHalo + rank] = 32 * w + __ffs(m) - 1;
+    }
+    for (int t = threadIdx.x; t < nslots; t += 256) {
+        const int c = ell_col[slot0 + t];
+        int l = kLocal;                              // not in use
+        if (ell_blk[slot0 + t] != 0xffffffffu) {
+            l = (c >= row0 && c < row1) ? c - row0
+                                        : kRows + before[c >> 5] + __popc(bits[c >> 5] & ((1u << (c & 31)) - 1u));
+        }
+        loc[slot0 + t] = (uint16_t)min(l, kLocal);
+    }
+}
+
 // Where each upper block is stored in the explicit full rows of the product:
 // slot_u[b] = ELL slot of block b in its row, slot_t[b] = ELL slot of its
 // transpose in the column's row (-1 for a diagonal block, set by the caller).
@@ -724,6 +801,15 @@ void launch_ell(int nn, int ell_w, const int* frow_ptr, const uint32_t* fblk, co
 void launch_ell_slots(int nn, int ell_w, const uint32_t* ell_blk, int* slot_u, int* slot_t, hipStream_t st) {
     const int n = nn * ell_w;
     hipLaunchKernelGGL(k_ell_slots, dim3((n + 255) / 256), dim3(256), 0, st, nn, ell_w, ell_blk, slot_u, slot_t);
+}
+
+void launch_pcg_local(int waves, int nn, int ell_w, const uint32_t* ell_blk, const int* ell_col, uint16_t* loc,
+                      int* halo, int* halo_n, int* need, hipStream_t st) {
+    const dim3 grid(cdiv(nn, pcg_rows(waves)));
+    if (waves == 4)
+        hipLaunchKernelGGL(k_pcg_local<4>, grid, dim3(256), 0, st, nn, ell_w, ell_blk, ell_col, loc, halo, halo_n, need);
+    else
+        hipLaunchKernelGGL(k_pcg_local<8>, grid, dim3(256), 0, st, nn, ell_w, ell_blk, ell_col, loc, halo, halo_n, need);
 }
 
 void launch_in_edge_store(int n, const uint32_t* val, int* in_list, hipStream_t st) {

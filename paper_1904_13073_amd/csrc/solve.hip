@@ -34,43 +34,12 @@
 #include "swgn_frame.h"
 #include "swgn_impl.h"
 #include "swgn_launch.h"
+#include "swgn_pcg.h"
 
 namespace swgn {
 
 namespace {
 
-
-__device__ void update_node_x(const FrameDesc& a, int k, const float (&x)[6]) {
-    float3 w = make_float3(x[0], x[1], x[2]);
-    float3 tau = make_float3(x[3], x[4], x[5]);
-    float th = sqrtf(dot3(w, w));
-    Q4 e;
-    if (th < 1e-8f) {
-        e = Q4{1.f, 0.5f * w.x, 0.5f * w.y, 0.5f * w.z};
-    } else {
-        float sn, cs;
-        sincosf(0.5f * th, &sn, &cs);
-        float sc = sn / th;
-        e = Q4{cs, sc * w.x, sc * w.y, sc * w.z};
-    }
-    float en = sqrtf(((e.w * e.w + e.x * e.x) + e.y * e.y) + e.z * e.z);
-    e = Q4{e.w / en, e.x / en, e.y / en, e.z / en};
-    Q4 r = q4(a.rq[k]);
-    float4 t4 = a.tt[k];
-    float3 t = make_float3(t4.x, t4.y, t4.z);
-    float4 p = a.pref[k];
-    float3 c = add3(qrot(r.w, make_float3(r.x, r.y, r.z), make_float3(p.x, p.y, p.z)), t);
-    Q4 rn = qmul(e, r);
-    float nr = sqrtf(((rn.w * rn.w + rn.x * rn.x) + rn.y * rn.y) + rn.z * rn.z);
-    float sg = rn.w < 0.f ? -1.f : 1.f;
-    rn = Q4{sg * rn.w / nr, sg * rn.x / nr, sg * rn.y / nr, sg * rn.z / nr};
-    float3 tn = add3(add3(qrot(e.w, make_float3(e.x, e.y, e.z), sub3(t, c)), c), tau);
-    bool fin = fabsf(rn.w) <= 1.f && fabsf(tn.x) < INFINITY && fabsf(tn.y) < INFINITY && fabsf(tn.z) < INFINITY;
-    if (!fin) atomicOr(a.flags, 4);
-    a.rq[k] = f4(rn);
-    a.tt[k] = make_float4(tn.x, tn.y, tn.z, 0.f);
-    node_tables(p, rn, tn, a.dq, a.cl, k);
-}
 
 __device__ void update_node(const FrameDesc& a, int k) {
     float x[6];
@@ -78,25 +47,6 @@ __device__ void update_node(const FrameDesc& a, int k) {
     for (int j = 0; j < 6; ++j) x[j] = a.x[6 * k + j];
     update_node_x(a, k, x);
 }
-
-// Index map of the next iteration: tile `tile` of a launch with `ntiles`
-// tiles for the stream clears its share of the pixels.
-__device__ __forceinline__ void reset_index_map(const FrameDesc& a, int tile, int ntiles) {
-    const int chunk = cdiv(a.npx, ntiles);
-    const int p0 = tile * chunk, p1 = min(a.npx, p0 + chunk);
-    for (int p = p0 + (int)threadIdx.x; p < p1; p += (int)blockDim.x) a.zbuf[p] = ~0ull;
-}
-
-// The node update of a stream's last PCG finish, inside the finishing lane
-// group (lane c holds component c of x_k): the group's 6 entries of x to
-// every lane, lane 0 moves node k.
-__device__ __forceinline__ void update_from_lanes(const FrameDesc& a, int k, int c, float xc) {
-    float x[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) x[j] = bcast8(xc, j);
-    if (c == 0 && k < a.nn) update_node_x(a, k, x);
-}
-
 
 // The start of PCG (pcg_start_lane), 8 lanes per node, 32 nodes per
 // workgroup, as a launch of its own: the solve forms it inside the assembly
@@ -133,10 +83,6 @@ __global__ void __launch_bounds__(kSolveBlock) k_pcg_init(Batch b) {
 // rho_k = 0 stops the iteration: alpha = beta = 0 leave x, r and z as they are.
 // Every workgroup sums the same partials in the same order, so all take the
 // same scalars; workgroup 0 of the stream keeps rho_k for the next finish.
-struct PcgScalars {
-    float alpha, beta;
-};
-
 // Four sums of partials at once, each in the fixed shape of a 256-thread
 // reduction whatever the workgroup size (thread t < 256 adds part[t],
 // part[t + 256], ..., then the wave sums, then the 4 waves in order): one
@@ -178,37 +124,10 @@ __device__ __forceinline__ Sum4 reduce4_parts256(const double* __restrict__ p0, 
 __device__ __forceinline__ PcgScalars pcg_scalars(const FrameDesc& a, int k, bool keep, double* sh) {
     const int par = k & 1, nsp = spmv_parts(a);
     const Sum4 t = reduce4_parts256(by_parity(a.part_rho, par), solve_parts(a), by_parity(a.part_c, par), nsp, sh);
-    const double rho = t.s[0], c1 = t.s[1], c2 = t.s[2], c3 = t.s[3];
-    const bool stop = (rho == 0.0);
-    const float beta = (k > 0 && !stop) ? (float)(rho / a.sc[(k - 1) & 1]) : 0.f;
-    const double bd = (double)beta;
-    const double pq = (c1 + bd * c2) + (bd * bd) * c3;
-    const float alpha = stop ? 0.f : (float)(rho / pq);
+    const double rho = t.s[0];
+    const PcgScalars s = pcg_scalars_of(k, rho, t.s[1], t.s[2], t.s[3], k > 0 ? a.sc[(k - 1) & 1] : 0.0);
     if (keep && threadIdx.x == 0) a.sc[par] = rho;
-    return PcgScalars{alpha, beta};
-}
-
-// The finish of iteration k for one component of one node (8 lanes per node,
-// component c = lane & 7 < 6, lanes 6 and 7 carry zeros): p_k, r_{k+1},
-// z_{k+1} = M r_{k+1} (FP64 sum of the node's 6 entries, read by shuffles
-// within the lane group) and x_{k+1}. A fused step repeats the same
-// operations for the nodes of its rows' columns, so both agree bit for bit.
-struct Finished {
-    float p, r, z, x;
-};
-
-__device__ __forceinline__ Finished finish_lane(float zk, float pprev, float uk, float vk, float rk, float xk,
-                                                const double (&mrow)[6], PcgScalars s, int base) {
-    Finished f;
-    f.p = zk + s.beta * pprev;
-    const float q = uk + s.beta * vk;
-    f.x = xk + s.alpha * f.p;
-    f.r = rk - s.alpha * q;
-    double zc = 0.0;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) zc += mrow[j] * (double)bcast8(f.r, j);
-    f.z = (float)zc;
-    return f;
+    return s;
 }
 
 // Finish of iteration k = b.pcg_it: x_{k+1}, r_{k+1}, z_{k+1}, p_k; partials
@@ -247,7 +166,7 @@ __global__ void __launch_bounds__(kSolveBlock) k_pcg_finish(Batch b) {
         const int n = at.tile * NPG * kSolveNodes + g * kSolveNodes + (threadIdx.x >> 3);
         const bool on = (n < a.nn) && (c < 6);
         const int t = 6 * n + c;
-        const Finished f = finish_lane(zc[g], pc[g], uc[g], vc[g], rc[g], xc[g], mrow[g], s, base);
+        const Finished f = finish_lane(zc[g], pc[g], uc[g], vc[g], rc[g], xc[g], mrow[g], s);
         double rz = 0.0, rr = 0.0;
         if (on) {
             a.x[t] = f.x;
@@ -348,7 +267,7 @@ __device__ __forceinline__ void slot_vectors(const float (&cv)[5], const double 
         for (int j = 0; j < 6; ++j) mr[j] = sub < 6 ? m[j] : 0.0;
         const bool on = sub < 6;
         const Finished fin = finish_lane(on ? cv[0] : 0.f, on ? cv[1] : 0.f, on ? cv[2] : 0.f, on ? cv[3] : 0.f,
-                                         on ? cv[4] : 0.f, 0.f, mr, s, base);
+                                         on ? cv[4] : 0.f, 0.f, mr, s);
         zv = fin.z;
         pv = fin.p;
     } else {
@@ -404,18 +323,6 @@ __device__ __forceinline__ RowAcc row_products(const FrameDesc& a, int i, int ro
     av += xchg<16>(av);
     av += xchg<32>(av);
     return RowAcc{au, av};
-}
-
-// Sum of a value that only lanes 0-5 hold (every other lane holds +0): the
-// value the wave butterfly 32, 16, ..., 1 gives, valid in lanes 0-7. Its
-// first three steps only add +0, which turns -0 into +0, as one addition of
-// +0 does.
-__device__ __forceinline__ double low6_sum(double v) {
-    v += 0.0;
-    v += xchg<4>(v);
-    v += xchg<2>(v);
-    v += xchg<1>(v);
-    return v;
 }
 
 // Stores u_i, v_i of a row and returns the row's three products
@@ -526,7 +433,7 @@ __global__ void __launch_bounds__(kStepBlock) k_pcg_step(Batch b) {
     if (prod) row_prefetch<true>(a, i, row, lane, sd);
     const PcgScalars s = pcg_scalars(a, k, at.tile == 0, sh);
     if (wave == 0) {
-        const Finished f = finish_lane(zk, pp, uk, vk, rk, xk, mrow, s, base);
+        const Finished f = finish_lane(zk, pp, uk, vk, rk, xk, mrow, s);
         double rz = 0.0, rr = 0.0;
         if (on) {
             a.x[t] = f.x;

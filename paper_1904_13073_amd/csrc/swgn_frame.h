@@ -45,6 +45,19 @@ constexpr int kSpmvPart = 8;
 static_assert(kSpmvRows == kSpmvPart && kStepNodes == kSpmvPart && kStepNodes == kSolvePart,
               "a product or fused-step workgroup writes exactly one partial of each kind");
 constexpr int kNodeBlock = 256;
+// Whole linear solve in one launch (pcg.hip). A workgroup has 4 or 8 waves of
+// 8 block rows and holds a bounded number of nodes, its rows and the columns
+// they touch (sets of one node per lane group; 400 bytes of LDS each), at most
+// 24 slots per row and, per wave, kPcgFar slots from 16 on. With 4 waves two
+// workgroups share a CU and a stream spreads over more CUs; with 8 waves each
+// foreign column serves more rows and there are fewer workgroups to meet.
+constexpr int kPcgMaxSlots = 24;
+constexpr int kPcgFar = 16;
+constexpr int kPcgCopies = 4;         // of the parts' exchange words, each for every fourth workgroup
+__host__ __device__ constexpr int pcg_rows(int waves) { return 8 * waves; }
+__host__ __device__ constexpr int pcg_local(int waves) { return waves == 4 ? 160 : 320; }
+__host__ __device__ constexpr int pcg_halo(int waves) { return pcg_local(waves) - pcg_rows(waves); }
+
 constexpr int kRigidSurfels = 1024;   // surfels per rigid-system workgroup (4 per thread)
 
 
@@ -113,6 +126,16 @@ struct FrameDesc {
     const int *in_ptr, *in_list;
     const uint32_t* ell_blk;      // [nn][ell_w] upper block id (bit 31: used transposed), ~0 = padding
     const int* ell_col;           // [nn][ell_w] column node
+    // resident: the whole-solve kernel's layouts for workgroups of 4 ([0]) and
+    // 8 ([1]) waves: local columns ([nn][ell_w], a column's place among its
+    // workgroup's nodes), the foreign nodes of each workgroup ([tiles][pcg_halo],
+    // halo_n of them); and the exchange words (null when the node set fits
+    // neither): per parity kPcgCopies of the parts' sums (pcg_part_word) and
+    // u, v ([nn][6][2])
+    const uint16_t *loc4, *loc8;
+    const int *halo4, *halo8, *halo_n4, *halo_n8;
+    unsigned long long *xpart, *xuv;
+    long long pcg_wait;           // longest wait of a workgroup for the others, in 10 ns
     const int *slot_u, *slot_t;   // [nb] ELL slot of each upper block and of its transpose (-1: diagonal)
     // resident: capture of one iteration (null unless requested)
     int* dbg_corr;
@@ -161,17 +184,30 @@ __device__ __forceinline__ bool visible(const FrameDesc& d, int i) {
 // kStPcgStep does both in one launch (finish of iteration i - 1, products of i).
 enum Stage {
     kStDepth = 0, kStWarp, kStCorr, kStAsmSeg, kStPcgInit, kStSpmv, kStUpdate, kStNodeUpdate, kStAsmFold,
-    kStRigidWarp, kStRigidSys, kStRigidSolve, kStRigidCompose, kStPcgStep, kStStatsOut, kNumStages
+    kStRigidWarp, kStRigidSys, kStRigidSolve, kStRigidCompose, kStPcgStep, kStStatsOut,
+    kStPcgSolve, kNumStages
 };
-// timing slot (sw_frame_stats.stage_us) of each stage; fused PCG steps take
-// slot 3 (the segment stage has no launch of its own)
-inline int stage_slot(int stage) { return stage == kStPcgStep ? kStAsmSeg : stage < kStRigidCompose ? stage : 11; }
+// timing slot (sw_frame_stats.stage_us) of each stage; fused PCG steps and
+// whole solves take slot 3 (the segment stage has no launch of its own)
+inline int stage_slot(int stage) { return stage == kStPcgStep || stage == kStPcgSolve ? kStAsmSeg : stage < kStRigidCompose ? stage : 11; }
 
 __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ inline int corr_tiles(const FrameDesc& d) { return d.npack; }
 __host__ __device__ inline int solve_parts(const FrameDesc& d) { return cdiv(d.nn, kSolvePart); }
 __host__ __device__ inline int solve_tiles(const FrameDesc& d) { return cdiv(d.nn, kSolveNodes); }
 __host__ __device__ inline int spmv_parts(const FrameDesc& d) { return cdiv(d.nn, kSpmvPart); }
+
+__host__ __device__ inline int pcg_tiles(const FrameDesc& d, int waves) { return cdiv(d.nn, pcg_rows(waves)); }
+// Exchange words of one copy of the parts' sums (a multiple of 4 KiB and a
+// bit, so that the copies start in different memory channels), and where word
+// q (0..7) of a part lies: four parts together, in pairs of words, so that a
+// 16-byte load per lane reads whole lines.
+__host__ __device__ inline size_t pcg_part_words(const FrameDesc& d) {
+    return (((size_t)cdiv(solve_parts(d), 4) * 32 + 511) & ~size_t(511)) + 64;
+}
+__host__ __device__ inline size_t pcg_part_word(int part, int q) {
+    return (size_t)(part >> 2) * 32 + (size_t)((q >> 1) * 8 + (part & 3) * 2 + (q & 1));
+}
 
 // Launch variant of a stage: bit 0 = tile order (kOrderXcd), bit 1 = the
 // wider geometry of the stage where it has one (2 block rows per product
@@ -197,6 +233,7 @@ inline int stage_tiles(int stage, const FrameDesc& d, int variant = 0) {
         case kStSpmv: return cdiv(d.nn, kSpmvRows);
         case kStUpdate: return cdiv(d.nn, (variant & kVarWide) ? 2 * kSolveNodes : kSolveNodes);
         case kStPcgStep: return cdiv(d.nn, kStepNodes);
+        case kStPcgSolve: return pcg_tiles(d, (variant & kVarWide) ? 8 : 4);
         case kStNodeUpdate: return cdiv(d.nn > d.npx ? d.nn : d.npx, kNodeBlock);
         case kStRigidWarp: return cdiv(d.ns, kWarpBlock);
         case kStRigidSys: return cdiv(d.ns, kRigidSurfels);
@@ -213,8 +250,9 @@ struct Batch {
     int pcg_it;                   // PCG iteration of this launch (products of it; finish of it, or of
                                   // it - 1 in a fused step)
     int order;                    // kOrderXcd: tiles in XCD-contiguous order
-    int wide;                     // the stage's wider geometry (kVarWide)
+    int wide;                     // the stage's wider geometry (kVarWide); whole solves: 8 waves per workgroup
     int splat;                    // some stream renders splats (the kernels with splat code run)
+    int sets;                     // whole solves: most sets of local nodes of a workgroup
     int update;                   // a stream's last PCG finish in this launch also moves its nodes
     int off[kMaxBatch + 1];       // stream s owns tiles [off[s], off[s+1])
     const FrameDesc* d[kMaxBatch];
@@ -354,6 +392,9 @@ __device__ __forceinline__ void pcg_start_lane(const FrameDesc& a, int k, int ro
 void launch_frame_stage(int stage, const Batch& b, const DepthIn* depth, hipStream_t st);
 void launch_asm_stage(int stage, const Batch& b, hipStream_t st);
 void launch_solve_stage(int stage, const Batch& b, void* stats_out, hipStream_t st);
+void launch_pcg_solve(const Batch& b, hipStream_t st);
+// workgroups of so many waves of the whole-solve kernel that a device of so many CUs holds at once
+int pcg_resident_workgroups(int waves, int cus);
 
 // Bytes per stream written by the statistics copy: kMaxIters IterStats, the
 // failure flags, kMaxIters RigidStats.

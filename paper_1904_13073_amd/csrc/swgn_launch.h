@@ -42,6 +42,13 @@ void launch_ell_slots(int nn, int ell_w, const uint32_t* ell_blk, int* slot_u, i
 void launch_ell(int nn, int ell_w, const int* frow_ptr, const uint32_t* fblk, const int* fcol, uint32_t* ell_blk,
                 int* ell_col, hipStream_t st);
 
+// the whole-solve kernel's local columns and foreign nodes per workgroup of
+// 4 or 8 waves;
+// need (zero before) becomes the largest number of foreign nodes, or a number
+// beyond any when a wave's slots from 16 on are more than the kernel holds
+void launch_pcg_local(int waves, int nn, int ell_w, const uint32_t* ell_blk, const int* ell_col, uint16_t* loc,
+                      int* halo, int* halo_n, int* need, hipStream_t st);
+
 // node state and capture helpers
 void launch_offlist(int nb, const int* blk_row, const int* col_idx, int* offlist, hipStream_t st);
 void launch_nodes_from_se3(int nn, const float* se3, const float4* pref, float4* rq, float4* tt, float4* dq,
