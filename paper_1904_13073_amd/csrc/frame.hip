@@ -1022,8 +1022,9 @@ __global__ void k_nodes_from_se3(int nn, const float* __restrict__ se3, const fl
     node_tables(pref[k], r, t, dq, cl, k);
 }
 
+// [R | t] of node k to row caller[k] of out (which may be host memory).
 __global__ void k_node_se3_out(int nn, const float4* __restrict__ rq, const float4* __restrict__ tt,
-                               float* __restrict__ out) {
+                               const int* __restrict__ caller, float4* __restrict__ out) {
     int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nn) return;
     float4 q = rq[k];
@@ -1031,13 +1032,10 @@ __global__ void k_node_se3_out(int nn, const float4* __restrict__ rq, const floa
     double n2 = w * w + x * x + y * y + z * z;
     double s = 2.0 / n2;
     float4 t = tt[k];
-    float* o = out + 12 * k;
-    o[0] = (float)(1 - s * (y * y + z * z)); o[1] = (float)(s * (x * y - w * z)); o[2] = (float)(s * (x * z + w * y));
-    o[3] = t.x;
-    o[4] = (float)(s * (x * y + w * z)); o[5] = (float)(1 - s * (x * x + z * z)); o[6] = (float)(s * (y * z - w * x));
-    o[7] = t.y;
-    o[8] = (float)(s * (x * z - w * y)); o[9] = (float)(s * (y * z + w * x)); o[10] = (float)(1 - s * (x * x + y * y));
-    o[11] = t.z;
+    float4* o = out + 3 * (size_t)caller[k];
+    o[0] = make_float4((float)(1 - s * (y * y + z * z)), (float)(s * (x * y - w * z)), (float)(s * (x * z + w * y)), t.x);
+    o[1] = make_float4((float)(s * (x * y + w * z)), (float)(1 - s * (x * x + z * z)), (float)(s * (y * z - w * x)), t.y);
+    o[2] = make_float4((float)(s * (x * z - w * y)), (float)(s * (y * z + w * x)), (float)(1 - s * (x * x + y * y)), t.z);
 }
 
 __global__ void k_export_index_map(int npx, const unsigned long long* __restrict__ z, int* __restrict__ out) {
@@ -1081,8 +1079,8 @@ void launch_nodes_from_se3(int nn, const float* se3, const float4* pref, float4*
     hipLaunchKernelGGL(k_nodes_from_se3, dim3((nn + 255) / 256), dim3(256), 0, st, nn, se3, pref, rq, tt, dq, cl);
 }
 
-void launch_node_se3_out(int nn, const float4* rq, const float4* tt, float* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_node_se3_out, dim3((nn + 255) / 256), dim3(256), 0, st, nn, rq, tt, out);
+void launch_node_se3_out(int nn, const float4* rq, const float4* tt, const int* caller, float4* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_node_se3_out, dim3((nn + 255) / 256), dim3(256), 0, st, nn, rq, tt, caller, out);
 }
 
 void launch_export_index_map(int npx, const unsigned long long* z, int* out, hipStream_t st) {

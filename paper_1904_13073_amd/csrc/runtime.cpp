@@ -85,7 +85,6 @@ Executor::~Executor() {
     drop_graph();
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
     if (stats_host) (void)hipHostFree(stats_host);
-    if (stats_dev) (void)hipFree(stats_dev);
     if (own_stream && st) (void)hipStreamDestroy(st);
 }
 
@@ -154,8 +153,8 @@ void Executor::init(void* hip_stream) {
     SWGN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
     if (device < kMaxDevices)
         pcg_resident = std::min(4 * pcg_resident_workgroups(4, cus), 8 * pcg_resident_workgroups(8, cus));
-    SWGN_HIP(hipMalloc(reinterpret_cast<void**>(&stats_dev), (size_t)kStatsOutBytes * kMaxBatch));
     SWGN_HIP(hipHostMalloc(&stats_host, (size_t)kStatsOutBytes * kMaxBatch, hipHostMallocDefault));
+    SWGN_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&stats_dev), stats_host, 0));
 }
 
 int Executor::variant_of(int stage, int64_t rows) const {
@@ -953,14 +952,13 @@ void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std
     }
 }
 
-// Brings back the statistics of the streams' finished frames (one launch,
-// one copy, one synchronisation), fills stats / status and restores the node
+// Brings back the statistics of the streams' finished frames (one launch that
+// writes them to pinned host memory, one synchronisation), fills stats / status and restores the node
 // state of every stream whose frame failed numerically.
 void enqueue_collect(Executor& ex, const std::vector<sw_stream>& ss) {
     const int n = (int)ss.size();
     std::vector<int> its(n, 0), ev;
     run_stage(ex, kStStatsOut, ss, its, 0, nullptr, false, ev);
-    SWGN_HIP(hipMemcpyAsync(ex.stats_host, ex.stats_dev, (size_t)kStatsOutBytes * n, hipMemcpyDeviceToHost, ex.st));
 }
 
 sw_status collect_frames(Executor& ex, const std::vector<sw_stream>& ss, const float* stage_us,
@@ -1427,15 +1425,22 @@ sw_status sw_get_node_se3(sw_stream s, float* out, int32_t capacity) {
     if (!s->graph_set) return fail(s->err, SW_ESTATE, "node graph not set");
     if (!out || capacity < s->h.nn) return fail(s->err, SW_EINVAL, "output capacity below n_nodes");
     return guarded(s->err, [&]() -> sw_status {
-        Arena tmp;
-        const int nn = s->h.nn;
-        float* d = tmp.alloc<float>(12 * (size_t)nn);
-        launch_node_se3_out(nn, s->h.rq, s->h.tt, d, s->exec.st);
-        std::vector<float> lib((size_t)12 * nn);
-        SWGN_HIP(hipMemcpyAsync(lib.data(), d, sizeof(float) * 12 * nn, hipMemcpyDeviceToHost, s->exec.st));
+        // the kernel writes the caller's rows straight into pinned host memory
+        // that the stream keeps (an allocation and a copy per call took 150 us)
+        const size_t nn = (size_t)s->h.nn, bytes = 48 * nn;
+        if (s->se3_host_nodes < nn) {
+            if (s->se3_host) (void)hipHostFree(s->se3_host);
+            s->se3_host = nullptr;
+            s->se3_host_nodes = 0;
+            SWGN_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->se3_host), bytes, hipHostMallocDefault));
+            s->se3_host_nodes = nn;
+        }
+        float4* dst = nullptr;
+        SWGN_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&dst), s->se3_host, 0));
+        launch_node_se3_out((int)nn, s->h.rq, s->h.tt, s->d_node_id, dst, s->exec.st);
+        SWGN_HIP(hipGetLastError());
         SWGN_HIP(hipStreamSynchronize(s->exec.st));
-        for (int k = 0; k < nn; ++k)            // back to the caller's node order
-            std::memcpy(out + 12 * (size_t)s->node_perm[k], &lib[12 * (size_t)k], 12 * sizeof(float));
+        std::memcpy(out, s->se3_host, bytes);
         return SW_OK;
     });
 }

@@ -68,13 +68,13 @@ private:
 };
 
 // A HIP stream plus what a solve needs besides the streams' own memory: the
-// device and pinned host slots of the statistics copy (kMaxBatch streams)
-// and timing events.
+// pinned host slots the statistics are written to (kMaxBatch streams) and
+// timing events.
 struct Executor {
     hipStream_t st = nullptr;
     bool own_stream = false;
-    char* stats_dev = nullptr;
     void* stats_host = nullptr;
+    char* stats_dev = nullptr;            // the device's address of stats_host
     std::vector<hipEvent_t> events;
     // launch variant per stage (kVarXcd | kVarWide bits), per shape bucket of
     // a batch; chosen by the autotuner, a size rule where it has not run
@@ -203,6 +203,9 @@ struct sw_stream_s {
     int* d_node_id = nullptr;             // [nn] node_perm on the device
     int* d_node_inv = nullptr;            // [nn] node_inv on the device
 
+    float* se3_host = nullptr;            // pinned, node transforms for the caller; room for se3_host_nodes
+    size_t se3_host_nodes = 0;
+
     // captured iteration (allocated only when the config asks for a capture)
     int* dbg_index = nullptr;
     float *dbg_H = nullptr, *dbg_g = nullptr, *dbg_x = nullptr, *dbg_J = nullptr;
@@ -211,6 +214,7 @@ struct sw_stream_s {
     ~sw_stream_s() {
         if (h_pinned) (void)hipHostFree(h_pinned);
         if (fcount_host) (void)hipHostFree(fcount_host);
+        if (se3_host) (void)hipHostFree(se3_host);
     }
 };
 

@@ -53,7 +53,7 @@ void launch_pcg_local(int waves, int nn, int ell_w, const uint32_t* ell_blk, con
 void launch_offlist(int nb, const int* blk_row, const int* col_idx, int* offlist, hipStream_t st);
 void launch_nodes_from_se3(int nn, const float* se3, const float4* pref, float4* rq, float4* tt, float4* dq,
                            float4* cl, hipStream_t st);
-void launch_node_se3_out(int nn, const float4* rq, const float4* tt, float* out, hipStream_t st);
+void launch_node_se3_out(int nn, const float4* rq, const float4* tt, const int* caller, float4* out, hipStream_t st);
 void launch_export_index_map(int npx, const unsigned long long* z, int* out, hipStream_t st);
 void launch_positions_to_f4(int n, const float* pos, float4* out, hipStream_t st);
 
