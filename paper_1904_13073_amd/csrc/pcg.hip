@@ -15,8 +15,10 @@
 // the memory side: 1.5 us for 2 workgroups and 1.8 us for 56 over 8 XCDs, of
 // 4.4 us per iteration), then the wave's own chain of products (0.8 us), sums
 // and publication (0.55 us), scalars (0.2 us) and finishes (0.6 us). Measured,
-// 10 iterations: 640x480, 1,788 nodes: 54.6 us, as 11 step-wise launches
-// 84 us; 16 uneven streams, 41,000 nodes: 244 us against 385 us.
+// 10 iterations: 640x480, 1,788 nodes: 51.9 us, as 11 step-wise launches
+// 84 us; 16 uneven streams, 41,000 nodes: 225 us against 385 us. Of the 52 us
+// about 9 are the way to the first product (all loads of the blocks issued
+// before any is waited for: 54.6 -> 51.9 us).
 //
 // Why 32 rows per workgroup (4 waves): alone on its SIMD a wave runs its chain
 // fastest and a stream spreads over more CUs (4.4 us per iteration against
@@ -214,7 +216,6 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
     const int row0 = at.tile * kRows;
     const uint16_t* loc = kWaves == 4 ? a.loc4 : a.loc8;
     const int* halo = (kWaves == 4 ? a.halo4 : a.halo8) + at.tile * kHalo;
-    const int nlocal = kRows + gld((kWaves == 4 ? a.halo_n4 : a.halo_n8) + at.tile);
     const int part = at.tile * kWaves + wave;
     if (tid == 0) stalled = 0;
 
@@ -229,8 +230,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
 #pragma unroll                                         // row, then foreign columns
     for (int m = 0; m < kSets; ++m) {
         const int l = m * kRows + gi;
-        node[m] = m == 0 ? (row0 + gi < a.nn ? row0 + gi : -1)
-                         : (l < nlocal ? gld(halo + l - kRows) : -1);
+        node[m] = m == 0 ? (row0 + gi < a.nn ? row0 + gi : -1) : gld(halo + l - kRows);
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -251,6 +251,26 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
         }
     }
     double rho_own = part < nparts ? gld(a.part_rho.b0 + part) : 0.0;
+    // the local nodes' state, which needs their numbers: z_0 = M r_0, p_{-1} = 0,
+    // x = 0 (written by the fold), the inverses
+    int word[kSets];                                   // the lane's exchange words in set m; -1: none
+    float z0[kSets], r0[kSets];
+    double mr[kSets][6];
+#pragma unroll
+    for (int m = 0; m < kSets; ++m) {
+        word[m] = -1;
+        z0[m] = r0[m] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) mr[m][j] = 0.0;    // (a row past the last node stays zero)
+        if (node[m] >= 0 && sub < 6) {
+            word[m] = (6 * node[m] + sub) * 2;
+            z0[m] = gld(a.z.b0 + 6 * node[m] + sub);
+            r0[m] = gld(a.r.b0 + 6 * node[m] + sub);
+#pragma unroll
+            for (int j = 0; j < 6; ++j) mr[m][j] = gld(a.Minv + (size_t)node[m] * 36 + sub * 6 + j);
+        }
+    }
+    const int nlocal = kRows + gld((kWaves == 4 ? a.halo_n4 : a.halo_n8) + at.tile);
     // a slot that is not in use is a zero block on the zero node; local columns packed 9 bits each
     unsigned col[8];
     unsigned farx[2];                                  // rows' blocks from slot 16 on in LDS, 8 bits each
@@ -285,35 +305,21 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
             }
         }
     }
-    // local nodes: z_0 = M r_0, p_{-1} = 0, x = 0 (written by the fold), the inverses
-    float z = 0.f, p = 0.f, r = 0.f, x = 0.f;
-    int word[kSets];                                   // the lane's exchange words in set m; -1: none
+    float z = z0[0], p = 0.f, r = r0[0], x = 0.f;
 #pragma unroll
     for (int m = 0; m < kSets; ++m) {
         const int l = m * kRows + gi;
-        float z0 = 0.f, r0 = 0.f;
-        word[m] = -1;
-        double mr[6];
-#pragma unroll
-        for (int j = 0; j < 6; ++j) mr[j] = 0.0;       // (a row past the last node stays zero)
-        if (node[m] >= 0 && sub < 6) {
-            word[m] = (6 * node[m] + sub) * 2;
-            z0 = gld(a.z.b0 + 6 * node[m] + sub);
-            r0 = gld(a.r.b0 + 6 * node[m] + sub);
-#pragma unroll
-            for (int j = 0; j < 6; ++j) mr[j] = gld(a.Minv + (size_t)node[m] * 36 + sub * 6 + j);
-        }
         if (sub < 6) {
 #pragma unroll
-            for (int j = 0; j < 6; ++j) minv[l * 36 + sub * 6 + j] = mr[j];
+            for (int j = 0; j < 6; ++j) minv[l * 36 + sub * 6 + j] = mr[m][j];
         }
-        put_vec(vec + l * kVecStride, sub, z0, 0.f);
-        res[l * 8 + sub] = r0;
-        if (m == 0) { z = z0; r = r0; }
+        put_vec(vec + l * kVecStride, sub, z0[m], 0.f);
+        res[l * 8 + sub] = r0[m];
     }
     if (tid < 4) vec[kLocal * kVecStride + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (tid < 18) far[kWaves * kPcgFar][tid] = make_float2(0.f, 0.f);
     double rho_prev = 0.0;
+    float4 nq = make_float4(0.f, 0.f, 0.f, 0.f), nt = nq, npos = nq;
     const size_t part_words = pcg_part_words(a);      // of one copy
     const int copy = at.tile % kPcgCopies;
     const long long t_limit = a.pcg_wait;
@@ -402,6 +408,11 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
                 xchg_store(xp + (lane >> 3) * part_words + pcg_part_word(part, lane & 7), tag,
                            (unsigned)((lane & 1) ? bits >> 32 : bits));
             }
+        }
+        if (last && sub == 0 && row0 + gi < a.nn) {    // (for the node update, while the others' words are on their way)
+            nq = gld4(a.rq + row0 + gi);
+            nt = gld4(a.tt + row0 + gi);
+            npos = gld4(a.pref + row0 + gi);
         }
         // the index map of the next Gauss-Newton iteration (this one's is done
         // with), while the others' words are on their way
@@ -541,7 +552,10 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
     const double rr = wave_sum(own ? (double)r * (double)r : 0.0);
     if (lane == 0 && part < nparts) by_parity(e.part_rr, iters & 1)[part] = rr;
     if (own) e.x[6 * (row0 + gi) + sub] = x;
-    update_from_lanes(e, row0 + gi, sub, x);
+    float xs[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) xs[j] = bcast8(x, j);
+    if (sub == 0 && row0 + gi < e.nn) update_node_x(e, row0 + gi, xs, nq, nt, npos);
 }
 
 }  // namespace

@@ -612,7 +612,7 @@ __global__ void k_ell(int nn, int ell_w, const int* __restrict__ frow_ptr, const
 }
 
 // The whole-solve kernel's view of the rows: per workgroup of 8 WAVES rows
-// the foreign nodes its slots touch, ascending (at most kHalo are kept),
+// the foreign nodes its slots touch, ascending (at most kHalo are kept, the rest is -1),
 // and per slot the column's place among the workgroup's local nodes
 // (its own rows first, then the foreign ones; kLocal: the slot is not in use). One workgroup per tile: the
 // columns are marked in a bitmap over the nodes, a column's place is its rank.
@@ -671,6 +671,7 @@ __global__ void __launch_bounds__(256) k_pcg_local(int nn, int ell_w, const uint
         }
         if (nfar > kPcgFar) atomicMax(need, 1 << 20);
     }
+    for (int r = min(total, kHalo) + threadIdx.x; r < kHalo; r += 256) halo[(size_t)blockIdx.x * kHalo + r] = -1;
     for (int w = threadIdx.x; w < words; w += 256) {
         int rank = before[w];
         for (uint32_t m = bits[w]; m != 0u; m &= m - 1u, ++rank)

@@ -45,7 +45,7 @@ __device__ void update_node(const FrameDesc& a, int k) {
     float x[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) x[j] = a.x[6 * k + j];
-    update_node_x(a, k, x);
+    update_node_x(a, k, x, a.rq[k], a.tt[k], a.pref[k]);
 }
 
 // The start of PCG (pcg_start_lane), 8 lanes per node, 32 nodes per

@@ -129,7 +129,7 @@ struct FrameDesc {
     // resident: the whole-solve kernel's layouts for workgroups of 4 ([0]) and
     // 8 ([1]) waves: local columns ([nn][ell_w], a column's place among its
     // workgroup's nodes), the foreign nodes of each workgroup ([tiles][pcg_halo],
-    // halo_n of them); and the exchange words (null when the node set fits
+    // halo_n of them, the rest -1); and the exchange words (null when the node set fits
     // neither): per parity kPcgCopies of the parts' sums (pcg_part_word) and
     // u, v ([nn][6][2])
     const uint16_t *loc4, *loc8;

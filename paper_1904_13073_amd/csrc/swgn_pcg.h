@@ -9,7 +9,9 @@
 
 namespace swgn {
 
-__device__ __forceinline__ void update_node_x(const FrameDesc& a, int k, const float (&x)[6]) {
+// T_k <- Delta_k(x) o T_k from the node's state q, t4 and reference position p.
+__device__ __forceinline__ void update_node_x(const FrameDesc& a, int k, const float (&x)[6], float4 q4f, float4 t4,
+                                              float4 p) {
     float3 w = make_float3(x[0], x[1], x[2]);
     float3 tau = make_float3(x[3], x[4], x[5]);
     float th = sqrtf(dot3(w, w));
@@ -24,10 +26,8 @@ __device__ __forceinline__ void update_node_x(const FrameDesc& a, int k, const f
     }
     float en = sqrtf(((e.w * e.w + e.x * e.x) + e.y * e.y) + e.z * e.z);
     e = Q4{e.w / en, e.x / en, e.y / en, e.z / en};
-    Q4 r = q4(a.rq[k]);
-    float4 t4 = a.tt[k];
+    Q4 r = q4(q4f);
     float3 t = make_float3(t4.x, t4.y, t4.z);
-    float4 p = a.pref[k];
     float3 c = add3(qrot(r.w, make_float3(r.x, r.y, r.z), make_float3(p.x, p.y, p.z)), t);
     Q4 rn = qmul(e, r);
     float nr = sqrtf(((rn.w * rn.w + rn.x * rn.x) + rn.y * rn.y) + rn.z * rn.z);
@@ -56,7 +56,7 @@ __device__ __forceinline__ void update_from_lanes(const FrameDesc& a, int k, int
     float x[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) x[j] = bcast8(xc, j);
-    if (c == 0 && k < a.nn) update_node_x(a, k, x);
+    if (c == 0 && k < a.nn) update_node_x(a, k, x, a.rq[k], a.tt[k], a.pref[k]);
 }
 
 
