@@ -207,21 +207,6 @@ __device__ __forceinline__ void fold_block(const FrameDesc& in, bool capture, bo
     }
 }
 
-// Clears the tags of the whole-solve kernel's exchange words, both parities:
-// u and v of node k by its lane group, the sums of the tile's two parts by
-// the tile's first threads. The kernel boundary orders them before the solve.
-__device__ __forceinline__ void clear_exchange(const FrameDesc& in, int tile, int k, int g) {
-    if (in.xuv == nullptr) return;
-    if (k >= 0 && g < 12) {
-#pragma unroll
-        for (int par = 0; par < 2; ++par) gst(in.xuv + ((size_t)par * in.nn + k) * 12 + g, 0ull);
-    }
-    constexpr int kParts = kFoldGroups / kSolvePart, kSets = 2 * kPcgCopies;   // (parity, copy)
-    const int t = threadIdx.x, part = tile * kParts + t / (8 * kSets);
-    if (t < 8 * kSets * kParts && part < solve_parts(in))
-        gst(in.xpart + ((t >> 3) % kSets) * pcg_part_words(in) + pcg_part_word(part, t & 7), 0ull);
-}
-
 // Diagonal blocks first, one per 16-lane group (node order, kFoldGroups per
 // workgroup); then the off-diagonal ones, which have few segments each, one
 // per 4-lane group (kFoldOffGroups per workgroup).
@@ -237,7 +222,7 @@ __global__ void __launch_bounds__(256) k_asm_fold(Batch wl) {
         const int gi = at.tile * kFoldGroups + grp;
         const bool active = gi < in.nn;
         fold_block<16>(in, capture, active, true, active ? in.row_ptr[gi] : 0, g, rho, rr);
-        clear_exchange(in, at.tile, active ? gi : -1, g);
+        if (at.tile == 0 && threadIdx.x == 0 && in.xepoch != nullptr) gst(in.xepoch, gld(in.xepoch) + 1);
         // partials of r_0.z_0 and r_0.r_0 per 8 nodes, summed in the layout of
         // a wave of 8 nodes x 8 lanes (the start kernel's)
         if (g < 8) {

@@ -30,7 +30,9 @@
 // the upper half and 32 bits of payload in the lower, written and read by
 // relaxed agent-scope atomics: a word is its own flag, so no fence, no cache
 // write-back and no second round trip is needed. The fold that precedes the
-// solve clears the tags. Words are double-buffered by iteration parity: a
+// solve counts it, and a tag is the iteration in the range of that count, so
+// nothing has to be cleared (2^32 / kPcgTags solves later a tag comes again,
+// but every word a solve reads was written by the solve before). Words are double-buffered by iteration parity: a
 // workgroup writes iteration i + 2 only after it has every part of iteration
 // i + 1, which their owners publish after they have read all of iteration i.
 //
@@ -318,6 +320,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
     }
     if (tid < 4) vec[kLocal * kVecStride + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (tid < 18) far[kWaves * kPcgFar][tid] = make_float2(0.f, 0.f);
+    const unsigned tag0 = (unsigned)__builtin_amdgcn_readfirstlane(gld(a.xepoch)) * (unsigned)kPcgTags + 1u;
     double rho_prev = 0.0;
     float4 nq = make_float4(0.f, 0.f, 0.f, 0.f), nt = nq, npos = nq;
     const size_t part_words = pcg_part_words(a);      // of one copy
@@ -334,7 +337,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
         const int lane = tl % kWave, sub = lane & 7, grp = lane >> 3, gi = tl >> 3, quad = lane & 3;
         const int sl = sub < 6 ? sub : 0;
         const int par = i & 1;
-        const unsigned tag = (unsigned)i + 1u;
+        const unsigned tag = tag0 + (unsigned)i;
         const bool last = i == iters - 1;
         u64* xp = a.xpart + (size_t)par * kPcgCopies * part_words;
         u64* xu = a.xuv + (size_t)par * a.nn * 12;

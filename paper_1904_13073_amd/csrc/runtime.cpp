@@ -732,6 +732,10 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
             h.xuv = G.alloc<unsigned long long>(2 * (size_t)nn * 12);
         }
     }
+            h.xepoch = G.alloc<int>(1);
+            launch_fill_i32(reinterpret_cast<int*>(h.xpart), (int)(4 * kPcgCopies * pcg_part_words(h)), 0, st);
+            launch_fill_i32(reinterpret_cast<int*>(h.xuv), 48 * nn, 0, st);
+            launch_fill_i32(h.xepoch, 1, 0, st);
     h.pcg_wait = pcg_wait_limit();
     int* slot_u = G.alloc<int>(h.nb);
     int* slot_t = G.alloc<int>(h.nb);

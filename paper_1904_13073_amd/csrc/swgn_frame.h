@@ -60,6 +60,7 @@ __host__ __device__ constexpr int pcg_halo(int waves) { return pcg_local(waves) 
 
 constexpr int kRigidSurfels = 1024;   // surfels per rigid-system workgroup (4 per thread)
 
+constexpr int kPcgTags = 8192;        // tags per solve (more than kMaxPcg)
 
 // Per-step statistics of the rigid alignment.
 struct RigidStats {
@@ -145,6 +146,7 @@ struct FrameDesc {
     float* depth;                 // copy of a host depth image
     float4* nmap;                 // (normal, depth) per pixel
     unsigned long long* zbuf;     // index map: (z bits << 32 | surfel) per pixel
+    int* xepoch;                  // solves so far (the fold before each counts it): the words' tags follow from it
     int* flags;                   // [4] failure bits of the frame
     IterStats* stats;             // [kMaxIters]
     float4 *rq_bak, *tt_bak;      // node state at the start of the frame
