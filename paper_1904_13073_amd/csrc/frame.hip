@@ -163,53 +163,59 @@ __global__ void __launch_bounds__(kWarpBlock) k_warp_zbuf(Batch b) {
 // segment is a run of surfels whose nodes number at most 5 in all). Each
 // thread forms its surfel's row [J | r] in LDS: node block k at the position
 // of its node in the segment's ascending node list (pos4), r in column 30.
-// Then each wave takes segments of the pack and sums the 31 x 31 Gram matrix
-// [J | r]^T [J | r] over the segment's surfels with the 32x32x2 FP32 MFMA,
-// the sum over surfels being the MFMA's k dimension (two surfels per
-// instruction; the A and B operands are the same register: lane = component,
-// half-wave = surfel). The 6x6 sub-blocks of the node pairs that share a
-// surfel (seg_mask), J^T r and r^T r are stored for the block fold. Jacobian
-// rows leave the chip only when an iteration is captured.
+// Then the waves sum the 31 x 31 Gram matrices [J | r]^T [J | r] over each
+// segment's surfels with the 16x16x4 FP32 MFMA, the sum over surfels being
+// the MFMA's k dimension (segment_grams). The 6x6 sub-blocks of the node
+// pairs that share a surfel (seg_mask), J^T r and r^T r are stored for the
+// block fold. Jacobian rows leave the chip only when an iteration is captured.
 // ---------------------------------------------------------------------------
 // LDS row stride in floats: 31 entries (J at 5 node positions, r), odd so
 // that a row per lane is conflict-free. The MFMA reads 32 columns per row;
 // column 31 runs into the next row (or the slack after the last one) and
 // only feeds Gram entries with an index of 31, which are discarded.
 constexpr int kRowPad = 31;
-constexpr int kStageFloats = 576;    // per wave: a segment's whole output (at most 36 x 15 + 32 floats)
-constexpr int kStageSlots = kStageFloats + kWave;   // and one discard word per lane
+// Staging of the Gram outputs: whole segments (at most 36 x 15 + 32 floats
+// each, consecutive in memory) up to this many floats.
+constexpr int kStageFloats = 2560;
+constexpr int kLongSegment = 32;      // rows per segment on average, from which tiles are dealt
 
-// Code of accumulator element t of lane l in a segment's Gram tile (element
-// G[i][j], j = l % 32, i = (t / 4) * 8 + (l / 32) * 4 + t % 4): for a node-pair
-// block (i, j < 30, pa = i / 6 <= pb = j / 6) its pair bit
-// 5 pa - pa (pa - 1) / 2 + pb - pa (bits 0-3) and its position
-// (i % 6) * 6 + j % 6 in the 6x6 sub-block (bits 4-9); for J^T r and r^T r
-// (j = 30, i <= 30) bit field 15 and i; 0xffff for elements not kept.
+// A segment's Gram matrix in 16 x 16 tiles: 0 = rows 0-15, columns 0-15; 1 =
+// rows 0-15, columns 16-31; 2 = rows 16-31, columns 16-31. Element t (0..3)
+// of lane l of a tile is G[i][j], i = its first row + 4 (l / 16) + t, j = its
+// first column + l % 16. Code of an element: for a node-pair block (i, j < 30,
+// pa = i / 6 <= pb = j / 6) its pair bit 5 pa - pa (pa - 1) / 2 + pb - pa
+// (bits 0-3) and its position (i % 6) * 6 + j % 6 in the 6x6 sub-block (bits
+// 4-9); for J^T r and r^T r (j = 30, i <= 30) bit field 15 and i; 0xffff for
+// elements not kept. The diagonal block of node position 2 crosses tiles: its
+// rows 16, 17 and columns 12-15 lie in the tile that is not formed and equal
+// (bit for bit, a product's factors being all that trade places) the
+// mirrored elements of tile 1.
 struct GramCodes {
-    uint16_t c[kWave][16];
+    uint16_t c[3][kWave][4];
 };
 
 constexpr GramCodes make_gram_codes() {
     GramCodes g{};
-    for (int l = 0; l < kWave; ++l)
-        for (int t = 0; t < 16; ++t) {
-            const int i = (t / 4) * 8 + (l / 32) * 4 + t % 4, j = l % 32;
-            uint16_t code = 0xffff;
-            if (i < 30 && j < 30) {
-                const int pa = i / 6, pb = j / 6;
-                if (pa <= pb) code = (uint16_t)((5 * pa - pa * (pa - 1) / 2 + pb - pa) | (((i % 6) * 6 + j % 6) << 4));
-            } else if (j == 30 && i <= 30) {
-                code = (uint16_t)(15 | (i << 4));
+    for (int tile = 0; tile < 3; ++tile)
+        for (int l = 0; l < kWave; ++l)
+            for (int t = 0; t < 4; ++t) {
+                const int i = (tile == 2 ? 16 : 0) + 4 * (l / 16) + t, j = (tile == 0 ? 0 : 16) + l % 16;
+                uint16_t code = 0xffff;
+                if (i < 30 && j < 30) {
+                    const int pa = i / 6, pb = j / 6;
+                    if (pa <= pb)
+                        code = (uint16_t)((5 * pa - pa * (pa - 1) / 2 + pb - pa) | (((i % 6) * 6 + j % 6) << 4));
+                } else if (j == 30 && i <= 30) {
+                    code = (uint16_t)(15 | (i << 4));
+                }
+                g.c[tile][l][t] = code;
             }
-            g.c[l][t] = code;
-        }
     return g;
 }
 
 __constant__ GramCodes kGramCodes = make_gram_codes();
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
+typedef float f32x4m __attribute__((ext_vector_type(4)));
 
 // d r / d xi_k for the 4 nodes of a matched surfel: the closed form of
 // N^T dF/db(b; v) w_k s_k M(q_k, c_k). With P = N c_r, Q = N c_d, PV = P (0,v)
@@ -397,98 +403,213 @@ __device__ __forceinline__ int extra_before(const unsigned long long* planes, in
     return c;
 }
 
-// Segment Gram matrices of the pack's rows, one wave per segment. Accumulator
-// element t of lane l is G[i][j], j = l % 32, i = (t / 4) * 8 + (l / 32) * 4 +
-// t % 4. The output slot of each element: the rank of its node pair among the
-// segment's pairs x 36 + position in the 6x6 sub-block; J^T r and r^T r after
-// the sub-blocks. The whole output is staged in LDS and stored as whole lines;
-// with `more` (later splat rounds) segments without a marked row are skipped
-// and the sums are added to the stored ones (the same lanes stored those words);
-// with `planes` the rows are the compacted extra rows from slot `base` on, a
-// segment's being those of its surfels in order.
-__device__ __forceinline__ void segment_grams(const FrameDesc& d, const float* rows, float4* stage, int tile, int p0,
-                                              const unsigned long long* more,
-                                              const unsigned long long* planes = nullptr, int base = 0) {
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const int comp = lane & 31, half = lane >> 5;
-    const int g0 = gld(d.pack_seg + tile), g1 = gld(d.pack_seg + tile + 1);
+// One 16 x 16 tile of the Gram matrix of n rows from `first` (16 components
+// from column ca by 16 from column cb), four rows per MFMA: lane = component,
+// quarter-wave = row. The next 16 rows are read while the MFMAs of the last 16
+// run; only the rows of the last, partial 16 are tested against n.
+template <bool SAME>
+__device__ __forceinline__ f32x4m gram_tile(const float* rows, int first, int n, int ca, int cb) {
+    const int lane = threadIdx.x % kWave, k = lane >> 4, c = lane & 15;
+    const float* pa = rows + (first + k) * kRowPad + ca + c;
+    const float* pb = rows + (first + k) * kRowPad + cb + c;
+    f32x4m acc = {0.f, 0.f, 0.f, 0.f};
+    float va[4], vb[4];
+    auto fetch = [&](int m) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            va[q] = pa[(m + 4 * q) * kRowPad];
+            vb[q] = SAME ? va[q] : pb[(m + 4 * q) * kRowPad];
+        }
+    };
+    int m = 0;
+    if (n >= 16) {
+        fetch(0);
+        for (; m + 32 <= n; m += 16) {
+            float xa[4], xb[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { xa[q] = va[q]; xb[q] = vb[q]; }
+            fetch(m + 16);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[q], xb[q], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[q], vb[q], acc, 0, 0, 0);
+        m += 16;
+    }
+    if (m < n) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool in = m + 4 * q + k < n;
+            const int o = in ? (m + 4 * q) * kRowPad : 0 - k * kRowPad;   // (a row of the segment)
+            const float ea = pa[o], eb = SAME ? ea : pb[o];
+            va[q] = in ? ea : 0.f;
+            vb[q] = in ? eb : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (m + 4 * q >= n) break;                         // uniform over the wave
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[q], vb[q], acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
+// The three tiles of a segment of few rows at once (each row read once).
+__device__ __forceinline__ void gram_tiles(const float* rows, int first, int n, f32x4m (&acc)[3]) {
+    const int lane = threadIdx.x % kWave, k = lane >> 4, c = lane & 15;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) acc[t] = f32x4m{0.f, 0.f, 0.f, 0.f};
+    for (int m = 0; m < n; m += 16) {
+        float lo[4], hi[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = m + 4 * q + k;
+            const float* p = rows + (first + (row < n ? row : 0)) * kRowPad + c;   // (a row of the segment)
+            const float el = p[0], eh = p[16];
+            lo[q] = row < n ? el : 0.f;
+            hi[q] = row < n ? eh : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (m + 4 * q >= n) break;                         // uniform over the wave
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(lo[q], lo[q], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(lo[q], hi[q], acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(hi[q], hi[q], acc[2], 0, 0, 0);
+        }
+    }
+}
+
+// Elements of tile tl to their slots of a segment's output: the rank of the
+// node pair among the segment's pairs x 36 + position in the 6x6 sub-block;
+// J^T r and r^T r after the sub-blocks.
+__device__ __forceinline__ void put_tile(float* out, int tl, uint2 codes, uint32_t mask, f32x4m acc) {
+    const int lane = threadIdx.x % kWave;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const uint32_t code = ((t & 2 ? codes.y : codes.x) >> (16 * (t & 1))) & 0xffffu;
+        const uint32_t bit = code & 15u;
+        // pairs of the segment below the element's (all of them below J^T r)
+        const int below = 36 * __builtin_popcount(bit == 15u ? mask : (mask & ((1u << bit) - 1u)));
+        const bool keep = code != 0xffffu && (bit == 15u || ((mask >> bit) & 1u) != 0u);
+        const int pos = (int)(code >> 4);
+        if (keep) out[below + pos] = acc[t];
+        // rows 16, 17 of the diagonal block of position 2 from its columns 16, 17
+        if (tl == 1 && keep && 4 * (lane >> 4) + t >= 12 && (lane & 15) < 2)
+            out[below + (pos % 6) * 6 + pos / 6] = acc[t];
+    }
+}
+
+// Whole lines from the staging to memory, or added to what is there.
+__device__ __forceinline__ void put_lines(float* dst, const float* stage, int size, bool add, int t, int nt) {
+    float4* out = reinterpret_cast<float4*>(dst);
+    const float4* in = reinterpret_cast<const float4*>(stage);
+    for (int q = t; q < size / 4; q += nt) {
+        const float4 c4 = in[q];
+        if (add) {
+            const float4 a = gld4(out + q);
+            gst4(out + q, make_float4(a.x + c4.x, a.y + c4.y, a.z + c4.z, a.w + c4.w));
+        } else {
+            gst4(out + q, c4);
+        }
+    }
+}
+
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Gram matrices of segments [g0, g1), whose rows are in LDS (row 0: surfel p0):
+// the symmetric 32 x 32 matrix of a
+// segment as three 16 x 16 tiles. Where the segments are long, the tiles of
+// several segments are dealt to the waves in turn: the longest chain of
+// dependent MFMAs is a quarter of what one wave per segment and the 32x32x2
+// instruction gave, and a pack of few segments keeps all waves busy. Where
+// they are short (kLongSegment; 32 was fastest of 8, 16, 32, 48 and always
+// short: 640x480, 45 rows per segment: 24.7 us against 26.1 us short; 4,000
+// nodes, 24 rows: 29.5 us against 34.2 us dealt), a wave takes a whole segment, so that its
+// rows are read once and no barrier is needed. Sums are the same bit for bit
+// either way, and as those of the 32x32x2 instruction (tested instruction
+// against instruction). Outputs are staged in LDS and stored as whole lines.
+// With `planes` (splat streams) the rows are the compacted extra rows from
+// slot `base` on, a segment's being those of its surfels in order; segments
+// without one are skipped and the sums are added to the stored ones (stored
+// by this workgroup, a barrier ago). Every thread of the workgroup calls
+// this; ends with a barrier.
+__device__ __forceinline__ void segment_grams(const FrameDesc& d, const float* rows, float* stage, int g0, int g1,
+                                              int p0, const unsigned long long* planes = nullptr, int base = 0) {
+    constexpr int kWavesPerBlock = kCorrBlock / kWave;
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     // the descriptor's pointers read once (the stores below could alias it)
     const int* seg_start = d.seg_start;
     const uint16_t* seg_mask = d.seg_mask;
     const uint32_t* seg_off = d.seg_off;
     float* part = d.part;
-    float* sg = reinterpret_cast<float*>(stage);
-    // this lane's 16 accumulator elements: the pair's bit as a mask (bit 31
-    // for J^T r and r^T r, which follow the sub-blocks; 0 for an element that
-    // is not kept) and the offset. An element's output slot is then
-    // 36 x (pairs of the segment below its pair) + offset, where the pairs
-    // below bit 31 are all of them; a dropped element goes to the lane's
-    // discard word, so every element is one unconditional LDS store.
-    uint32_t bm[16];
-    int off[16];
-    {
-        const uint4* codes = reinterpret_cast<const uint4*>(kGramCodes.c[lane]);
-        const uint4 q0 = codes[0], q1 = codes[1];
-        const uint32_t cw[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-#pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            const uint32_t code = (cw[t >> 1] >> (16 * (t & 1))) & 0xffffu;
-            const uint32_t bit = code & 15u;
-            bm[t] = code == 0xffffu ? 0u : (bit == 15u ? 0x80000000u : (1u << bit));
-            off[t] = (int)(code >> 4);
-        }
-    }
-    for (int seg = g0 + wave; seg < g1; seg += kCorrBlock / kWave) {
-        int s0 = gld(seg_start + seg) - p0, s1 = gld(seg_start + seg + 1) - p0;
-        if (planes != nullptr) {
+    const bool add = planes != nullptr;
+    const bool deal = gld(seg_start + g1) - gld(seg_start + g0) >= kLongSegment * (g1 - g0);   // (uniform)
+    for (int g = g0; g < g1;) {
+        // lane l: segment g + l of the pack
+        const int gl = min(g + lane, g1 - 1);
+        int s0 = gld(seg_start + gl) - p0, s1 = gld(seg_start + gl + 1) - p0;
+        const uint32_t off = gld(seg_off + gl), end = gld(seg_off + gl + 1);
+        const uint32_t mask = gld(seg_mask + gl);
+        if (add) {
             s0 = min(max(extra_before(planes, s0) - base, 0), kCorrPack);
             s1 = min(max(extra_before(planes, s1) - base, 0), kCorrPack);
-            if (s0 == s1) continue;                            // uniform over the wave
-        } else if (more != nullptr) {
-            bool any = false;
-            for (int m = s0 + lane; m < s1; m += kWave) any |= ((more[m / kWave] >> (m % kWave)) & 1ull) != 0;
-            if (__ballot(any) == 0) continue;                  // uniform over the wave
         }
-        const uint32_t mask = gld(seg_mask + seg);          // (issued before the sums)
-        float4* out = reinterpret_cast<float4*>(part + gld(seg_off + seg));
-        f32x16 acc;
+        if (!deal) {
+            uint2 codes[3];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) acc[t] = 0.f;
-        for (int m0 = s0; m0 < s1; m0 += 16) {
-            float v[8];
+            for (int t = 0; t < 3; ++t) codes[t] = *reinterpret_cast<const uint2*>(kGramCodes.c[t][lane]);
+            float* out = stage + wave * (kStageFloats / kWavesPerBlock);
+            const int cnt = min(kWave, g1 - g);
+            for (int sg = wave; sg < cnt; sg += kWavesPerBlock) {
+                const int first = __builtin_amdgcn_readlane(s0, sg), n = __builtin_amdgcn_readlane(s1, sg) - first;
+                if (add && n == 0) continue;                   // uniform over the wave
+                const uint32_t mk = (uint32_t)__builtin_amdgcn_readlane((int)mask, sg);
+                const uint32_t o0 = (uint32_t)__builtin_amdgcn_readlane((int)off, sg);
+                const int size = (int)((uint32_t)__builtin_amdgcn_readlane((int)end, sg) - o0);
+                f32x4m acc[3];
+                gram_tiles(rows, first, n, acc);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int sr = m0 + 2 * q + half;   // surfel of this half-wave
-                const float e = rows[(sr < s1 ? sr : s0) * kRowPad + comp];   // (a row of the segment)
-                v[q] = sr < s1 ? e : 0.f;
+                for (int t = 0; t < 3; ++t) put_tile(out, t, codes[t], mk, acc[t]);
+                wave_lds_fence();
+                put_lines(part + o0, out, size, add, lane, kWave);
+                wave_lds_fence();
             }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q], v[q], acc, 0, 0, 0);
+            g += cnt;
+            continue;
         }
-        const int npr = __builtin_popcount(mask);
-        const int size = 36 * npr + 32;
-        const uint32_t mk = mask | 0x80000000u;
-        // the whole output staged in LDS, then stored as whole float4 lines
-#pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            const int sl = 36 * __builtin_popcount(mask & (bm[t] - 1u)) + off[t];
-            sg[(mk & bm[t]) != 0u ? sl : kStageFloats + lane] = acc[t];
+        // the segments whose outputs fit the staging together
+        const uint32_t off0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+        const int cnt = __popcll(__ballot(g + lane < g1 && end - off0 <= (uint32_t)kStageFloats));
+        for (int task = wave; task < 3 * cnt; task += kWavesPerBlock) {
+            const int sg = task / 3, tl = task - 3 * sg;
+            const int first = __builtin_amdgcn_readlane(s0, sg), n = __builtin_amdgcn_readlane(s1, sg) - first;
+            if (add && n == 0) continue;                       // uniform over the wave
+            const uint2 codes = *reinterpret_cast<const uint2*>(kGramCodes.c[tl][lane]);   // (there when the sums are)
+            const f32x4m acc = tl == 1 ? gram_tile<false>(rows, first, n, 0, 16)
+                                       : gram_tile<true>(rows, first, n, 8 * tl, 8 * tl);
+            put_tile(stage + ((uint32_t)__builtin_amdgcn_readlane((int)off, sg) - off0), tl, codes,
+                     (uint32_t)__builtin_amdgcn_readlane((int)mask, sg), acc);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (more != nullptr || planes != nullptr) {
-            for (int q = lane; q < size / 4; q += kWave) {
-                const float4 a = gld4(out + q), c4 = stage[q];
-                gst4(out + q, make_float4(a.x + c4.x, a.y + c4.y, a.z + c4.z, a.w + c4.w));
+        __syncthreads();
+        if (add) {
+            for (int sg = 0; sg < cnt; ++sg) {
+                if (__builtin_amdgcn_readlane(s0, sg) == __builtin_amdgcn_readlane(s1, sg)) continue;
+                const uint32_t o0 = (uint32_t)__builtin_amdgcn_readlane((int)off, sg);
+                put_lines(part + o0, stage + (o0 - off0), (int)((uint32_t)__builtin_amdgcn_readlane((int)end, sg) - o0),
+                          true, threadIdx.x, kCorrBlock);
             }
         } else {
-            for (int q = lane; q < size / 4; q += kWave) gst4(out + q, stage[q]);
+            put_lines(part + off0, stage, (int)((uint32_t)__builtin_amdgcn_readlane((int)end, cnt - 1) - off0), false,
+                      threadIdx.x, kCorrBlock);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __syncthreads();
+        g += cnt;
     }
+    if (!deal) __syncthreads();
 }
 
 // A captured iteration's live surfel (caller order): position in dbg_live[0,
@@ -513,11 +634,29 @@ __global__ void __launch_bounds__(kCorrBlock, 4) k_corr_gram(Batch b) {
     __shared__ int shi[16];
     __shared__ unsigned long long planes[2 * (kCorrBlock / kWave)];   // splat: extra rows per surfel
     __shared__ float rows[kCorrPack * kRowPad + 8];
-    __shared__ float4 stage4[kCorrBlock / kWave][kStageSlots / 4];
+    __shared__ __align__(16) float stage[kStageFloats];
     const Where at = locate(b);
     const FrameDesc& d = *b.d[at.s];
-    const bool capture = (b.it[at.s] == d.debug_iter) && d.dbg_corr != nullptr;
-    const int p0 = gld(d.pack_start + at.tile), p1 = gld(d.pack_start + at.tile + 1);
+    const bool capture_it = (b.it[at.s] == d.debug_iter) && d.dbg_corr != nullptr;
+    // in a launch of few packs, one of many short segments is shared by
+    // corr_split workgroups, each with a run of its segments and their surfels; the first takes all of the
+    // pack's surfels for the sums of the pack
+    const int split = b.wide ? d.corr_split : 1;
+    const int pack = at.tile / split, share = at.tile - pack * split;
+    int g0 = gld(d.pack_seg + pack), g1 = gld(d.pack_seg + pack + 1);
+    int p0 = gld(d.pack_start + pack), p1 = gld(d.pack_start + pack + 1);
+    if (split > 1) {
+        const int per = cdiv(g1 - g0, split);
+        const int ga = g0 + share * per, gb = min(g1, ga + per);
+        if (ga >= gb) return;
+        g0 = ga;
+        g1 = gb;
+        if (share > 0) {
+            p0 = gld(d.seg_start + ga);
+            p1 = gld(d.seg_start + gb);
+        }
+    }
+    const bool capture = capture_it && share == 0;
     const int i = p0 + (int)threadIdx.x;
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const bool live = i < p1;
@@ -590,7 +729,7 @@ __global__ void __launch_bounds__(kCorrBlock, 4) k_corr_gram(Batch b) {
                 }
             }
         }
-        tile_sums(d, rows, sh, shi, at.tile, e_own, npair);
+        tile_sums(d, rows, sh, shi, pack, e_own, npair);
         // round 0: row 0 of the factor of every surfel with a pair
         {
 #pragma unroll
@@ -612,7 +751,7 @@ __global__ void __launch_bounds__(kCorrBlock, 4) k_corr_gram(Batch b) {
             put_row(d, rows, threadIdx.x, live, i, Jw, Jt, r);
             __syncthreads();
             if (capture) capture_rows(d, rows, p0, p1);
-            segment_grams(d, rows, stage4[wave], at.tile, p0, nullptr);
+            segment_grams(d, rows, stage, g0, g1, p0);
         }
         // the surfels' further factor rows (1 to 3 each), compacted in surfel
         // order into the rows, so that a segment's are contiguous; their Gram
@@ -650,7 +789,7 @@ __global__ void __launch_bounds__(kCorrBlock, 4) k_corr_gram(Batch b) {
                 }
             }
             __syncthreads();
-            segment_grams(d, rows, stage4[wave], at.tile, p0, nullptr, planes, base);
+            segment_grams(d, rows, stage, g0, g1, p0, planes, base);
         }
         return;
     }
@@ -709,15 +848,19 @@ __global__ void __launch_bounds__(kCorrBlock, 4) k_corr_gram(Batch b) {
         capture_live(d, org, wp);
         if (matched) d.dbg_corr[pix] = org;
     }
-    double e = block_sum((double)r * (double)r, sh);   // (synchronises the rows too)
-    int cnt = wave_sumi(matched ? 1 : 0);
-    if ((threadIdx.x % kWave) == 0) shi[threadIdx.x / kWave] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int c = 0;
-        for (int q = 0; q < (int)(blockDim.x / kWave); ++q) c += shi[q];
-        gst(d.part_e + at.tile, e);
-        gst(d.part_n + at.tile, c);
+    if (share == 0) {                                          // uniform
+        const double e = block_sum((double)r * (double)r, sh);
+        const int cnt = wave_sumi(matched ? 1 : 0);
+        if ((threadIdx.x % kWave) == 0) shi[threadIdx.x / kWave] = cnt;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int c = 0;
+            for (int q = 0; q < (int)(blockDim.x / kWave); ++q) c += shi[q];
+            gst(d.part_e + pack, e);
+            gst(d.part_n + pack, c);
+        }
+    } else {
+        __syncthreads();                                       // (the rows are written)
     }
     if (capture) {
         // the wave's rows as whole 128-byte lines, two rows per store
@@ -729,8 +872,7 @@ __global__ void __launch_bounds__(kCorrBlock, 4) k_corr_gram(Batch b) {
             if (rr < nrow) dst[rr * 32 + c] = c < 31 ? rows[(base + rr) * kRowPad + c] : 0.f;
         }
     }
-    // segment Gram matrices, one wave per segment
-    segment_grams(d, rows, stage4[wave], at.tile, p0, nullptr);
+    segment_grams(d, rows, stage, g0, g1, p0);
 }
 
 // ---------------------------------------------------------------------------

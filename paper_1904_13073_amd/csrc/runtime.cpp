@@ -660,6 +660,8 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     h.offlist = offlist;
 
     build_segments(s, h, key, set_start, fpos, s->nsets, sidx, row_ptr, col_idx, G, tmp);
+    // (the disc splats' second pass needs the whole pack in one workgroup)
+    h.corr_split = h.splat ? 1 : std::min(kCorrSplit, std::max(1, cdiv(h.nseg, std::max(1, h.npack) * kCorrSegs)));
 
     // in-edges of every node (j with the node in N_j), ascending j
     const int npad_i = pow2_at_least(8 * (int64_t)nn, 1024);
@@ -730,12 +732,12 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
         if (s->pcg_sets4 > 0 || s->pcg_sets8 > 0) {
             h.xpart = G.alloc<unsigned long long>(2 * kPcgCopies * pcg_part_words(h));
             h.xuv = G.alloc<unsigned long long>(2 * (size_t)nn * 12);
-        }
-    }
             h.xepoch = G.alloc<int>(1);
             launch_fill_i32(reinterpret_cast<int*>(h.xpart), (int)(4 * kPcgCopies * pcg_part_words(h)), 0, st);
             launch_fill_i32(reinterpret_cast<int*>(h.xuv), 48 * nn, 0, st);
             launch_fill_i32(h.xepoch, 1, 0, st);
+        }
+    }
     h.pcg_wait = pcg_wait_limit();
     int* slot_u = G.alloc<int>(h.nb);
     int* slot_t = G.alloc<int>(h.nb);
@@ -798,8 +800,13 @@ void run_stage(Executor& ex, int stage, const std::vector<sw_stream>& ss, const 
     int64_t rows = 0;
     for (int i = 0; i < b.n; ++i)
         if (its[i] >= 0) rows += ss[i]->h.nn;
-    const int variant =
-        stage == kStPcgSolve ? (ex.pcg_waves == 8 ? kVarWide : 0) : ex.variant_of(stage, rows);
+    int variant = stage == kStPcgSolve ? (ex.pcg_waves == 8 ? kVarWide : 0) : ex.variant_of(stage, rows);
+    if (stage == kStCorr) {
+        int64_t packs = 0;
+        for (int i = 0; i < b.n; ++i)
+            if (its[i] >= 0) packs += corr_tiles(ss[i]->h);
+        variant = (variant & ~kVarWide) | (packs <= kCorrFewPacks ? kVarWide : 0);
+    }
     b.order = (variant & kVarXcd) ? kOrderXcd : kOrderLinear;
     b.wide = (variant & kVarWide) ? 1 : 0;
     if (stage == kStPcgSolve)

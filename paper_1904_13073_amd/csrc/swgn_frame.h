@@ -29,6 +29,15 @@ constexpr int kCorrBlock = 256;
 // Jacobian rows (28.8 KB) and the waves' output staging (10 KB) let four
 // workgroups share a CU.
 constexpr int kCorrPack = 232;
+// Where a launch has at most kCorrFewPacks packs (half of what the chip holds
+// at once), workgroups share a pack, at most kCorrSplit of them, so that each
+// takes kCorrSegs segments on average (10.7k surfels, 2,000 nodes: 47 packs of
+// 70 segments, 25.8 us alone, 11.5, 10.6 and 11.3 us with 4, 8 and 16
+// segments each). A launch that fills the chip is slower for the surfels then
+// seen twice (16 streams, 4,400 packs: 96.7 us, 132 us with 8 segments each).
+constexpr int kCorrSegs = 8;
+constexpr int kCorrSplit = 16;
+constexpr int kCorrFewPacks = 512;
 constexpr int kFoldGroups = 16;       // diagonal blocks per fold workgroup (16 lanes each)
 constexpr int kFoldOffLanes = 4;      // lanes per off-diagonal block
 constexpr int kFoldOffGroups = 256 / kFoldOffLanes;   // off-diagonal blocks per fold workgroup
@@ -51,6 +60,7 @@ constexpr int kNodeBlock = 256;
 // 24 slots per row and, per wave, kPcgFar slots from 16 on. With 4 waves two
 // workgroups share a CU and a stream spreads over more CUs; with 8 waves each
 // foreign column serves more rows and there are fewer workgroups to meet.
+constexpr int kPcgTags = 8192;        // tags per solve (more than kMaxPcg)
 constexpr int kPcgMaxSlots = 24;
 constexpr int kPcgFar = 16;
 constexpr int kPcgCopies = 4;         // of the parts' exchange words, each for every fourth workgroup
@@ -60,7 +70,6 @@ __host__ __device__ constexpr int pcg_halo(int waves) { return pcg_local(waves) 
 
 constexpr int kRigidSurfels = 1024;   // surfels per rigid-system workgroup (4 per thread)
 
-constexpr int kPcgTags = 8192;        // tags per solve (more than kMaxPcg)
 
 // Per-step statistics of the rigid alignment.
 struct RigidStats {
@@ -93,6 +102,7 @@ __host__ __device__ __forceinline__ T* by_parity(const ParityPair<T>& pp, int q)
 struct FrameDesc {
     // shapes
     int ns, nn, nb, noff, nseg, pitch, npx, ell_w;
+    int corr_split;               // workgroups that share a pack in the correspondence launch
     int npack;                    // packs: consecutive whole segments, at most kCorrPack surfels
     int64_t part_floats;          // floats of all segments' Gram sub-blocks
     int pcg_iters, debug_iter;
@@ -136,6 +146,7 @@ struct FrameDesc {
     const uint16_t *loc4, *loc8;
     const int *halo4, *halo8, *halo_n4, *halo_n8;
     unsigned long long *xpart, *xuv;
+    int* xepoch;                  // solves so far (the fold before each counts it): the words' tags follow from it
     long long pcg_wait;           // longest wait of a workgroup for the others, in 10 ns
     const int *slot_u, *slot_t;   // [nb] ELL slot of each upper block and of its transpose (-1: diagonal)
     // resident: capture of one iteration (null unless requested)
@@ -146,7 +157,6 @@ struct FrameDesc {
     float* depth;                 // copy of a host depth image
     float4* nmap;                 // (normal, depth) per pixel
     unsigned long long* zbuf;     // index map: (z bits << 32 | surfel) per pixel
-    int* xepoch;                  // solves so far (the fold before each counts it): the words' tags follow from it
     int* flags;                   // [4] failure bits of the frame
     IterStats* stats;             // [kMaxIters]
     float4 *rq_bak, *tt_bak;      // node state at the start of the frame
@@ -228,7 +238,7 @@ inline int stage_tiles(int stage, const FrameDesc& d, int variant = 0) {
             return px > nt ? px : nt;
         }
         case kStWarp: return cdiv(d.ns, kWarpBlock);
-        case kStCorr: return corr_tiles(d);
+        case kStCorr: return corr_tiles(d) * ((variant & kVarWide) ? d.corr_split : 1);
         case kStAsmSeg: return 0;     // the segment Gram matrices are formed by the correspondence kernel
         case kStAsmFold: return cdiv(d.nn, kFoldGroups) + cdiv(d.noff, kFoldOffGroups);
         case kStPcgInit: return solve_tiles(d);
@@ -252,7 +262,8 @@ struct Batch {
     int pcg_it;                   // PCG iteration of this launch (products of it; finish of it, or of
                                   // it - 1 in a fused step)
     int order;                    // kOrderXcd: tiles in XCD-contiguous order
-    int wide;                     // the stage's wider geometry (kVarWide); whole solves: 8 waves per workgroup
+    int wide;                     // the stage's wider geometry (kVarWide); correspondence: shared packs;
+                                  // whole solves: 8 waves per workgroup
     int splat;                    // some stream renders splats (the kernels with splat code run)
     int sets;                     // whole solves: most sets of local nodes of a workgroup
     int update;                   // a stream's last PCG finish in this launch also moves its nodes
