@@ -24,7 +24,11 @@
 // fastest and a stream spreads over more CUs (4.4 us per iteration against
 // 5.2 us with 64 rows); with more waves than SIMDs, 64 rows (8 waves) make
 // half the workgroups to meet and each foreign column serves more rows (16
-// streams: 86 us against 88 us for a third of them, and fewer launches).
+// streams: 86 us against 88 us for a third of them, and fewer launches). That
+// holds also where a tile has so many foreign columns that its workgroup takes
+// a CU's LDS for itself (1,788 nodes, up to 136 of them: 56.5 us, 64.2 us with
+// 64 rows). A node set of 64 nodes at most is one workgroup of 8 waves, which
+// has nobody to wait for (40 nodes: 41.4 us, two workgroups 43.4 us).
 //
 // The exchange. A value travels as 64-bit words, each the iteration's tag in
 // the upper half and 32 bits of payload in the lower, written and read by
@@ -189,8 +193,11 @@ __device__ __forceinline__ double wave_sum2(double a, double b) {
 // kWaves: waves (of 8 block rows) per workgroup; kSets: sets of local nodes,
 // one node of a set per lane group, that the launch's largest workgroup needs.
 template <int kWaves, int kSets>
-__global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
-    constexpr int kRows = pcg_rows(kWaves), kLocal = pcg_local(kWaves), kHalo = pcg_halo(kWaves);
+__global__ void __launch_bounds__(64 * kWaves, kWaves == 4 && kSets > kPcgPairSets ? 1 : 2) k_pcg_solve(Batch b) {
+    // kNone: the local column of a slot that is not in use; kLocal: local nodes held, the zero node's place
+    constexpr int kRows = pcg_rows(kWaves), kNone = pcg_local(kWaves), kHalo = pcg_halo(kWaves);
+    constexpr int kLocal = kSets * kRows;
+    static_assert(kLocal <= kNone && kLocal < 512, "the local columns' layout and their 9 bits");
     // the sums over parts have the shape of a 256-thread sum of four values:
     // with 8 waves each half of the workgroup forms two of them
     constexpr int kValues = 16 / kWaves;
@@ -285,7 +292,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) k_pcg_solve(Batch b) {
         col[j] = 0;
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
-            const bool use = row < a.nn && grp + 8 * s < a.ell_w && lcol[j][s] != (unsigned)kLocal;
+            const bool use = row < a.nn && grp + 8 * s < a.ell_w && lcol[j][s] != (unsigned)kNone;
             col[j] |= (use ? lcol[j][s] : (unsigned)kLocal) << (9 * s);
             if (s < 2) {
 #pragma unroll
@@ -567,12 +574,14 @@ void launch_pcg_solve(const Batch& b, hipStream_t st) {
     const int grid = b.off[b.n];
     if (grid <= 0) return;
     // (most node sets need few sets; the kernels for more hold fewer of them side by side)
+    static_assert(kPcgPairSets == 5, "the sets of the kernels below");
     if (b.wide) {
         if (b.sets <= 4) hipLaunchKernelGGL((k_pcg_solve<8, 4>), dim3(grid), dim3(512), 0, st, b);
         else hipLaunchKernelGGL((k_pcg_solve<8, 5>), dim3(grid), dim3(512), 0, st, b);
     } else {
         if (b.sets <= 4) hipLaunchKernelGGL((k_pcg_solve<4, 4>), dim3(grid), dim3(256), 0, st, b);
-        else hipLaunchKernelGGL((k_pcg_solve<4, 5>), dim3(grid), dim3(256), 0, st, b);
+        else if (b.sets <= 5) hipLaunchKernelGGL((k_pcg_solve<4, 5>), dim3(grid), dim3(256), 0, st, b);
+        else hipLaunchKernelGGL((k_pcg_solve<4, 8>), dim3(grid), dim3(256), 0, st, b);
     }
 }
 
@@ -583,7 +592,14 @@ int pcg_resident_workgroups(int waves, int cus) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, few, 64 * waves, 0) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, many, 64 * waves, 0) != hipSuccess)
         return 0;
-    return (n < m ? n : m) * cus;
+    n = n < m ? n : m;
+    if (waves == 8) {
+        // (a workgroup of 4 waves and more than kPcgPairSets sets counts as one of 8)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, (const void*)k_pcg_solve<4, 8>, 256, 0) != hipSuccess)
+            return 0;
+        n = n < m ? n : m;
+    }
+    return n * cus;
 }
 
 }  // namespace swgn

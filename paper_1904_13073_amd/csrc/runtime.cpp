@@ -92,35 +92,42 @@ Executor::~Executor() {
 constexpr int kMaxDevices = 64;
 static std::atomic<int> g_pcg_leased[kMaxDevices];
 
-// waves that a whole linear solve of stream s takes, in workgroups of so many; 0: it cannot take one
-static int whole_solve_waves(const Executor& ex, sw_stream s, int waves) {
-    if (s->pcg_sets(waves) == 0 || s->h.pcg_iters == 0) return 0;
-    const int n = pcg_tiles(s->h, waves) * waves;
+// waves that a whole linear solve of stream s counts as with the executor's
+// workgroups; 0: it cannot take one
+static int whole_solve_waves(const Executor& ex, sw_stream s) {
+    if (s->pcg_sets(ex.pcg_waves) == 0 || s->h.pcg_iters == 0) return 0;
+    const int n = pcg_tiles(s->h, ex.pcg_waves) * ex.pcg_charge;
     return n <= ex.pcg_resident ? n : 0;
 }
 
 PcgLease::PcgLease(Executor& ex, const std::vector<sw_stream>& ss) : ex_(ex) {
     ex.pcg_lease = 0;
     if (ex.pcg_mode != kPcgAuto || ex.pcg_resident == 0) return;
-    // workgroups of 4 waves while every SIMD then has one wave at most (a wave
-    // alone on its SIMD is not slowed by another); beyond, of 8
     auto total = [&](int waves, int& most) {
-        int all = 0;
+        int all = 0, sets = 0;
         most = 0;
+        for (sw_stream s : ss) sets = std::max(sets, s->pcg_sets(waves));
+        ex.pcg_waves = waves;
+        ex.pcg_charge = waves == 4 && sets > kPcgPairSets ? 8 : waves;
         for (sw_stream s : ss) {
-            const int n = whole_solve_waves(ex, s, waves);
+            const int n = whole_solve_waves(ex, s);
             most = std::max(most, n);
             all += n;
         }
         return all;
     };
-    int most = 0;
-    int all = total(4, most);
-    ex.pcg_waves = 4;
-    if (all > ex.pcg_resident / 2 || most == 0) {
-        all = total(8, most);
-        ex.pcg_waves = 8;
-    }
+    // One workgroup of 8 waves where it holds the whole node set (nothing is
+    // exchanged: 40 nodes, 10 iterations: 43.4 -> 41.4 us). Otherwise of 4 waves while every SIMD then has
+    // one wave at most (a wave alone on its SIMD is not slowed by another),
+    // also where few tiles have so many foreign nodes that a workgroup needs a
+    // CU to itself (1,788 nodes, at most 136 of them: 64.2 -> 56.5 us);
+    // beyond, of 8.
+    int most = 0, all = 0;
+    const bool one = std::all_of(ss.begin(), ss.end(), [](sw_stream s) {
+        return s->h.nn <= pcg_rows(8) && s->pcg_sets(8) > 0;
+    });
+    if (!one) all = total(4, most);
+    if (one || all / ex.pcg_charge * 4 > ex.pcg_resident / 2 || most == 0) all = total(8, most);
     if (most == 0) return;
     std::atomic<int>& leased = g_pcg_leased[ex.device];
     int now = leased.load();
@@ -923,7 +930,7 @@ void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std
         int waves = 0;
         bool any = false;
         for (; i < n; ++i) {
-            const int w = its[i] >= 0 ? whole_solve_waves(ex, ss[i], ex.pcg_waves) : 0;
+            const int w = its[i] >= 0 ? whole_solve_waves(ex, ss[i]) : 0;
             if (w == 0) continue;
             // (with the whole device leased, workgroups start in order as others
             // end: the first stream that is not done always gets all of its own)
@@ -1073,7 +1080,7 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         std::vector<std::pair<sw_stream, uint64_t>> key;
         for (sw_stream s : ss) key.emplace_back(s, s->generation);
         key.emplace_back(nullptr, ex.tune_epoch);
-        key.emplace_back(nullptr, (uint64_t)ex.pcg_lease * 16 + (uint64_t)ex.pcg_waves);
+        key.emplace_back(nullptr, (uint64_t)ex.pcg_lease * 256 + (uint64_t)ex.pcg_waves * 16 + (uint64_t)ex.pcg_charge);
         if (!ex.graph_exec || key != ex.graph_key) {
             ex.drop_graph();
             hipGraph_t g = nullptr;

@@ -92,6 +92,7 @@ struct Executor {
     int pcg_resident = 0;
     int pcg_lease = 0;
     int pcg_waves = 4;
+    int pcg_charge = 4;                   // waves that such a workgroup counts as (8: it has a CU to itself)
     hipGraphExec_t graph_exec = nullptr;
     std::vector<std::pair<sw_stream, uint64_t>> graph_key;   // (stream, generation) it was captured for
     ~Executor();

@@ -58,14 +58,16 @@ constexpr int kNodeBlock = 256;
 // 8 block rows and holds a bounded number of nodes, its rows and the columns
 // they touch (sets of one node per lane group; 400 bytes of LDS each), at most
 // 24 slots per row and, per wave, kPcgFar slots from 16 on. With 4 waves two
-// workgroups share a CU and a stream spreads over more CUs; with 8 waves each
-// foreign column serves more rows and there are fewer workgroups to meet.
+// workgroups share a CU up to kPcgPairSets sets (with more, one has the CU to
+// itself) and a stream spreads over more CUs; with 8 waves each foreign column
+// serves more rows and there are fewer workgroups to meet.
 constexpr int kPcgTags = 8192;        // tags per solve (more than kMaxPcg)
 constexpr int kPcgMaxSlots = 24;
 constexpr int kPcgFar = 16;
+constexpr int kPcgPairSets = 5;
 constexpr int kPcgCopies = 4;         // of the parts' exchange words, each for every fourth workgroup
 __host__ __device__ constexpr int pcg_rows(int waves) { return 8 * waves; }
-__host__ __device__ constexpr int pcg_local(int waves) { return waves == 4 ? 160 : 320; }
+__host__ __device__ constexpr int pcg_local(int waves) { return waves == 4 ? 256 : 320; }
 __host__ __device__ constexpr int pcg_halo(int waves) { return pcg_local(waves) - pcg_rows(waves); }
 
 constexpr int kRigidSurfels = 1024;   // surfels per rigid-system workgroup (4 per thread)

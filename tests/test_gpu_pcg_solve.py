@@ -179,3 +179,29 @@ def test_a_solve_that_gives_up_waiting_is_done_again_in_steps(swgn, monkeypatch)
     sv.close()
     for st in sts:
         st.close()
+
+
+# a nearly flat sheet, whose node order jumps about in it: 148 and 201 foreign
+# columns in a tile of 32 rows, so 6 and 8 sets of local nodes, one workgroup per CU
+@pytest.mark.parametrize("n_nodes", [600, 1000])
+def test_workgroups_with_many_foreign_columns_equal_steps(swgn, n_nodes):
+    s = _surface(n_nodes, n_nodes)
+    s["nodes"][:, 2] = 1.2 - np.random.default_rng(1).uniform(0, 0.1 * s["cfg"]["node_sigma"], n_nodes)
+    want = _steps(swgn, s, frames=2)
+    st = _stream(swgn, s, stage_timing=1)
+    for _ in range(2):
+        stats = st.solve_frame(s["depth"])
+    assert _whole(stats)
+    _same((stats, st.node_se3()), want, n_nodes)
+    st.close()
+    # beside a stream whose tiles have few of them
+    pair = [s, _surface(900, 3)]
+    want = [_steps(swgn, q, frames=2) for q in pair]
+    sts = [_stream(swgn, q) for q in pair]
+    bx = swgn.Batch()
+    for _ in range(2):
+        stats, _ = bx.solve(sts, [q["depth"] for q in pair])
+    for k, st in enumerate(sts):
+        _same((stats[k], st.node_se3()), want[k], (n_nodes, k))
+        st.close()
+    bx.close()
