@@ -69,6 +69,20 @@ void Arena::release() {
     bytes_ = 0;
 }
 
+void* Arena::renew(size_t bytes) {
+    bytes = ((bytes == 0 ? 1 : bytes) + 255) & ~size_t(255);
+    if (chunks_.size() != 1 || chunks_[0].size < bytes || chunks_[0].size / 2 > bytes) {
+        release();
+        Chunk c{nullptr, bytes + ((bytes / 8 + 255) & ~size_t(255)), 0};
+        void* p = nullptr;
+        SWGN_HIP(hipMalloc(&p, c.size));
+        c.base = static_cast<char*>(p);
+        chunks_.push_back(c);
+    }
+    reset();
+    return raw(bytes);
+}
+
 void Arena::reset() {
     for (Chunk& c : chunks_) c.used = 0;
     cur_ = 0;
@@ -497,7 +511,6 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     // of the device may still use it
     SWGN_HIP(hipDeviceSynchronize());
     s->graph_mem.reset();
-    s->ws_mem.release();
     s->graph_set = false;
     s->captured = false;
     ++s->generation;
@@ -525,7 +538,7 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     h.stable_conf = s->cfg.stable_conf;
     h.recent = s->cfg.recent_frames;
     h.t_now = s->t_now;
-    s->fuse_mem.release();
+    s->fuse_mem.reset();
     s->fz4 = nullptr;
     s->fused = false;
 
@@ -768,7 +781,7 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
 
     // the stream's own workspace
     s->ws_bytes = carve_workspace(h, nullptr);
-    char* ws = static_cast<char*>(s->ws_mem.raw(s->ws_bytes));
+    char* ws = static_cast<char*>(s->ws_mem.renew(s->ws_bytes));
     carve_workspace(h, ws);
 
     s->h = h;
@@ -1315,15 +1328,26 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos, con
     if (!pos || !nrm) return fail(s->err, SW_EINVAL, "surfel pointers must not be NULL");
     if (on_device != 0 && on_device != 1) return fail(s->err, SW_EINVAL, "on_device must be 0 or 1");
     return guarded(s->err, [&]() -> sw_status {
-        s->graph_mem.release();
-        s->ws_mem.release();
         s->graph_set = false;
         s->captured = false;
         ++s->generation;
-        s->surf_mem.release();
+        // a model of about the size of the last one takes over its memory (to
+        // free and allocate it anew takes longer than the rest of a model's
+        // installation); no work of the device may still use it
+        SWGN_HIP(hipDeviceSynchronize());
+        if (!s->surfels_set || n < s->ns / 4 || n > 2 * s->ns) {
+            s->graph_mem.release();
+            s->ws_mem.release();
+            s->setup_mem.release();
+            s->surf_mem.release();
+            s->spare_mem.release();
+            s->geo_mem.release();
+            s->fuse_mem.release();
+        }
+        s->surf_mem.reset();
         s->surfels_set = false;
         s->ns = n;
-        s->fuse_mem.release();
+        s->fuse_mem.reset();
         s->fz4 = nullptr;
         s->fused = false;
         s->in_pos = s->surf_mem.alloc<float>(3 * (size_t)n);
@@ -1555,7 +1579,7 @@ sw_status sw_fuse_frame(sw_stream s, const float* depth, int32_t on_device, int3
         hipStream_t st = s->exec.st;
         FrameDesc& h = s->h;
         if (!s->fz4) {
-            s->fuse_mem.release();
+            s->fuse_mem.reset();
             s->fz4 = s->fuse_mem.alloc<unsigned long long>((size_t)16 * h.npx);
             s->flive = s->fuse_mem.alloc<float>(6 * (size_t)h.pitch);
             s->fmatch = s->fuse_mem.alloc<int>(h.npx);
@@ -1744,7 +1768,8 @@ sw_status sw_update_geometry(sw_stream s, sw_geometry_stats* stats) {
         run_append(s, s->h.npx, nullptr, nullptr, nullptr, nullptr, nullptr, &as);
         const int napp = as.n_written;
         // which existing surfels stay (caller order), and where
-        Arena tmp;
+        Arena& tmp = s->geo_mem;
+        tmp.reset();
         int* flag = tmp.alloc<int>(ns + 1);
         int* pos = tmp.alloc<int>(ns + 1);
         int* scan = tmp.alloc<int>(scan_tmp_size(ns + 1));
@@ -1763,7 +1788,8 @@ sw_status sw_update_geometry(sw_stream s, sw_geometry_stats* stats) {
         SWGN_HIP(hipMemcpyAsync(tt, s->h.tt, sizeof(float4) * nn, hipMemcpyDeviceToDevice, st));
         launch_f4_to_positions(nn, s->h.pref, np3, st);
         // the compacted caller-order arrays
-        Arena fresh;
+        Arena& fresh = s->spare_mem;
+        fresh.reset();
         CompactArgs c{};
         c.ns = ns; c.nkeep = nkeep; c.napp = napp; c.t_now = s->t_now;
         c.flag = flag; c.pos = pos;
@@ -1779,7 +1805,7 @@ sw_status sw_update_geometry(sw_stream s, sw_geometry_stats* stats) {
         launch_compact_surfels(c, st);
         SWGN_HIP(hipGetLastError());
         SWGN_HIP(hipStreamSynchronize(st));
-        // swap in the new surfels (the old arrays go with `fresh`) and rebuild
+        // swap in the new surfels (the old arrays are the next update's spare memory) and rebuild
         s->surf_mem.swap(fresh);
         s->ns = nnew;
         s->in_pos = c.dpos; s->in_nrm = c.dnrm; s->in_rad = c.drad; s->in_conf = c.dconf;

@@ -50,6 +50,10 @@ public:
     // hands the chunks out again from the start (no device memory is freed;
     // the caller makes sure no work still uses what they held)
     void reset();
+    // one piece instead of everything handed out before: in the memory at hand
+    // if it holds that and is not much larger, else in new memory with an
+    // eighth to spare (a model that grows a little each frame)
+    void* renew(size_t bytes);
     size_t bytes() const { return bytes_; }   // bytes handed out (aligned)
     void swap(Arena& o) {
         chunks_.swap(o.chunks_);
@@ -152,6 +156,7 @@ struct sw_stream_s {
     swgn::rt::Executor exec;              // the stream's own HIP stream
     swgn::rt::Arena frame_mem, surf_mem, graph_mem, ws_mem;
     swgn::rt::Arena setup_mem;            // temporaries of the node-set build, kept for the next one
+    swgn::rt::Arena geo_mem, spare_mem;   // geometry update: temporaries, and the surfels before it (the next update's)
     uint64_t generation = 0;              // bumped whenever device buffers are replaced
 
     // surfels as given
