@@ -249,19 +249,7 @@ __global__ void __launch_bounds__(256) k_asm_fold(Batch wl) {
     }
 }
 
-__global__ void k_offlist(int nb, const int* __restrict__ blk_row, const int* __restrict__ col_idx,
-                          int* __restrict__ offlist) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    int k = blk_row[b];
-    if (col_idx[b] != k) offlist[b - k - 1] = b;   // the diagonal is first in each row
-}
-
 }  // namespace
-
-void launch_offlist(int nb, const int* blk_row, const int* col_idx, int* offlist, hipStream_t st) {
-    hipLaunchKernelGGL(k_offlist, dim3((nb + 255) / 256), dim3(256), 0, st, nb, blk_row, col_idx, offlist);
-}
 
 void launch_asm_stage(int stage, const Batch& b, hipStream_t st) {
     const int grid = b.off[b.n];

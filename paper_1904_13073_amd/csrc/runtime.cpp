@@ -19,6 +19,7 @@
 #include <cstdlib>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <string>
@@ -359,37 +360,56 @@ long long pcg_wait_limit() {
 // list the float offsets of its sub-blocks (and, for a diagonal block, of the
 // matching J^T r piece) in segment order.
 // The greedy cuts are successor chains walked on the device (segwalk.hip);
-// the host reads back three sizes (segments; Gram floats, entries and packs;
-// the consistency flag) to size the resident arrays.
-void build_segments(sw_stream s, FrameDesc& h, const uint64_t* key, const int* set_start, const int* run_pos,
-                    int nsets, const int4* sidx, const int* row_ptr, const int* col_idx, Arena& G, Arena& tmp) {
+// the host reads back the segments' number, then the Gram floats, entries and
+// packs, to size the resident arrays.
+struct SegmentChain {
+    int *cuts, *count, *bad, *work;            // the chain from surfel 0, its length, the consistency flag
+};
+
+// The segment cuts, enqueued (their number comes back with the other sizes).
+SegmentChain enqueue_segments(int ns, const uint64_t* set_key, const int* set_start, const int* run_pos, Arena& tmp,
+                              hipStream_t st) {
+    if (kCorrPack > chain_max_hop()) throw HipFail{hipErrorInvalidValue, "segment layout: pack size above the chain hop"};
+    SegmentChain c{};
+    c.bad = tmp.alloc<int>(6);                 // flag, segments, packs, -, units (64 bits)
+    c.count = c.bad + 1;
+    launch_fill_i32(c.bad, 6, 0, st);
+    c.work = tmp.alloc<int>(chain_work_ints(ns, kCorrPack));
+    int* nxt = tmp.alloc<int>(ns);
+    c.cuts = tmp.alloc<int>(ns);
+    launch_seg_next(ns, set_key, set_start, run_pos, kCorrPack, nxt, st);
+    chain_from_zero(nxt, ns, kCorrPack, c.cuts, c.count, c.work, c.bad, st);
+    return c;
+}
+
+// Sizes the device has worked out, on the host (one launch, one synchronisation).
+const int* read_info(sw_stream s, std::initializer_list<const int*> from) {
+    if (!s->info_host)
+        SWGN_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->info_host), sizeof(int) * kInfo, hipHostMallocDefault));
+    int* dst = nullptr;
+    SWGN_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&dst), s->info_host, 0));
+    InfoList l{};
+    int n = 0;
+    for (const int* p : from) l.p[n++] = p;
+    launch_info(l, dst, s->exec.st);
+    SWGN_HIP(hipGetLastError());
+    SWGN_HIP(hipStreamSynchronize(s->exec.st));
+    return s->info_host;
+}
+
+// (the caller reads chain.bad once more when it is done)
+void build_segments(sw_stream s, FrameDesc& h, const SegmentChain& chain, int nseg, const uint64_t* d_keys,
+                    const int* run_pos, const int4* sidx, const int* row_ptr, const int* col_idx, Arena& G,
+                    Arena& tmp) {
     hipStream_t st = s->exec.st;
     const int ns = h.ns, nb = h.nb;
-    if (kCorrPack > chain_max_hop()) throw HipFail{hipErrorInvalidValue, "segment layout: pack size above the chain hop"};
-    uint64_t* d_keys = tmp.alloc<uint64_t>(std::max(1, nsets));
-    launch_set_keys(nsets, key, set_start, d_keys, st);
-    int* d_bad = tmp.alloc<int>(1);
-    int* d_cnt = tmp.alloc<int>(2);
-    unsigned long long* d_units = tmp.alloc<unsigned long long>(1);
-    launch_fill_i32(d_bad, 1, 0, st);
-    launch_fill_i32(reinterpret_cast<int*>(d_units), 2, 0, st);
-    int* work = tmp.alloc<int>(chain_work_ints(ns, kCorrPack));
+    int* d_bad = chain.bad;
+    int* d_cnt = chain.count;
+    unsigned long long* d_units = reinterpret_cast<unsigned long long*>(chain.bad + 4);
+    int* work = chain.work;
     int* scan_tmp = tmp.alloc<int>(scan_tmp_size(std::max(ns, nb) + 16));
-
-    // segment cuts
-    int* nxt = tmp.alloc<int>(ns);
-    int* cuts = tmp.alloc<int>(ns);
-    launch_seg_next(ns, nsets, d_keys, set_start, run_pos, kCorrPack, nxt, st);
-    chain_from_zero(nxt, ns, kCorrPack, cuts, d_cnt, work, d_bad, st);
-    int cut[2] = {0, 0};                       // segments, flag
-    SWGN_HIP(hipMemcpyAsync(&cut[0], d_cnt, sizeof(int), hipMemcpyDeviceToHost, st));
-    SWGN_HIP(hipMemcpyAsync(&cut[1], d_bad, sizeof(int), hipMemcpyDeviceToHost, st));
-    SWGN_HIP(hipStreamSynchronize(st));
-    const int nseg = cut[0];
-    if (cut[1] != 0 || nseg < 1 || nseg > ns)
-        throw HipFail{hipErrorInvalidValue, "segment layout: the segment cut is inconsistent"};
     int* d_seg = G.alloc<int>(nseg + 1);
-    SWGN_HIP(hipMemcpyAsync(d_seg, cuts, sizeof(int) * nseg, hipMemcpyDeviceToDevice, st));
+    SWGN_HIP(hipMemcpyAsync(d_seg, chain.cuts, sizeof(int) * nseg, hipMemcpyDeviceToDevice, st));
     launch_fill_i32(d_seg + nseg, 1, ns, st);
 
     // per segment: nodes, pair mask, output offsets, entry bases; packs
@@ -406,13 +426,9 @@ void build_segments(sw_stream s, FrameDesc& h, const uint64_t* key, const int* s
     int* pcuts = tmp.alloc<int>(nseg);
     launch_pack_next(nseg, d_seg, kCorrPack, pnext, st);
     chain_from_zero(pnext, nseg, kCorrPack, pcuts, d_cnt + 1, work, d_bad, st);
-    unsigned long long total_units = 0;
-    int sizes[3] = {0, 0, 0};                  // entries, packs, flag
-    SWGN_HIP(hipMemcpyAsync(&total_units, d_units, sizeof(total_units), hipMemcpyDeviceToHost, st));
-    SWGN_HIP(hipMemcpyAsync(&sizes[0], ebase + nseg, sizeof(int), hipMemcpyDeviceToHost, st));
-    SWGN_HIP(hipMemcpyAsync(&sizes[1], d_cnt + 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    SWGN_HIP(hipMemcpyAsync(&sizes[2], d_bad, sizeof(int), hipMemcpyDeviceToHost, st));
-    SWGN_HIP(hipStreamSynchronize(st));
+    // entries, packs, flag, units (low and high word)
+    const int* sizes = read_info(s, {ebase + nseg, d_cnt + 1, d_bad, chain.bad + 4, chain.bad + 5});
+    const unsigned long long total_units = ((unsigned long long)(unsigned)sizes[4] << 32) | (unsigned)sizes[3];
     if (sizes[2] != 0) throw HipFail{hipErrorInvalidValue, "segment layout: a segment has more than 5 nodes"};
     if (total_units >= (1ull << 30)) throw HipFail{hipErrorInvalidValue, "segment Gram storage exceeds 2^32 floats"};
     const int ne = sizes[0], npack = sizes[1];
@@ -447,9 +463,6 @@ void build_segments(sw_stream s, FrameDesc& h, const uint64_t* key, const int* s
     // each surfel's node positions in its segment
     uint16_t* d_pos4 = G.alloc<uint16_t>(ns);
     launch_seg_pos4(ns, nseg, d_seg, d_nodes, sidx, d_pos4, d_bad, st);
-    SWGN_HIP(hipGetLastError());
-    if (read_scalar(d_bad, st) != 0)
-        throw HipFail{hipErrorInvalidValue, "segment layout: a block or a surfel's node is missing from its segment"};
     h.nseg = nseg;
     h.npack = npack;
     h.part_floats = 4 * (int64_t)total_units;
@@ -564,20 +577,22 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
                 hlib[3 * k + a] = hin[3 * (size_t)perm[k] + a];
             }
         }
-    int* d_id = G.alloc<int>(nn);
-    int* d_inv = G.alloc<int>(nn);
-    SWGN_HIP(hipMemcpyAsync(d_id, perm.data(), sizeof(int) * nn, hipMemcpyHostToDevice, st));
-    SWGN_HIP(hipMemcpyAsync(d_inv, s->node_inv.data(), sizeof(int) * nn, hipMemcpyHostToDevice, st));
+    // the numberings and both orders' positions in one copy
+    std::vector<int> up(8 * (size_t)nn);
+    std::memcpy(up.data(), perm.data(), sizeof(int) * nn);
+    std::memcpy(up.data() + nn, s->node_inv.data(), sizeof(int) * nn);
+    std::memcpy(up.data() + 2 * (size_t)nn, hlib.data(), sizeof(float) * 3 * nn);
+    std::memcpy(up.data() + 5 * (size_t)nn, hcall.data(), sizeof(float) * 3 * nn);
+    int* d_id = G.alloc<int>(8 * (size_t)nn);
+    int* d_inv = d_id + nn;
+    SWGN_HIP(hipMemcpyAsync(d_id, up.data(), sizeof(int) * up.size(), hipMemcpyHostToDevice, st));
     s->d_node_id = d_id;
     s->d_node_inv = d_inv;
-    float* pos_in = tmp.alloc<float>(3 * (size_t)nn);
-    SWGN_HIP(hipMemcpyAsync(pos_in, hlib.data(), sizeof(float) * 3 * nn, hipMemcpyHostToDevice, st));
+    const float* pos_in = reinterpret_cast<const float*>(d_id + 2 * (size_t)nn);
     float4* pref = G.alloc<float4>(nn);
     launch_positions_to_f4(nn, pos_in, pref, st);
-    float* pos_call = tmp.alloc<float>(3 * (size_t)nn);
-    SWGN_HIP(hipMemcpyAsync(pos_call, hcall.data(), sizeof(float) * 3 * nn, hipMemcpyHostToDevice, st));
     float4* pcall = tmp.alloc<float4>(nn);
-    launch_positions_to_f4(nn, pos_call, pcall, st);
+    launch_positions_to_f4(nn, pos_in + 3 * (size_t)nn, pcall, st);
     h.pref = pref;
     h.rq = G.alloc<float4>(nn);
     h.tt = G.alloc<float4>(nn);
@@ -619,15 +634,7 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     int* nbr_call = tmp.alloc<int>(8 * (size_t)nn);
     launch_node_graph(nn, pcall, nbr_call, st);
     int* nbr = G.alloc<int>(8 * (size_t)nn);
-    {
-        std::vector<int> hn((size_t)8 * nn), hl((size_t)8 * nn);
-        SWGN_HIP(hipMemcpyAsync(hn.data(), nbr_call, sizeof(int) * 8 * nn, hipMemcpyDeviceToHost, st));
-        SWGN_HIP(hipStreamSynchronize(st));
-        for (int k = 0; k < nn; ++k)
-            for (int q = 0; q < 8; ++q) hl[8 * (size_t)k + q] = s->node_inv[(size_t)hn[8 * (size_t)perm[k] + q]];
-        SWGN_HIP(hipMemcpyAsync(nbr, hl.data(), sizeof(int) * 8 * nn, hipMemcpyHostToDevice, st));
-        SWGN_HIP(hipStreamSynchronize(st));
-    }
+    launch_map_graph(nn, nbr_call, d_id, d_inv, nbr, st);
     h.nbr = nbr;
 
     // order surfels by node set
@@ -651,86 +658,63 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     h.inv = sinv;
     int* flag = tmp.alloc<int>(ns + 1);
     int* fpos = tmp.alloc<int>(ns + 1);
-    int* scan_tmp = tmp.alloc<int>(scan_tmp_size(std::max(10 * ns, 64 * nn) + 16));
+    int* scan_tmp = tmp.alloc<int>(scan_tmp_size(ns));
     launch_permute_surfels(ns, 0, key, val, s->in_pos, s->in_nrm, idx_in, w_in, spx, spy, spz, snx, sny, snz,
                            sidx, sw, sorig, flag, st);
     launch_fuse_gather(ns, sorig, s->in_rad, s->in_conf, s->in_tobs, h.radius, h.conf, h.t_obs, sinv, st);
     exclusive_scan(flag, fpos, ns, scan_tmp, st);
-    s->nsets = read_scalar(fpos + ns, st);
-    int* set_start = tmp.alloc<int>(s->nsets + 1);      // runs of one node set
-    launch_run_starts(ns, flag, fpos, set_start, st);
+    int* set_start = tmp.alloc<int>(ns + 1);            // runs of one node set
+    uint64_t* set_key = tmp.alloc<uint64_t>(ns);
+    launch_run_starts(ns, flag, fpos, key, set_start, set_key, st);
 
-    // upper block pattern: every pair of a surfel's node set, every graph edge
+    // block pattern: every pair of a surfel's node set, every graph edge; in-edges of
+    // every node (j with the node in N_j)
     const int words = (nn + 31) / 32;
-    uint32_t* bm = tmp.alloc<uint32_t>((size_t)nn * words);
-    launch_fill_i32(reinterpret_cast<int*>(bm), nn * words, 0, st);
-    launch_pattern(s->nsets, key, set_start, nn, nbr, bm, words, st);
-    int* rcnt = tmp.alloc<int>(nn);
-    launch_row_counts(nn, bm, words, rcnt, st);
+    uint32_t* bm = tmp.alloc<uint32_t>(2 * (size_t)nn * words);
+    uint32_t* in_bm = bm + (size_t)nn * words;
+    launch_fill_i32(reinterpret_cast<int*>(bm), 2 * nn * words, 0, st);
+    launch_pattern(ns, key, flag, nn, nbr, bm, in_bm, words, st);
+    int* counts = tmp.alloc<int>(3 * (size_t)nn + 1);   // upper, full, in-edges; the longest full row
+    int* full = counts + nn;
+    int* longest = counts + 3 * (size_t)nn;
     int* row_ptr = G.alloc<int>(nn + 1);
-    exclusive_scan(rcnt, row_ptr, nn, scan_tmp, st);
-    h.nb = read_scalar(row_ptr + nn, st);
+    int* in_ptr = G.alloc<int>(nn + 1);
+    launch_row_counts(nn, bm, in_bm, words, counts, full, counts + 2 * (size_t)nn, row_ptr, in_ptr, longest, st);
+    const SegmentChain chain = enqueue_segments(ns, set_key, set_start, fpos, tmp, st);
+    const int* got = read_info(s, {fpos + ns, row_ptr + nn, longest, chain.count, chain.bad});
+    s->nsets = got[0];
+    h.nb = got[1];
+    h.ell_w = (got[2] + 7) & ~7;
+    const int nseg = got[3];
+    if (got[4] != 0 || nseg < 1 || nseg > ns)
+        throw HipFail{hipErrorInvalidValue, "segment layout: the segment cut is inconsistent"};
     h.noff = h.nb - nn;
     int* col_idx = G.alloc<int>(h.nb);
     int* blk_row = G.alloc<int>(h.nb);
-    launch_row_fill(nn, bm, words, row_ptr, col_idx, blk_row, st);
-    h.row_ptr = row_ptr; h.col_idx = col_idx; h.blk_row = blk_row;
     int* offlist = G.alloc<int>(std::max(1, h.noff));
-    launch_offlist(h.nb, blk_row, col_idx, offlist, st);
-    h.offlist = offlist;
-
-    build_segments(s, h, key, set_start, fpos, s->nsets, sidx, row_ptr, col_idx, G, tmp);
-    // (the disc splats' second pass needs the whole pack in one workgroup)
-    h.corr_split = h.splat ? 1 : std::min(kCorrSplit, std::max(1, cdiv(h.nseg, std::max(1, h.npack) * kCorrSegs)));
-
-    // in-edges of every node (j with the node in N_j), ascending j
-    const int npad_i = pow2_at_least(8 * (int64_t)nn, 1024);
-    uint64_t* ikey = tmp.alloc<uint64_t>(npad_i);
-    uint32_t* ival = tmp.alloc<uint32_t>(npad_i);
-    int* icount = tmp.alloc<int>(nn);
-    launch_fill_i32(icount, nn, 0, st);
-    launch_in_edge_keys(nn, npad_i, nbr, ikey, ival, icount, st);
-    sort_pairs(ikey, ival, npad_i, st);
-    int* in_ptr = G.alloc<int>(nn + 1);
-    exclusive_scan(icount, in_ptr, nn, scan_tmp, st);
     int* in_list = G.alloc<int>(8 * (size_t)nn);
-    launch_in_edge_store(8 * nn, ival, in_list, st);
+    launch_row_fill(nn, bm, in_bm, words, row_ptr, in_ptr, col_idx, blk_row, offlist, in_list, st);
+    h.row_ptr = row_ptr; h.col_idx = col_idx; h.blk_row = blk_row;
+    h.offlist = offlist;
     h.in_ptr = in_ptr; h.in_list = in_list;
 
     // full symmetric rows for the matrix product, in ELL layout
-    const int npad_t = pow2_at_least(h.nb, 1024);
-    uint64_t* tkey = tmp.alloc<uint64_t>(npad_t);
-    uint32_t* tval = tmp.alloc<uint32_t>(npad_t);
-    int* tcount = tmp.alloc<int>(nn);
-    launch_fill_i32(tcount, nn, 0, st);
-    launch_transpose_keys(h.nb, npad_t, blk_row, col_idx, tkey, tval, tcount, st);
-    sort_pairs(tkey, tval, npad_t, st);
-    int* tstart = tmp.alloc<int>(nn + 1);
-    exclusive_scan(tcount, tstart, nn, scan_tmp, st);
-    int* fcount = tmp.alloc<int>(nn);
-    launch_full_counts(nn, row_ptr, tcount, fcount, st);
-    int* frow_ptr = tmp.alloc<int>(nn + 1);
-    exclusive_scan(fcount, frow_ptr, nn, scan_tmp, st);
-    const int nf = 2 * h.nb - nn;
-    uint32_t* fblk = tmp.alloc<uint32_t>(nf);
-    int* fcol = tmp.alloc<int>(nf);
-    launch_full_rows(nn, h.noff, row_ptr, col_idx, tcount, tstart, frow_ptr, tkey, tval, fblk, fcol, st);
-    {
-        std::vector<int> hrow(nn + 1);
-        SWGN_HIP(hipMemcpyAsync(hrow.data(), frow_ptr, sizeof(int) * (nn + 1), hipMemcpyDeviceToHost, st));
-        SWGN_HIP(hipStreamSynchronize(st));
-        int wmax = 1;
-        for (int k = 0; k < nn; ++k) wmax = std::max(wmax, hrow[k + 1] - hrow[k]);
-        h.ell_w = (wmax + 7) & ~7;
-    }
     uint32_t* ell_blk = G.alloc<uint32_t>((size_t)nn * h.ell_w);
     int* ell_col = G.alloc<int>((size_t)nn * h.ell_w);
-    launch_ell(nn, h.ell_w, frow_ptr, fblk, fcol, ell_blk, ell_col, st);
+    int* slot_u = G.alloc<int>(h.nb);
+    int* slot_t = G.alloc<int>(h.nb);
+    launch_ell(nn, h.ell_w, bm, words, row_ptr, full, col_idx, ell_blk, ell_col, slot_u, slot_t, st);
     h.ell_blk = ell_blk; h.ell_col = ell_col;
+    h.slot_u = slot_u; h.slot_t = slot_t;
+
+    build_segments(s, h, chain, nseg, set_key, fpos, sidx, row_ptr, col_idx, G, tmp);
+    // (the disc splats' second pass needs the whole pack in one workgroup)
+    h.corr_split = h.splat ? 1 : std::min(kCorrSplit, std::max(1, cdiv(h.nseg, std::max(1, h.npack) * kCorrSegs)));
     // the whole-solve kernel's local columns and exchange words
     s->pcg_sets4 = s->pcg_sets8 = 0;
-    if (h.ell_w <= kPcgMaxSlots) {
-        int* need = tmp.alloc<int>(2);
+    const bool fits = h.ell_w <= kPcgMaxSlots;
+    int* need = tmp.alloc<int>(2);
+    if (fits) {
         launch_fill_i32(need, 2, 0, st);
         uint16_t* loc[2];
         int *halo[2], *halo_n[2];
@@ -742,28 +726,25 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
             halo_n[q] = G.alloc<int>(tiles);
             launch_pcg_local(waves, nn, h.ell_w, ell_blk, ell_col, loc[q], halo[q], halo_n[q], need + q, st);
         }
-        int got[2];
-        SWGN_HIP(hipMemcpyAsync(got, need, sizeof(got), hipMemcpyDeviceToHost, st));
-        SWGN_HIP(hipStreamSynchronize(st));
-        if (got[0] <= pcg_halo(4)) s->pcg_sets4 = 1 + cdiv(got[0], pcg_rows(4));
-        if (got[1] <= pcg_halo(8)) s->pcg_sets8 = 1 + cdiv(got[1], pcg_rows(8));
         h.loc4 = loc[0]; h.halo4 = halo[0]; h.halo_n4 = halo_n[0];
         h.loc8 = loc[1]; h.halo8 = halo[1]; h.halo_n8 = halo_n[1];
+    }
+    got = read_info(s, {chain.bad, fits ? need : nullptr, fits ? need + 1 : nullptr});
+    if (got[0] != 0)
+        throw HipFail{hipErrorInvalidValue, "segment layout: a block or a surfel's node is missing from its segment"};
+    if (fits) {
+        if (got[1] <= pcg_halo(4)) s->pcg_sets4 = 1 + cdiv(got[1], pcg_rows(4));
+        if (got[2] <= pcg_halo(8)) s->pcg_sets8 = 1 + cdiv(got[2], pcg_rows(8));
         if (s->pcg_sets4 > 0 || s->pcg_sets8 > 0) {
-            h.xpart = G.alloc<unsigned long long>(2 * kPcgCopies * pcg_part_words(h));
-            h.xuv = G.alloc<unsigned long long>(2 * (size_t)nn * 12);
-            h.xepoch = G.alloc<int>(1);
-            launch_fill_i32(reinterpret_cast<int*>(h.xpart), (int)(4 * kPcgCopies * pcg_part_words(h)), 0, st);
-            launch_fill_i32(reinterpret_cast<int*>(h.xuv), 48 * nn, 0, st);
-            launch_fill_i32(h.xepoch, 1, 0, st);
+            // the exchange words and the solve count, zero
+            const size_t xwords = 2 * kPcgCopies * pcg_part_words(h) + 2 * (size_t)nn * 12 + 1;
+            h.xpart = G.alloc<unsigned long long>(xwords);
+            h.xuv = h.xpart + 2 * kPcgCopies * pcg_part_words(h);
+            h.xepoch = reinterpret_cast<int*>(h.xuv + 2 * (size_t)nn * 12);
+            launch_fill_i32(reinterpret_cast<int*>(h.xpart), (int)(2 * xwords), 0, st);
         }
     }
     h.pcg_wait = pcg_wait_limit();
-    int* slot_u = G.alloc<int>(h.nb);
-    int* slot_t = G.alloc<int>(h.nb);
-    launch_fill_i32(slot_t, h.nb, -1, st);
-    launch_ell_slots(nn, h.ell_w, ell_blk, slot_u, slot_t, st);
-    h.slot_u = slot_u; h.slot_t = slot_t;
 
     // capture buffers, only when an iteration is to be captured
     s->dbg_index = nullptr;
@@ -786,8 +767,7 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
 
     s->h = h;
     SWGN_HIP(hipGetLastError());
-    SWGN_HIP(hipStreamSynchronize(st));
-    publish_desc(s);
+    publish_desc(s);                       // (synchronises)
     s->graph_set = true;
 }
 
@@ -1872,8 +1852,9 @@ sw_status sw_check_layout(sw_stream s, int64_t* differ) {
         const int ns = h.ns, nn = h.nn, nb = h.nb;
         hipStream_t st = s->exec.st;
         std::vector<int4> idx(ns);
-        std::vector<int> rp(nn + 1), ci(nb);
+        std::vector<int> rp(nn + 1), ci(nb), org(ns);
         SWGN_HIP(hipMemcpyAsync(idx.data(), h.idx, sizeof(int4) * ns, hipMemcpyDeviceToHost, st));
+        SWGN_HIP(hipMemcpyAsync(org.data(), h.orig, sizeof(int) * ns, hipMemcpyDeviceToHost, st));
         SWGN_HIP(hipMemcpyAsync(rp.data(), h.row_ptr, sizeof(int) * (nn + 1), hipMemcpyDeviceToHost, st));
         SWGN_HIP(hipMemcpyAsync(ci.data(), h.col_idx, sizeof(int) * nb, hipMemcpyDeviceToHost, st));
         SWGN_HIP(hipStreamSynchronize(st));
@@ -1911,7 +1892,10 @@ sw_status sw_check_layout(sw_stream s, int64_t* differ) {
             for (size_t i = 0; i < n; ++i) d += (int64_t)(a[i] != b[i]);
             return d;
         };
+        // (segment starts also count surfels out of order: ascending node set, then caller's index)
         differ[0] = cmp(seg, L.seg_start);
+        for (int i = 1; i < ns; ++i)
+            differ[0] += (int64_t)!(key[i - 1] < key[i] || (key[i - 1] == key[i] && org[i - 1] < org[i]));
         differ[1] = cmp(mask, L.mask);
         differ[2] = cmp(off, L.off) + (int64_t)((uint64_t)h.part_floats != L.total);
         differ[3] = cmp(ep, L.ent_ptr);

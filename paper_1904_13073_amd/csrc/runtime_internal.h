@@ -211,6 +211,7 @@ struct sw_stream_s {
 
     float* se3_host = nullptr;            // pinned, node transforms for the caller; room for se3_host_nodes
     size_t se3_host_nodes = 0;
+    int* info_host = nullptr;             // pinned, [kInfo]: sizes a setup hands to the host
 
     // captured iteration (allocated only when the config asks for a capture)
     int* dbg_index = nullptr;
@@ -221,6 +222,7 @@ struct sw_stream_s {
         if (h_pinned) (void)hipHostFree(h_pinned);
         if (fcount_host) (void)hipHostFree(fcount_host);
         if (se3_host) (void)hipHostFree(se3_host);
+        if (info_host) (void)hipHostFree(info_host);
     }
 };
 

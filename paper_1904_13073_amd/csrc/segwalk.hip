@@ -58,11 +58,11 @@ __device__ __forceinline__ int first_pair(int pa) { return 5 * pa - pa * (pa - 1
 // Within s's run only the length cuts; each following run joins while the
 // node union stays within 5 nodes and the segment within M surfels, and a run
 // that would take it past M surfels cuts it at s + M.
-__global__ void k_seg_next(int ns, int nsets, const uint64_t* __restrict__ set_key, const int* __restrict__ set_start,
+__global__ void k_seg_next(int ns, const uint64_t* __restrict__ set_key, const int* __restrict__ set_start,
                            const int* __restrict__ run_pos, int M, int* __restrict__ next) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= ns) return;
-    const int r = run_pos[s + 1] - 1;
+    const int r = run_pos[s + 1] - 1, nsets = run_pos[ns];
     int nx = ns;
     if (set_start[r + 1] - s > M) {
         nx = s + M;
@@ -333,9 +333,9 @@ void chain_from_zero(const int* next, int n, int M, int* out, int* count, int* w
 
 int chain_max_hop() { return kChainBlock; }
 
-void launch_seg_next(int ns, int nsets, const uint64_t* set_key, const int* set_start, const int* run_pos, int M,
+void launch_seg_next(int ns, const uint64_t* set_key, const int* set_start, const int* run_pos, int M,
                      int* next, hipStream_t st) {
-    hipLaunchKernelGGL(k_seg_next, dim3(grid_of(ns, 256)), dim3(256), 0, st, ns, nsets, set_key, set_start, run_pos, M,
+    hipLaunchKernelGGL(k_seg_next, dim3(grid_of(ns, 256)), dim3(256), 0, st, ns, set_key, set_start, run_pos, M,
                        next);
 }
 

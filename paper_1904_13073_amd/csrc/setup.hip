@@ -317,57 +317,102 @@ void sort_pairs(uint64_t* key, uint32_t* val, int n_pow2, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan of int32 (n elements -> out[0..n], out[n] = total).
+// Exclusive scan of int32 (n elements -> out[0..n], out[n] = total): tiles of
+// 4,096 elements scanned by themselves, then every tile adds the sum of the
+// tiles before it, which it forms itself from their totals (up to
+// kScanFlat tiles; beyond, the totals are scanned the same way). Setup is bound by
+// the number of its launches: one or two here (tiles of 1,024, a scan of their
+// totals and a launch for the total: five).
 // ---------------------------------------------------------------------------
-constexpr int kScanBlock = 1024;
+constexpr int kScanBlock = 1024, kScanItems = 4, kScanTile = kScanBlock * kScanItems;
+constexpr int kScanFlat = 256;
 
-__global__ void __launch_bounds__(kScanBlock) k_scan_block(const int* __restrict__ in, int* __restrict__ out,
-                                                           int* __restrict__ sums, int n) {
-    __shared__ int s[kScanBlock];
-    int i = blockIdx.x * kScanBlock + threadIdx.x;
-    int v = i < n ? in[i] : 0;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < kScanBlock; off <<= 1) {
-        int t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-        __syncthreads();
-        s[threadIdx.x] += t;
-        __syncthreads();
+// Exclusive prefix of v over the 1024 threads of a workgroup; total = the sum.
+__device__ __forceinline__ int block_prefix(int v, int* sh, int& total) {
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    int inc = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int t = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += t;
     }
-    if (i < n) out[i] = s[threadIdx.x] - v;
-    if (threadIdx.x == kScanBlock - 1) sums[blockIdx.x] = s[threadIdx.x];
+    __syncthreads();                         // (sh may still be read from the last call)
+    if (lane == kWave - 1) sh[wave] = inc;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kScanBlock / kWave; ++w) {
+        const int t = sh[w];
+        if (w < wave) before += t;
+        total += t;
+    }
+    return before + inc - v;
 }
 
-__global__ void k_scan_add(int* __restrict__ out, const int* __restrict__ offs, int n) {
-    int i = blockIdx.x * kScanBlock + threadIdx.x;
-    if (i < n) out[i] += offs[blockIdx.x];
+__global__ void __launch_bounds__(kScanBlock) k_scan_tiles(const int* __restrict__ in, int* __restrict__ out,
+                                                           int* __restrict__ sums, int n) {
+    __shared__ int sh[kScanBlock / kWave];
+    const int64_t i = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanItems;
+    int v[kScanItems], own = 0;
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        v[q] = i + q < n ? in[i + q] : 0;
+        own += v[q];
+    }
+    int total;
+    int run = block_prefix(own, sh, total);
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        if (i + q < n) out[i + q] = run;
+        run += v[q];
+    }
+    if (threadIdx.x == 0) {
+        if (gridDim.x == 1) out[n] = total;
+        else sums[blockIdx.x] = total;
+    }
 }
 
-__global__ void k_scan_total(int* __restrict__ out, const int* __restrict__ in, int n) {
-    out[n] = (n > 0 ? out[n - 1] + in[n - 1] : 0);
+// sums: the tiles' totals, or (scanned) their exclusive scan
+__global__ void __launch_bounds__(kScanBlock) k_scan_add(int* __restrict__ out, const int* __restrict__ sums,
+                                                         int scanned, int n) {
+    __shared__ int sh[kScanBlock / kWave];
+    const int b = blockIdx.x;
+    int before = 0;
+    if (scanned) {
+        before = sums[b];
+        if (b == (int)gridDim.x - 1 && threadIdx.x == 0) out[n] = sums[b + 1];
+    } else {
+        int own = 0;
+        for (int q = threadIdx.x; q < b; q += kScanBlock) own += sums[q];
+        block_prefix(own, sh, before);
+        if (b == (int)gridDim.x - 1 && threadIdx.x == 0) out[n] = before + sums[b];
+    }
+    const int64_t i = ((int64_t)b * kScanBlock + threadIdx.x) * kScanItems;
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q)
+        if (i + q < n) out[i + q] += before;
 }
 
 void exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t st) {
     // tmp must hold scan_tmp_size(n) ints
-    int nb = (n + kScanBlock - 1) / kScanBlock;
-    if (n <= 0) {
-        hipLaunchKernelGGL(k_scan_total, dim3(1), dim3(1), 0, st, out, in, 0);
-        return;
-    }
+    const int nb = n > 0 ? (int)(((int64_t)n + kScanTile - 1) / kScanTile) : 1;
     int* sums = tmp;
-    int* sums_scan = tmp + nb;
-    hipLaunchKernelGGL(k_scan_block, dim3(nb), dim3(kScanBlock), 0, st, in, out, sums, n);
-    if (nb > 1) {
-        exclusive_scan(sums, sums_scan, nb, tmp + 2 * nb + 1, st);
-        hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, st, out, sums_scan, n);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(nb), dim3(kScanBlock), 0, st, in, out, sums, n);
+    if (nb == 1) return;
+    if (nb <= kScanFlat) {
+        hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, st, out, sums, 0, n);
+    } else {
+        int* scan = tmp + nb;
+        exclusive_scan(sums, scan, nb, scan + nb + 1, st);
+        hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, st, out, scan, 1, n);
     }
-    hipLaunchKernelGGL(k_scan_total, dim3(1), dim3(1), 0, st, out, in, n);
 }
 
 size_t scan_tmp_size(int n) {
     size_t total = 0;
-    while (n > 1) {
-        int nb = (n + kScanBlock - 1) / kScanBlock;
+    while (n > kScanTile) {
+        const int nb = (int)(((int64_t)n + kScanTile - 1) / kScanTile);
         total += 2 * (size_t)nb + 1;
         n = nb;
     }
@@ -418,18 +463,16 @@ __global__ void k_permute_surfels(int ns, int seg_len, const uint64_t* __restric
     flag[i] = (i == 0 || key[i] != key[i - 1] || (seg_len > 0 && (i % seg_len) == 0)) ? 1 : 0;
 }
 
+// First surfel and node set of every run of equal node sets; pos[ns] runs.
 __global__ void k_run_starts(int ns, const int* __restrict__ flag, const int* __restrict__ pos,
-                             int* __restrict__ run_start) {
+                             const uint64_t* __restrict__ key, int* __restrict__ run_start,
+                             uint64_t* __restrict__ run_key) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < ns && flag[i]) run_start[pos[i]] = i;
+    if (i < ns && flag[i]) {
+        run_start[pos[i]] = i;
+        run_key[pos[i]] = key[i];
+    }
     if (i == 0) run_start[pos[ns]] = ns;
-}
-
-// The node set of every run (its first surfel's key).
-__global__ void k_set_keys(int nsets, const uint64_t* __restrict__ key, const int* __restrict__ run_start,
-                           uint64_t* __restrict__ out) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < nsets) out[r] = key[run_start[r]];
 }
 
 // Positions (3 bits each) of surfel i's 4 nodes, in its slot order, among
@@ -466,149 +509,202 @@ __global__ void k_seg_pos4(int ns, int nseg, const int* __restrict__ seg_start, 
 }
 
 // ---------------------------------------------------------------------------
-// Block pattern: bitmap of the upper triangle, one row of nn bits per node.
+// Block pattern: a bitmap row of nn bits per node with the columns of its full
+// block row, and one with the nodes whose edges end in it. Everything that
+// lists them in ascending order (upper blocks, full rows, in-edges) is then a
+// walk of a wave over the row's bits; sorting the transposed blocks and the
+// in-edges instead took 20 launches.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void set_bit(uint32_t* bm, int words, int r, int c) {
     atomicOr(&bm[(size_t)r * words + (c >> 5)], 1u << (c & 31));
 }
 
-__global__ void k_pattern_runs(int nruns, const uint64_t* __restrict__ key, const int* __restrict__ run_start,
+// The node pairs of every run's node set (its first surfel's).
+__global__ void k_pattern_sets(int ns, const uint64_t* __restrict__ key, const int* __restrict__ flag,
                                uint32_t* __restrict__ bm, int words) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nruns) return;
-    uint64_t k = key[run_start[r]];
+    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ns || !flag[i]) return;
+    const uint64_t k = key[i];
     int t[4] = {(int)(k >> 48), (int)((k >> 32) & 0xffff), (int)((k >> 16) & 0xffff), (int)(k & 0xffff)};
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = a + 1; b < 4; ++b) set_bit(bm, words, t[a], t[b]);
+        for (int b = 0; b < 4; ++b)
+            if (a != b) set_bit(bm, words, t[a], t[b]);
 }
 
-__global__ void k_pattern_nodes(int nn, const int* __restrict__ nbr, uint32_t* __restrict__ bm, int words) {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= nn) return;
-    set_bit(bm, words, j, j);
-    for (int q = 0; q < 8; ++q) {
-        int m = nbr[8 * j + q];
-        set_bit(bm, words, min(j, m), max(j, m));
+// Edge e = 8 j + q of the graph: both blocks of j and its neighbour, the
+// diagonal, and the neighbour's in-edge.
+__global__ void k_pattern_nodes(int nn, const int* __restrict__ nbr, uint32_t* __restrict__ bm,
+                                uint32_t* __restrict__ in_bm, int words) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= 8 * nn) return;
+    const int j = e >> 3, m = nbr[e];
+    if ((e & 7) == 0) set_bit(bm, words, j, j);
+    set_bit(bm, words, j, m);
+    set_bit(bm, words, m, j);
+    set_bit(in_bm, words, m, j);
+}
+
+constexpr int kRowBlock = 256;               // 4 rows per workgroup, one per wave
+
+// Bits of word w at columns >= r.
+__device__ __forceinline__ uint32_t from_column(uint32_t m, int w, int r) {
+    return w < (r >> 5) ? 0u : (w == (r >> 5) ? m & (~0u << (r & 31)) : m);
+}
+
+// Per node: upper blocks, all blocks of its row, in-edges.
+__global__ void __launch_bounds__(kRowBlock) k_row_counts(int nn, const uint32_t* __restrict__ bm,
+        const uint32_t* __restrict__ in_bm, int words, int* __restrict__ upper, int* __restrict__ full,
+        int* __restrict__ in_cnt) {
+    const int r = blockIdx.x * (kRowBlock / kWave) + threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    if (r >= nn) return;
+    int u = 0, f = 0, n = 0;
+    for (int w = lane; w < words; w += kWave) {
+        const uint32_t m = bm[(size_t)r * words + w];
+        f += __popc(m);
+        u += __popc(from_column(m, w, r));
+        n += __popc(in_bm[(size_t)r * words + w]);
+    }
+    u = wave_sumi(u); f = wave_sumi(f); n = wave_sumi(n);
+    if (lane == 0) { upper[r] = u; full[r] = f; in_cnt[r] = n; }
+}
+
+// One workgroup each: row_ptr and in_ptr (exclusive scans with their totals),
+// the longest full row.
+__global__ void __launch_bounds__(kScanBlock) k_row_scan(int nn, const int* __restrict__ upper,
+        const int* __restrict__ full, const int* __restrict__ in_cnt, int* __restrict__ row_ptr,
+        int* __restrict__ in_ptr, int* __restrict__ longest) {
+    __shared__ int sh[kScanBlock / kWave];
+    if (blockIdx.x == 2) {
+        int m = 1;
+        for (int k = threadIdx.x; k < nn; k += kScanBlock) m = max(m, full[k]);
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
+        if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = m;
+        __syncthreads();
+        for (int w = 0; w < kScanBlock / kWave; ++w) m = max(m, sh[w]);
+        if (threadIdx.x == 0) *longest = m;
+        return;
+    }
+    const int* in = blockIdx.x == 0 ? upper : in_cnt;
+    int* out = blockIdx.x == 0 ? row_ptr : in_ptr;
+    int carry = 0;
+    for (int base = 0; base < nn; base += kScanTile) {
+        const int i = base + (int)threadIdx.x * kScanItems;
+        int v[kScanItems], own = 0;
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) {
+            v[q] = i + q < nn ? in[i + q] : 0;
+            own += v[q];
+        }
+        int total;
+        int run = carry + block_prefix(own, sh, total);
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) {
+            if (i + q < nn) out[i + q] = run;
+            run += v[q];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) out[nn] = carry;
+}
+
+// Exclusive prefix of v over the wave, and its sum.
+__device__ __forceinline__ int wave_prefix(int v, int& total) {
+    const int lane = threadIdx.x % kWave;
+    int inc = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int t = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += t;
+    }
+    total = __shfl(inc, kWave - 1, kWave);
+    return inc - v;
+}
+
+// Upper blocks of every row (columns, rows, the list of off-diagonal ones)
+// and the in-edges, ascending.
+__global__ void __launch_bounds__(kRowBlock) k_row_fill(int nn, const uint32_t* __restrict__ bm,
+        const uint32_t* __restrict__ in_bm, int words, const int* __restrict__ row_ptr,
+        const int* __restrict__ in_ptr, int* __restrict__ col_idx, int* __restrict__ blk_row,
+        int* __restrict__ offlist, int* __restrict__ in_list) {
+    const int r = blockIdx.x * (kRowBlock / kWave) + threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    if (r >= nn) return;
+    int p0 = row_ptr[r], n0 = in_ptr[r];
+    for (int w0 = 0; w0 < words; w0 += kWave) {
+        const int w = w0 + lane;
+        uint32_t m = w < words ? from_column(bm[(size_t)r * words + w], w, r) : 0u;
+        uint32_t n = w < words ? in_bm[(size_t)r * words + w] : 0u;
+        int total;
+        int p = p0 + wave_prefix(__popc(m), total);
+        p0 += total;
+        for (; m; m &= m - 1, ++p) {
+            const int c = w * 32 + __ffs(m) - 1;
+            col_idx[p] = c;
+            blk_row[p] = r;
+            if (c != r) offlist[p - r - 1] = p;   // (the diagonal is first in each row)
+        }
+        p = n0 + wave_prefix(__popc(n), total);
+        n0 += total;
+        for (; n; n &= n - 1, ++p) in_list[p] = w * 32 + __ffs(n) - 1;
     }
 }
 
-__global__ void k_row_counts(int nn, const uint32_t* __restrict__ bm, int words, int* __restrict__ cnt) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
+// Full rows in ELL layout (width ell_w, left-aligned, ~0 padding): the
+// transposed blocks (columns below the row, found in the column's own row),
+// then the upper ones; and the slot of every block and of its transpose (-1: diagonal).
+__global__ void __launch_bounds__(kRowBlock) k_ell(int nn, int ell_w, const uint32_t* __restrict__ bm, int words,
+        const int* __restrict__ row_ptr, const int* __restrict__ full, const int* __restrict__ col_idx,
+        uint32_t* __restrict__ ell_blk, int* __restrict__ ell_col, int* __restrict__ slot_u,
+        int* __restrict__ slot_t) {
+    const int r = blockIdx.x * (kRowBlock / kWave) + threadIdx.x / kWave, lane = threadIdx.x % kWave;
     if (r >= nn) return;
-    int c = 0;
-    for (int w = 0; w < words; ++w) c += __popc(bm[(size_t)r * words + w]);
-    cnt[r] = c;
-}
-
-__global__ void k_row_fill(int nn, const uint32_t* __restrict__ bm, int words, const int* __restrict__ row_ptr,
-                           int* __restrict__ col_idx, int* __restrict__ blk_row) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nn) return;
-    int p = row_ptr[r];
-    for (int w = 0; w < words; ++w) {
-        uint32_t m = bm[(size_t)r * words + w];
-        while (m) {
-            int b = __ffs(m) - 1;
-            m &= m - 1;
-            col_idx[p] = w * 32 + b;
-            blk_row[p] = r;
-            ++p;
+    const int b0 = row_ptr[r], low = full[r] - (row_ptr[r + 1] - b0);     // columns below the row
+    int s0 = 0;
+    for (int w0 = 0; w0 < words; w0 += kWave) {
+        const int w = w0 + lane;
+        uint32_t m = w < words ? bm[(size_t)r * words + w] : 0u;
+        int total;
+        int s = s0 + wave_prefix(__popc(m), total);
+        s0 += total;
+        for (; m; m &= m - 1, ++s) {
+            const int c = w * 32 + __ffs(m) - 1, e = r * ell_w + s;
+            int b = b0 + s - low;
+            if (c < r) {
+                int lo = row_ptr[c], hi = row_ptr[c + 1];
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (col_idx[mid] < r) lo = mid + 1;
+                    else hi = mid;
+                }
+                b = lo;
+                slot_t[b] = e;
+            } else {
+                slot_u[b] = e;
+                if (c == r) slot_t[b] = -1;
+            }
+            ell_blk[e] = c < r ? (uint32_t)b | kTransposed : (uint32_t)b;
+            ell_col[e] = c;
         }
     }
-}
-
-__global__ void k_pad_keys(uint64_t* __restrict__ key, uint32_t* __restrict__ val, int from, int to) {
-    int i = from + blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= to) return;
-    key[i] = ~0ull;
-    val[i] = 0xffffffffu;
-}
-
-// Transposed uses of the upper off-diagonal blocks, keyed by (col, row).
-__global__ void k_transpose_keys(int nb, const int* __restrict__ blk_row, const int* __restrict__ col_idx,
-                                 uint64_t* __restrict__ tkey, uint32_t* __restrict__ tval,
-                                 int* __restrict__ tcount) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    int r = blk_row[b], c = col_idx[b];
-    if (r == c) {
-        tkey[b] = ~0ull;
-        tval[b] = 0xffffffffu;
-        return;
-    }
-    tkey[b] = ((uint64_t)c << 32) | (uint64_t)r;
-    tval[b] = (uint32_t)b;
-    atomicAdd(&tcount[c], 1);
-}
-
-__global__ void k_full_counts(int nn, const int* __restrict__ row_ptr, const int* __restrict__ tcount,
-                              int* __restrict__ fcount) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < nn) fcount[r] = tcount[r] + (row_ptr[r + 1] - row_ptr[r]);
-}
-
-// Fill full rows: first the transposed blocks (ascending row), then the upper ones.
-__global__ void k_full_fill_t(int ntr, const uint64_t* __restrict__ tkey, const uint32_t* __restrict__ tval,
-                              const int* __restrict__ tstart, const int* __restrict__ frow_ptr,
-                              uint32_t* __restrict__ fblk, int* __restrict__ fcol) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ntr) return;
-    int c = (int)(tkey[i] >> 32);
-    int r = (int)(tkey[i] & 0xffffffffull);
-    int slot = frow_ptr[c] + (i - tstart[c]);
-    fblk[slot] = tval[i] | kTransposed;
-    fcol[slot] = r;
-}
-
-__global__ void k_full_fill_u(int nn, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
-                              const int* __restrict__ tcount, const int* __restrict__ frow_ptr,
-                              uint32_t* __restrict__ fblk, int* __restrict__ fcol) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nn) return;
-    int p = frow_ptr[r] + tcount[r];
-    for (int b = row_ptr[r]; b < row_ptr[r + 1]; ++b) {
-        fblk[p] = (uint32_t)b;
-        fcol[p] = col_idx[b];
-        ++p;
+    for (int s = s0 + lane; s < ell_w; s += kWave) {
+        ell_blk[(size_t)r * ell_w + s] = 0xffffffffu;
+        ell_col[(size_t)r * ell_w + s] = 0;
     }
 }
 
-// ---------------------------------------------------------------------------
-// Node-graph in-edges and ELL rows
-// ---------------------------------------------------------------------------
-// in-edges of every node: (m << 32 | j) keys for every edge j -> m
-__global__ void k_in_edge_keys(int nn, int npad, const int* __restrict__ nbr, uint64_t* __restrict__ key,
-                               uint32_t* __restrict__ val, int* __restrict__ icount) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= npad) return;
-    if (e >= 8 * nn) {
-        key[e] = ~0ull;
-        val[e] = 0xffffffffu;
-        return;
-    }
-    int j = e / 8, m = nbr[e];
-    key[e] = ((uint64_t)m << 32) | (uint64_t)j;
-    val[e] = (uint32_t)j;
-    atomicAdd(&icount[m], 1);
+// The library's neighbour lists from the caller's.
+__global__ void k_map_graph(int nn, const int* __restrict__ nbr_call, const int* __restrict__ perm,
+                            const int* __restrict__ inv, int* __restrict__ nbr) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < 8 * nn) nbr[e] = inv[nbr_call[8 * perm[e >> 3] + (e & 7)]];
 }
 
-__global__ void k_in_edge_store(int n, const uint32_t* __restrict__ val, int* __restrict__ in_list) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) in_list[e] = (int)val[e];
-}
-
-// Full rows in ELL layout (width ell_w, left-aligned, ~0 padding).
-__global__ void k_ell(int nn, int ell_w, const int* __restrict__ frow_ptr, const uint32_t* __restrict__ fblk,
-                      const int* __restrict__ fcol, uint32_t* __restrict__ ell_blk, int* __restrict__ ell_col) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nn * ell_w) return;
-    int k = t / ell_w, i = t % ell_w;
-    int f = frow_ptr[k] + i;
-    bool in = f < frow_ptr[k + 1];
-    ell_blk[t] = in ? fblk[f] : 0xffffffffu;
-    ell_col[t] = in ? fcol[f] : 0;
+// Up to kInfo device integers to pinned host memory (null: 0).
+__global__ void k_info(InfoList l, int* __restrict__ out) {
+    const int i = threadIdx.x;
+    if (i < kInfo) out[i] = l.p[i] ? *l.p[i] : 0;
 }
 
 // The whole-solve kernel's view of the rows: per workgroup of 8 WAVES rows
@@ -688,19 +784,6 @@ __global__ void __launch_bounds__(256) k_pcg_local(int nn, int ell_w, const uint
     }
 }
 
-// Where each upper block is stored in the explicit full rows of the product:
-// slot_u[b] = ELL slot of block b in its row, slot_t[b] = ELL slot of its
-// transpose in the column's row (-1 for a diagonal block, set by the caller).
-__global__ void k_ell_slots(int nn, int ell_w, const uint32_t* __restrict__ ell_blk, int* __restrict__ slot_u,
-                            int* __restrict__ slot_t) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nn * ell_w) return;
-    const uint32_t bb = ell_blk[t];
-    if (bb == 0xffffffffu) return;
-    if (bb & 0x80000000u) slot_t[bb & 0x7fffffffu] = t;
-    else slot_u[bb] = t;
-}
-
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
@@ -732,11 +815,6 @@ void launch_permute_surfels(int ns, int seg_len, const uint64_t* key, const uint
                        iidx, iw, px, py, pz, nx, ny, nz, oidx, ow, orig, flag);
 }
 
-void launch_set_keys(int nsets, const uint64_t* key, const int* run_start, uint64_t* out, hipStream_t st) {
-    if (nsets > 0)
-        hipLaunchKernelGGL(k_set_keys, dim3((nsets + 255) / 256), dim3(256), 0, st, nsets, key, run_start, out);
-}
-
 void launch_seg_pos4(int ns, int nseg, const int* seg_start, const int* seg_nodes, const int4* idx, uint16_t* pos4,
                      int* bad, hipStream_t st) {
     if (ns > 0 && nseg > 0)
@@ -744,64 +822,44 @@ void launch_seg_pos4(int ns, int nseg, const int* seg_start, const int* seg_node
                            pos4, bad);
 }
 
-void launch_run_starts(int ns, const int* flag, const int* pos, int* run_start, hipStream_t st) {
-    hipLaunchKernelGGL(k_run_starts, dim3((ns + 255) / 256), dim3(256), 0, st, ns, flag, pos, run_start);
+void launch_run_starts(int ns, const int* flag, const int* pos, const uint64_t* key, int* run_start,
+                       uint64_t* run_key, hipStream_t st) {
+    hipLaunchKernelGGL(k_run_starts, dim3((ns + 255) / 256), dim3(256), 0, st, ns, flag, pos, key, run_start, run_key);
 }
 
-void launch_pattern(int nruns, const uint64_t* key, const int* run_start, int nn, const int* nbr,
-                    uint32_t* bm, int words, hipStream_t st) {
-    if (nruns > 0)
-        hipLaunchKernelGGL(k_pattern_runs, dim3((nruns + 255) / 256), dim3(256), 0, st, nruns, key,
-                           run_start, bm, words);
-    hipLaunchKernelGGL(k_pattern_nodes, dim3((nn + 255) / 256), dim3(256), 0, st, nn, nbr, bm, words);
+void launch_pattern(int ns, const uint64_t* key, const int* flag, int nn, const int* nbr, uint32_t* bm,
+                    uint32_t* in_bm, int words, hipStream_t st) {
+    hipLaunchKernelGGL(k_pattern_sets, dim3((ns + 255) / 256), dim3(256), 0, st, ns, key, flag, bm, words);
+    hipLaunchKernelGGL(k_pattern_nodes, dim3((8 * nn + 255) / 256), dim3(256), 0, st, nn, nbr, bm, in_bm, words);
 }
 
-void launch_row_counts(int nn, const uint32_t* bm, int words, int* cnt, hipStream_t st) {
-    hipLaunchKernelGGL(k_row_counts, dim3((nn + 255) / 256), dim3(256), 0, st, nn, bm, words, cnt);
+static dim3 row_grid(int nn) { return dim3((nn + kRowBlock / kWave - 1) / (kRowBlock / kWave)); }
+
+void launch_row_counts(int nn, const uint32_t* bm, const uint32_t* in_bm, int words, int* upper, int* full,
+                       int* in_cnt, int* row_ptr, int* in_ptr, int* longest, hipStream_t st) {
+    hipLaunchKernelGGL(k_row_counts, row_grid(nn), dim3(kRowBlock), 0, st, nn, bm, in_bm, words, upper, full, in_cnt);
+    hipLaunchKernelGGL(k_row_scan, dim3(3), dim3(kScanBlock), 0, st, nn, upper, full, in_cnt, row_ptr, in_ptr,
+                       longest);
 }
 
-void launch_row_fill(int nn, const uint32_t* bm, int words, const int* row_ptr, int* col_idx, int* blk_row,
-                     hipStream_t st) {
-    hipLaunchKernelGGL(k_row_fill, dim3((nn + 255) / 256), dim3(256), 0, st, nn, bm, words, row_ptr,
-                       col_idx, blk_row);
+void launch_row_fill(int nn, const uint32_t* bm, const uint32_t* in_bm, int words, const int* row_ptr,
+                     const int* in_ptr, int* col_idx, int* blk_row, int* offlist, int* in_list, hipStream_t st) {
+    hipLaunchKernelGGL(k_row_fill, row_grid(nn), dim3(kRowBlock), 0, st, nn, bm, in_bm, words, row_ptr, in_ptr,
+                       col_idx, blk_row, offlist, in_list);
 }
 
-void launch_transpose_keys(int nb, int npad, const int* blk_row, const int* col_idx, uint64_t* tkey,
-                           uint32_t* tval, int* tcount, hipStream_t st) {
-    hipLaunchKernelGGL(k_transpose_keys, dim3((nb + 255) / 256), dim3(256), 0, st, nb, blk_row, col_idx,
-                       tkey, tval, tcount);
-    if (npad > nb)
-        hipLaunchKernelGGL(k_pad_keys, dim3((npad - nb + 255) / 256), dim3(256), 0, st, tkey, tval, nb, npad);
+void launch_ell(int nn, int ell_w, const uint32_t* bm, int words, const int* row_ptr, const int* full,
+                const int* col_idx, uint32_t* ell_blk, int* ell_col, int* slot_u, int* slot_t, hipStream_t st) {
+    hipLaunchKernelGGL(k_ell, row_grid(nn), dim3(kRowBlock), 0, st, nn, ell_w, bm, words, row_ptr, full, col_idx,
+                       ell_blk, ell_col, slot_u, slot_t);
 }
 
-void launch_full_rows(int nn, int ntr, const int* row_ptr, const int* col_idx, const int* tcount,
-                      const int* tstart, const int* frow_ptr, const uint64_t* tkey, const uint32_t* tval,
-                      uint32_t* fblk, int* fcol, hipStream_t st) {
-    if (ntr > 0)
-        hipLaunchKernelGGL(k_full_fill_t, dim3((ntr + 255) / 256), dim3(256), 0, st, ntr, tkey, tval, tstart,
-                           frow_ptr, fblk, fcol);
-    hipLaunchKernelGGL(k_full_fill_u, dim3((nn + 255) / 256), dim3(256), 0, st, nn, row_ptr, col_idx, tcount,
-                       frow_ptr, fblk, fcol);
+void launch_map_graph(int nn, const int* nbr_call, const int* perm, const int* inv, int* nbr, hipStream_t st) {
+    hipLaunchKernelGGL(k_map_graph, dim3((8 * nn + 255) / 256), dim3(256), 0, st, nn, nbr_call, perm, inv, nbr);
 }
 
-void launch_full_counts(int nn, const int* row_ptr, const int* tcount, int* fcount, hipStream_t st) {
-    hipLaunchKernelGGL(k_full_counts, dim3((nn + 255) / 256), dim3(256), 0, st, nn, row_ptr, tcount, fcount);
-}
-
-void launch_in_edge_keys(int nn, int npad, const int* nbr, uint64_t* key, uint32_t* val, int* icount, hipStream_t st) {
-    hipLaunchKernelGGL(k_in_edge_keys, dim3((npad + 255) / 256), dim3(256), 0, st, nn, npad, nbr, key, val, icount);
-}
-
-void launch_ell(int nn, int ell_w, const int* frow_ptr, const uint32_t* fblk, const int* fcol, uint32_t* ell_blk,
-                int* ell_col, hipStream_t st) {
-    int n = nn * ell_w;
-    hipLaunchKernelGGL(k_ell, dim3((n + 255) / 256), dim3(256), 0, st, nn, ell_w, frow_ptr, fblk, fcol, ell_blk,
-                       ell_col);
-}
-
-void launch_ell_slots(int nn, int ell_w, const uint32_t* ell_blk, int* slot_u, int* slot_t, hipStream_t st) {
-    const int n = nn * ell_w;
-    hipLaunchKernelGGL(k_ell_slots, dim3((n + 255) / 256), dim3(256), 0, st, nn, ell_w, ell_blk, slot_u, slot_t);
+void launch_info(const InfoList& l, int* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_info, dim3(1), dim3(kWave), 0, st, l, out);
 }
 
 void launch_pcg_local(int waves, int nn, int ell_w, const uint32_t* ell_blk, const int* ell_col, uint16_t* loc,
@@ -811,10 +869,6 @@ void launch_pcg_local(int waves, int nn, int ell_w, const uint32_t* ell_blk, con
         hipLaunchKernelGGL(k_pcg_local<4>, grid, dim3(256), 0, st, nn, ell_w, ell_blk, ell_col, loc, halo, halo_n, need);
     else
         hipLaunchKernelGGL(k_pcg_local<8>, grid, dim3(256), 0, st, nn, ell_w, ell_blk, ell_col, loc, halo, halo_n, need);
-}
-
-void launch_in_edge_store(int n, const uint32_t* val, int* in_list, hipStream_t st) {
-    hipLaunchKernelGGL(k_in_edge_store, dim3((n + 255) / 256), dim3(256), 0, st, n, val, in_list);
 }
 
 }  // namespace swgn

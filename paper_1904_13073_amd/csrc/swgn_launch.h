@@ -23,24 +23,27 @@ void launch_tuple_keys(int ns, int npad, const int4* idx, uint64_t* key, uint32_
 void launch_permute_surfels(int ns, int seg_len, const uint64_t* key, const uint32_t* val, const float* ipos, const float* inrm,
                             const int4* iidx, const float4* iw, float* px, float* py, float* pz, float* nx,
                             float* ny, float* nz, int4* oidx, float4* ow, int* orig, int* flag, hipStream_t st);
-void launch_run_starts(int ns, const int* flag, const int* pos, int* run_start, hipStream_t st);
-void launch_pattern(int nruns, const uint64_t* key, const int* run_start, int nn, const int* nbr, uint32_t* bm,
-                    int words, hipStream_t st);
-void launch_row_counts(int nn, const uint32_t* bm, int words, int* cnt, hipStream_t st);
-void launch_row_fill(int nn, const uint32_t* bm, int words, const int* row_ptr, int* col_idx, int* blk_row,
-                     hipStream_t st);
-void launch_transpose_keys(int nb, int npad, const int* blk_row, const int* col_idx, uint64_t* tkey, uint32_t* tval,
-                           int* tcount, hipStream_t st);
-void launch_full_counts(int nn, const int* row_ptr, const int* tcount, int* fcount, hipStream_t st);
-void launch_full_rows(int nn, int ntr, const int* row_ptr, const int* col_idx, const int* tcount, const int* tstart,
-                      const int* frow_ptr, const uint64_t* tkey, const uint32_t* tval, uint32_t* fblk, int* fcol,
-                      hipStream_t st);
+// first surfel and node set of every run of equal node sets (run_pos[ns] runs)
+void launch_run_starts(int ns, const int* flag, const int* pos, const uint64_t* key, int* run_start,
+                       uint64_t* run_key, hipStream_t st);
+// bitmaps (zero before) of the full block rows and of the in-edges
+void launch_pattern(int ns, const uint64_t* key, const int* flag, int nn, const int* nbr, uint32_t* bm,
+                    uint32_t* in_bm, int words, hipStream_t st);
+// counts per row, their scans (row_ptr, in_ptr: [nn + 1]) and the longest full row
+void launch_row_counts(int nn, const uint32_t* bm, const uint32_t* in_bm, int words, int* upper, int* full,
+                       int* in_cnt, int* row_ptr, int* in_ptr, int* longest, hipStream_t st);
+void launch_row_fill(int nn, const uint32_t* bm, const uint32_t* in_bm, int words, const int* row_ptr,
+                     const int* in_ptr, int* col_idx, int* blk_row, int* offlist, int* in_list, hipStream_t st);
+void launch_ell(int nn, int ell_w, const uint32_t* bm, int words, const int* row_ptr, const int* full,
+                const int* col_idx, uint32_t* ell_blk, int* ell_col, int* slot_u, int* slot_t, hipStream_t st);
+void launch_map_graph(int nn, const int* nbr_call, const int* perm, const int* inv, int* nbr, hipStream_t st);
 
-void launch_in_edge_keys(int nn, int npad, const int* nbr, uint64_t* key, uint32_t* val, int* icount, hipStream_t st);
-void launch_in_edge_store(int n, const uint32_t* val, int* in_list, hipStream_t st);
-void launch_ell_slots(int nn, int ell_w, const uint32_t* ell_blk, int* slot_u, int* slot_t, hipStream_t st);
-void launch_ell(int nn, int ell_w, const int* frow_ptr, const uint32_t* fblk, const int* fcol, uint32_t* ell_blk,
-                int* ell_col, hipStream_t st);
+// what the host has to know of a setup's sizes, written to pinned host memory
+constexpr int kInfo = 8;
+struct InfoList {
+    const int* p[kInfo];
+};
+void launch_info(const InfoList& l, int* out, hipStream_t st);
 
 // the whole-solve kernel's local columns and foreign nodes per workgroup of
 // 4 or 8 waves;
@@ -50,7 +53,6 @@ void launch_pcg_local(int waves, int nn, int ell_w, const uint32_t* ell_blk, con
                       int* halo, int* halo_n, int* need, hipStream_t st);
 
 // node state and capture helpers
-void launch_offlist(int nb, const int* blk_row, const int* col_idx, int* offlist, hipStream_t st);
 void launch_nodes_from_se3(int nn, const float* se3, const float4* pref, float4* rq, float4* tt, float4* dq,
                            float4* cl, hipStream_t st);
 void launch_node_se3_out(int nn, const float4* rq, const float4* tt, const int* caller, float4* out, hipStream_t st);

@@ -7,9 +7,6 @@
 
 namespace swgn {
 
-// out[r] = key[run_start[r]]: the node set of each run of equal keys.
-void launch_set_keys(int nsets, const uint64_t* key, const int* run_start, uint64_t* out, hipStream_t st);
-
 // pos4[i]: positions (3 bits each, slot order) of surfel i's nodes among the
 // 5 nodes of its segment (seg_start[nseg + 1], seg_nodes[5 nseg]); *bad is set
 // if a node is missing.
@@ -26,10 +23,10 @@ int chain_max_hop();
 void chain_from_zero(const int* next, int n, int M, int* out, int* count, int* work, int* bad, hipStream_t st);
 
 // next[s]: the surfel where the greedy segment opening at surfel s ends (at
-// most M surfels, at most 5 nodes; runs of equal node sets set_start[nsets +
-// 1] with node sets set_key[nsets]; run_pos[ns + 1] the exclusive scan of the
-// run-start flags).
-void launch_seg_next(int ns, int nsets, const uint64_t* set_key, const int* set_start, const int* run_pos, int M,
+// most M surfels, at most 5 nodes; runs of equal node sets from set_start[] with
+// node sets set_key[]; run_pos[ns + 1] the exclusive scan of the run-start
+// flags, so run_pos[ns] runs).
+void launch_seg_next(int ns, const uint64_t* set_key, const int* set_start, const int* run_pos, int M,
                      int* next, hipStream_t st);
 
 // next[g]: the segment where the greedy pack of at most M surfels opening at

@@ -1,0 +1,44 @@
+"""The block pattern and the rows listed from it, at node counts around the
+words and waves of its bitmaps, against the pattern's plain definition; the
+segment layout that follows from it against the sequential walk."""
+import numpy as np
+import pytest
+
+from gpu_common import expected_pattern, gpu_lib
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def swgn():
+    return gpu_lib()
+
+
+def _stream(swgn, pos, nodes):
+    st = swgn.Stream(swgn.sw_config_default(width=64, height=48, fx=50.0, fy=50.0, cx=32.0, cy=24.0, node_sigma=0.1))
+    nrm = np.zeros_like(pos)
+    nrm[:, 2] = -1.0
+    st.set_reference_surfels(pos, nrm)
+    st.set_node_graph(nodes)
+    return st
+
+
+# a bitmap row of 1 word, 2 words, one wave of words (2048 nodes), more than one; many nodes per row in a volume
+@pytest.mark.parametrize("n_nodes,n_surfels,flat", [(9, 100, True), (32, 500, False), (33, 4097, True),
+                                                    (64, 4096, False), (65, 700, True), (2047, 9000, True),
+                                                    (2048, 3000, False), (2049, 8193, False), (4100, 30000, True)])
+def test_pattern_is_its_definition(swgn, n_nodes, n_surfels, flat):
+    rng = np.random.default_rng(n_nodes)
+    nodes = rng.uniform(0, 1, (n_nodes, 3)).astype(np.float32)
+    pos = rng.uniform(0, 1, (n_surfels, 3)).astype(np.float32)
+    if flat:
+        nodes[:, 2] *= 0.01
+        pos[:, 2] *= 0.01
+    st = _stream(swgn, pos, nodes)
+    idx, _ = st.skinning()
+    nbr = st.node_graph().reshape(n_nodes, 8)
+    rp, ci = st.pattern()
+    wrp, wci = expected_pattern(idx.reshape(-1, 4), nbr, n_nodes)
+    assert np.array_equal(rp, wrp) and np.array_equal(ci, wci)
+    assert all(v == 0 for v in st.check_layout().values())
+    st.close()
