@@ -397,8 +397,15 @@ const int* read_info(sw_stream s, std::initializer_list<const int*> from) {
     return s->info_host;
 }
 
-// (the caller reads chain.bad once more when it is done)
-void build_segments(sw_stream s, FrameDesc& h, const SegmentChain& chain, int nseg, const uint64_t* d_keys,
+// The fold's entries as listed by the segments, and where they go by block.
+struct SegmentEntries {
+    int ne;
+    int *blk, *over;                           // over: some block has too many for launch_ent_order
+    uint32_t *sub, *grad, *ent_sub, *ent_grad;
+};
+
+// (the caller reads chain.bad and the entries' flag when it is done)
+SegmentEntries build_segments(sw_stream s, FrameDesc& h, const SegmentChain& chain, int nseg, const uint64_t* d_keys,
                     const int* run_pos, const int4* sidx, const int* row_ptr, const int* col_idx, Arena& G,
                     Arena& tmp) {
     hipStream_t st = s->exec.st;
@@ -407,10 +414,9 @@ void build_segments(sw_stream s, FrameDesc& h, const SegmentChain& chain, int ns
     int* d_cnt = chain.count;
     unsigned long long* d_units = reinterpret_cast<unsigned long long*>(chain.bad + 4);
     int* work = chain.work;
-    int* scan_tmp = tmp.alloc<int>(scan_tmp_size(std::max(ns, nb) + 16));
+    int* scan_tmp = tmp.alloc<int>(2 * scan_tmp_size(std::max(nseg, nb)));
     int* d_seg = G.alloc<int>(nseg + 1);
-    SWGN_HIP(hipMemcpyAsync(d_seg, chain.cuts, sizeof(int) * nseg, hipMemcpyDeviceToDevice, st));
-    launch_fill_i32(d_seg + nseg, 1, ns, st);
+    launch_seg_starts(nseg, chain.cuts, ns, d_seg, st);
 
     // per segment: nodes, pair mask, output offsets, entry bases; packs
     int* d_nodes = tmp.alloc<int>(5 * (size_t)nseg);
@@ -420,8 +426,7 @@ void build_segments(sw_stream s, FrameDesc& h, const SegmentChain& chain, int ns
     launch_seg_info(nseg, d_seg, run_pos, d_keys, d_nodes, d_mask, units, npairs, d_units, d_bad, st);
     int* off_units = tmp.alloc<int>(nseg + 1);
     int* ebase = tmp.alloc<int>(nseg + 1);
-    exclusive_scan(units, off_units, nseg, scan_tmp, st);
-    exclusive_scan(npairs, ebase, nseg, scan_tmp, st);
+    exclusive_scan2(units, off_units, npairs, ebase, nseg, scan_tmp, st);
     int* pnext = tmp.alloc<int>(nseg);
     int* pcuts = tmp.alloc<int>(nseg);
     launch_pack_next(nseg, d_seg, kCorrPack, pnext, st);
@@ -435,30 +440,31 @@ void build_segments(sw_stream s, FrameDesc& h, const SegmentChain& chain, int ns
     if (ne < 1 || npack < 1 || npack > nseg)
         throw HipFail{hipErrorInvalidValue, "segment layout: the pack cut is inconsistent"};
     uint32_t* d_off = G.alloc<uint32_t>(nseg + 1);
-    launch_seg_off(nseg, off_units, d_off, st);
 
-    // the fold's entries, sorted by block (stable in segment order)
-    const int npad = pow2_at_least(ne, 1024);
-    uint64_t* ekey = tmp.alloc<uint64_t>(npad);
-    uint32_t* eval = tmp.alloc<uint32_t>(npad);
-    uint32_t* esub = tmp.alloc<uint32_t>(ne);
-    uint32_t* egrad = tmp.alloc<uint32_t>(ne);
-    int* bcount = tmp.alloc<int>(nb);
-    launch_fill_i32(bcount, nb, 0, st);
-    launch_seg_entries(nseg, nb, npad, d_nodes, d_mask, d_off, ebase, ne, row_ptr, col_idx, ekey, eval, esub, egrad,
-                       bcount, d_bad, st);
-    sort_pairs(ekey, eval, npad, st);
+    // the fold's entries, by block (in segment order)
+    SegmentEntries en{};
+    en.ne = ne;
+    en.blk = tmp.alloc<int>(ne);
+    int* eplace = tmp.alloc<int>(ne);
+    en.sub = tmp.alloc<uint32_t>(ne);
+    en.grad = tmp.alloc<uint32_t>(ne);
+    int* bcount = tmp.alloc<int>(nb + 1);
+    en.over = bcount + nb;
+    launch_fill_i32(bcount, nb + 1, 0, st);
+    launch_seg_entries(nseg, d_nodes, d_mask, off_units, d_off, ebase, row_ptr, col_idx, en.blk, eplace, en.sub,
+                       en.grad, bcount, d_bad, st);
     int* d_ep = G.alloc<int>(nb + 1);
     exclusive_scan(bcount, d_ep, nb, scan_tmp, st);
     uint32_t* d_es = G.alloc<uint32_t>(ne);
     uint32_t* d_eg = G.alloc<uint32_t>(ne);
-    launch_ent_gather(ne, eval, esub, egrad, d_es, d_eg, st);
+    launch_ent_order(ne, nb, en.blk, eplace, d_ep, en.sub, en.grad, tmp.alloc<int>(ne), d_es, d_eg, en.over, st);
+    en.ent_sub = d_es;
+    en.ent_grad = d_eg;
 
     // packs
     int* d_pg = G.alloc<int>(npack + 1);
     int* d_ps = G.alloc<int>(npack + 1);
-    SWGN_HIP(hipMemcpyAsync(d_pg, pcuts, sizeof(int) * npack, hipMemcpyDeviceToDevice, st));
-    launch_pack_arrays(npack, nseg, ns, d_seg, d_pg, d_ps, st);
+    launch_pack_arrays(npack, nseg, ns, pcuts, d_seg, d_pg, d_ps, st);
 
     // each surfel's node positions in its segment
     uint16_t* d_pos4 = G.alloc<uint16_t>(ns);
@@ -476,6 +482,7 @@ void build_segments(sw_stream s, FrameDesc& h, const SegmentChain& chain, int ns
     h.ent_sub = d_es;
     h.ent_grad = d_eg;
     s->nent = ne;
+    return en;
 }
 
 // The library's node order: ascending Morton code of the reference positions
@@ -630,7 +637,6 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     const float sig = s->cfg.node_sigma;
     float4* boxes = tmp.alloc<float4>(knn_box_count(nn));
     launch_knn_skin(ns, s->in_pos, nn, pref, d_id, boxes, 1.0f / (2.0f * sig * sig), idx_in, w_in, st);
-    launch_map_ids(reinterpret_cast<int*>(idx_in), 4 * ns, d_inv, st);
     int* nbr_call = tmp.alloc<int>(8 * (size_t)nn);
     launch_node_graph(nn, pcall, nbr_call, st);
     int* nbr = G.alloc<int>(8 * (size_t)nn);
@@ -638,11 +644,6 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     h.nbr = nbr;
 
     // order surfels by node set
-    const int npad = pow2_at_least(ns, 1024);
-    uint64_t* key = tmp.alloc<uint64_t>(npad);
-    uint32_t* val = tmp.alloc<uint32_t>(npad);
-    launch_tuple_keys(ns, npad, idx_in, key, val, st);
-    sort_pairs(key, val, npad, st);
     h.pitch = (ns + 255) & ~255;
     float* spx = G.alloc<float>(h.pitch); float* spy = G.alloc<float>(h.pitch); float* spz = G.alloc<float>(h.pitch);
     float* snx = G.alloc<float>(h.pitch); float* sny = G.alloc<float>(h.pitch); float* snz = G.alloc<float>(h.pitch);
@@ -659,29 +660,45 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     int* flag = tmp.alloc<int>(ns + 1);
     int* fpos = tmp.alloc<int>(ns + 1);
     int* scan_tmp = tmp.alloc<int>(scan_tmp_size(ns));
-    launch_permute_surfels(ns, 0, key, val, s->in_pos, s->in_nrm, idx_in, w_in, spx, spy, spz, snx, sny, snz,
-                           sidx, sw, sorig, flag, st);
-    launch_fuse_gather(ns, sorig, s->in_rad, s->in_conf, s->in_tobs, h.radius, h.conf, h.t_obs, sinv, st);
-    exclusive_scan(flag, fpos, ns, scan_tmp, st);
+    uint64_t* key_in = tmp.alloc<uint64_t>(ns);
+    uint64_t* key = tmp.alloc<uint64_t>(ns);
+    uint32_t* val = tmp.alloc<uint32_t>(ns);
+    int* over = tmp.alloc<int>(1);
+    launch_fill_i32(over, 1, 0, st);
+    launch_bucket_sort(ns, nn, idx_in, d_inv, key_in, tmp.alloc<int>(bucket_work_ints(ns)), key, val, over, st);
     int* set_start = tmp.alloc<int>(ns + 1);            // runs of one node set
     uint64_t* set_key = tmp.alloc<uint64_t>(ns);
-    launch_run_starts(ns, flag, fpos, key, set_start, set_key, st);
-
-    // block pattern: every pair of a surfel's node set, every graph edge; in-edges of
-    // every node (j with the node in N_j)
     const int words = (nn + 31) / 32;
     uint32_t* bm = tmp.alloc<uint32_t>(2 * (size_t)nn * words);
     uint32_t* in_bm = bm + (size_t)nn * words;
-    launch_fill_i32(reinterpret_cast<int*>(bm), 2 * nn * words, 0, st);
-    launch_pattern(ns, key, flag, nn, nbr, bm, in_bm, words, st);
     int* counts = tmp.alloc<int>(3 * (size_t)nn + 1);   // upper, full, in-edges; the longest full row
     int* full = counts + nn;
     int* longest = counts + 3 * (size_t)nn;
     int* row_ptr = G.alloc<int>(nn + 1);
     int* in_ptr = G.alloc<int>(nn + 1);
-    launch_row_counts(nn, bm, in_bm, words, counts, full, counts + 2 * (size_t)nn, row_ptr, in_ptr, longest, st);
-    const SegmentChain chain = enqueue_segments(ns, set_key, set_start, fpos, tmp, st);
-    const int* got = read_info(s, {fpos + ns, row_ptr + nn, longest, chain.count, chain.bad});
+    SegmentChain chain{};
+    const int* got = nullptr;
+    for (int general = 0;; ++general) {
+        launch_permute_surfels(ns, 0, key, val, s->in_pos, s->in_nrm, idx_in, w_in, spx, spy, spz, snx, sny, snz,
+                               sidx, sw, sorig, flag, st);
+        launch_fuse_gather(ns, sorig, s->in_rad, s->in_conf, s->in_tobs, h.radius, h.conf, h.t_obs, sinv, st);
+        exclusive_scan(flag, fpos, ns, scan_tmp, st);
+        launch_run_starts(ns, flag, fpos, key, set_start, set_key, st);
+        // block pattern: every pair of a surfel's node set, every graph edge; in-edges of
+        // every node (j with the node in N_j)
+        launch_fill_i32(reinterpret_cast<int*>(bm), 2 * nn * words, 0, st);
+        launch_pattern(ns, key, flag, nn, nbr, bm, in_bm, words, st);
+        launch_row_counts(nn, bm, in_bm, words, counts, full, counts + 2 * (size_t)nn, row_ptr, in_ptr, longest, st);
+        chain = enqueue_segments(ns, set_key, set_start, fpos, tmp, st);
+        got = read_info(s, {fpos + ns, row_ptr + nn, longest, chain.count, chain.bad, over});
+        if (got[5] == 0 || general) break;
+        // many surfels of few node sets: sorted by the general sort
+        const int npad = pow2_at_least(ns, 1024);
+        key = tmp.alloc<uint64_t>(npad);
+        val = tmp.alloc<uint32_t>(npad);
+        launch_tuple_keys(ns, npad, idx_in, key, val, st);
+        sort_pairs(key, val, npad, st);
+    }
     s->nsets = got[0];
     h.nb = got[1];
     h.ell_w = (got[2] + 7) & ~7;
@@ -707,7 +724,7 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     h.ell_blk = ell_blk; h.ell_col = ell_col;
     h.slot_u = slot_u; h.slot_t = slot_t;
 
-    build_segments(s, h, chain, nseg, set_key, fpos, sidx, row_ptr, col_idx, G, tmp);
+    const SegmentEntries en = build_segments(s, h, chain, nseg, set_key, fpos, sidx, row_ptr, col_idx, G, tmp);
     // (the disc splats' second pass needs the whole pack in one workgroup)
     h.corr_split = h.splat ? 1 : std::min(kCorrSplit, std::max(1, cdiv(h.nseg, std::max(1, h.npack) * kCorrSegs)));
     // the whole-solve kernel's local columns and exchange words
@@ -729,9 +746,15 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
         h.loc4 = loc[0]; h.halo4 = halo[0]; h.halo_n4 = halo_n[0];
         h.loc8 = loc[1]; h.halo8 = halo[1]; h.halo_n8 = halo_n[1];
     }
-    got = read_info(s, {chain.bad, fits ? need : nullptr, fits ? need + 1 : nullptr});
+    got = read_info(s, {chain.bad, fits ? need : nullptr, fits ? need + 1 : nullptr, en.over});
     if (got[0] != 0)
         throw HipFail{hipErrorInvalidValue, "segment layout: a block or a surfel's node is missing from its segment"};
+    if (got[3] != 0) {
+        // a block with very many segments
+        const int npad = pow2_at_least(en.ne, 1024);
+        sort_entries(en.ne, npad, en.blk, tmp.alloc<uint64_t>(npad), tmp.alloc<uint32_t>(npad), en.sub, en.grad,
+                     en.ent_sub, en.ent_grad, st);
+    }
     if (fits) {
         if (got[1] <= pcg_halo(4)) s->pcg_sets4 = 1 + cdiv(got[1], pcg_rows(4));
         if (got[2] <= pcg_halo(8)) s->pcg_sets8 = 1 + cdiv(got[2], pcg_rows(8));

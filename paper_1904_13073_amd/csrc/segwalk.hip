@@ -125,26 +125,46 @@ __global__ void __launch_bounds__(kChainBlock) k_chain_chunks(const int* __restr
     hops[q * M + t] = cnt;
 }
 
-// The chunks linked in order from position 0 (one thread): each chunk's entry
-// position and the number of chain positions before it; *count = the chain's
-// length. An entry outside the chunk's M entry positions flags the input and
-// marks the remaining chunks unused (entry -1).
-__global__ void k_chain_link(int nchunks, int n, int M, int C, const int* __restrict__ exit_pos,
+// The chunks linked in order from position 0: each chunk's entry position and
+// the number of chain positions before it; *count = the chain's length. An
+// entry outside the chunk's M entry positions flags the input and marks the
+// remaining chunks unused (entry -1). One thread walks; the chunks' walks come
+// to LDS first, kLinkWords / M chunks at a time, a word each (positions past
+// the chunk's start in the low half, hops in the high one: both below 2^15),
+// so that a step is an LDS read (61 chunks read from memory: 28 us).
+constexpr int kLinkWords = 15360;
+static_assert(kChainChunk + kChainBlock < 32768, "a chunk's walk in two 16-bit halves");
+__global__ void __launch_bounds__(1024) k_chain_link(int nchunks, int n, int M, int C, const int* __restrict__ exit_pos,
                              const int* __restrict__ hops, int* __restrict__ entry, int* __restrict__ base,
                              int* __restrict__ count, int* __restrict__ bad) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ uint32_t walk[kLinkWords];
+    const int per = kLinkWords / M;
     int e = 0, b = 0;
     bool ok = true;
-    for (int q = 0; q < nchunks; ++q) {
-        const int t = e - q * C;
-        ok = ok && t >= 0 && t < M;
-        entry[q] = ok ? e : -1;
-        base[q] = b;
-        if (ok) {
-            b += hops[q * M + t];
-            e = exit_pos[q * M + t];
+    for (int q0 = 0; q0 < nchunks; q0 += per) {
+        const int q1 = min(nchunks, q0 + per);
+        __syncthreads();
+        for (int t = threadIdx.x; t < (q1 - q0) * M; t += 1024) {
+            const int64_t src = (int64_t)q0 * M + t;
+            const int64_t over = (int64_t)exit_pos[src] - (int64_t)(q0 + t / M) * C;
+            // (a walk that broke the rule is flagged already; any value does)
+            walk[t] = (uint32_t)(over < 0 ? 0 : (over > 32767 ? 32767 : over)) | ((uint32_t)hops[src] << 16);
+        }
+        __syncthreads();
+        if (threadIdx.x != 0) continue;
+        for (int q = q0; q < q1; ++q) {
+            const int t = e - q * C;
+            ok = ok && t >= 0 && t < M;
+            entry[q] = ok ? e : -1;
+            base[q] = b;
+            if (ok) {
+                const uint32_t w = walk[(q - q0) * M + t];
+                b += (int)(w >> 16);
+                e = q * C + (int)(w & 0xffffu);
+            }
         }
     }
+    if (threadIdx.x != 0) return;
     if (!ok || e != n) *bad = 1;
     *count = ok ? b : 0;
 }
@@ -226,57 +246,114 @@ __global__ void __launch_bounds__(256) k_seg_info(int nseg, const int* __restric
     if ((threadIdx.x % kWave) == 0 && u != 0) atomicAdd(total_units, (unsigned long long)u);
 }
 
-__global__ void k_seg_off(int nseg, const int* __restrict__ off_units, uint32_t* __restrict__ off) {
+// The cuts as segment starts, closed by ns.
+__global__ void k_seg_starts(int nseg, const int* __restrict__ cuts, int ns, int* __restrict__ seg_start) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g <= nseg) off[g] = 4u * (uint32_t)off_units[g];
+    if (g <= nseg) seg_start[g] = g < nseg ? cuts[g] : ns;
 }
 
-// Per segment, one entry per pair of its mask (in mask order): the block of
-// the pair (binary search in the node's row of the upper pattern), the float
-// offsets of its sub-block and, on the diagonal, of the J^T r piece; keyed
-// (block, entry index) for a stable sort by block, and counted per block. A
-// pair missing from the pattern flags the input and keys past every block.
-__global__ void k_seg_entries(int nseg, int nb, const int* __restrict__ seg_nodes, const uint16_t* __restrict__ mask,
-                              const uint32_t* __restrict__ off, const int* __restrict__ ebase,
-                              const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
-                              uint64_t* __restrict__ ekey, uint32_t* __restrict__ eval, uint32_t* __restrict__ esub,
-                              uint32_t* __restrict__ egrad, int* __restrict__ bcount, int* __restrict__ bad) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= nseg) return;
-    const uint32_t m = mask[g], np = (uint32_t)__popc(m), o = off[g];
-    int e = ebase[g];
-    uint32_t rank = 0;
-    for (int pa = 0; pa < 5; ++pa)
-        for (int pb = pa; pb < 5; ++pb) {
-            if (!((m >> (first_pair(pa) + pb - pa)) & 1u)) continue;
-            const int ra = seg_nodes[5 * g + pa], cb = seg_nodes[5 * g + pb];
-            int lo = row_ptr[ra], hi = row_ptr[ra + 1];
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (col_idx[mid] < cb) lo = mid + 1;
-                else hi = mid;
+// Per segment 16 lanes, one entry per pair of its mask (in mask order): the
+// block of the pair (binary search in the node's row of the upper pattern), the
+// float offsets of its sub-block and, on the diagonal, of the J^T r piece; the
+// entry's place in the block is an atomic counter's (ordered by
+// k_ent_order). A pair missing from the pattern flags the input and has no
+// block (-1). Also the segments' float offsets. (One thread per segment
+// searched its pairs one after the other: 28.7 us for 3,000 segments.)
+__global__ void __launch_bounds__(256) k_seg_entries(int nseg, const int* __restrict__ seg_nodes,
+        const uint16_t* __restrict__ mask, const int* __restrict__ off_units, uint32_t* __restrict__ off,
+        const int* __restrict__ ebase, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
+        int* __restrict__ eblk, int* __restrict__ eplace, uint32_t* __restrict__ esub, uint32_t* __restrict__ egrad,
+        int* __restrict__ bcount, int* __restrict__ bad) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, g = t >> 4, bit = t & 15;
+    if (g > nseg) return;
+    const uint32_t o = 4u * (uint32_t)off_units[g];
+    if (bit == 15) off[g] = o;
+    if (g == nseg || bit == 15) return;
+    const uint32_t m = mask[g];
+    if (!((m >> bit) & 1u)) return;
+    int pa = 0;
+    while (pa < 4 && first_pair(pa + 1) <= bit) ++pa;
+    const int pb = pa + bit - first_pair(pa);
+    const uint32_t rank = (uint32_t)__popc(m & ((1u << bit) - 1u)), np = (uint32_t)__popc(m);
+    const int e = ebase[g] + (int)rank;
+    const int ra = seg_nodes[5 * g + pa], cb = seg_nodes[5 * g + pb];
+    const int end = row_ptr[ra + 1];
+    int lo = row_ptr[ra], hi = end;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (col_idx[mid] < cb) lo = mid + 1;
+        else hi = mid;
+    }
+    int blk = lo, place = 0;
+    if (lo >= end || col_idx[lo] != cb) {
+        atomicOr(bad, 1);
+        blk = -1;
+    } else {
+        place = atomicAdd(&bcount[blk], 1);
+    }
+    eblk[e] = blk;
+    eplace[e] = place;
+    esub[e] = o + 36u * rank;
+    egrad[e] = pa == pb ? o + 36u * np + 6u * (uint32_t)pa : 0xffffffffu;
+}
+
+__global__ void __launch_bounds__(256) k_ent_scatter(int ne, const int* __restrict__ eblk, const int* __restrict__ eplace,
+                                                     const int* __restrict__ ent_ptr, int* __restrict__ list) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < ne && eblk[e] >= 0) list[ent_ptr[eblk[e]] + eplace[e]] = e;
+}
+
+// Each block's entries in ascending order (segment order), by counting the
+// smaller ones: a wave per block of up to 64, then the workgroup together for
+// its longer ones; above kEntCap *over is set (the host sorts them instead).
+constexpr int kEntCap = 4096;
+__global__ void __launch_bounds__(256) k_ent_order(int nb, const int* __restrict__ ent_ptr,
+        const int* __restrict__ list, const uint32_t* __restrict__ esub, const uint32_t* __restrict__ egrad,
+        uint32_t* __restrict__ ent_sub, uint32_t* __restrict__ ent_grad, int* __restrict__ over) {
+    __shared__ int ids[kEntCap];
+    constexpr int kBlocks = 256 / kWave;
+    const int lane = threadIdx.x % kWave, b = blockIdx.x * kBlocks + threadIdx.x / kWave;
+    if (b < nb) {
+        const int p = ent_ptr[b], n = ent_ptr[b + 1] - p;
+        if (n <= kWave) {
+            const int e = lane < n ? list[p + lane] : 0x7fffffff;
+            int rank = 0;
+            for (int j = 0; j < n; ++j) rank += __builtin_amdgcn_readlane(e, j) < e ? 1 : 0;
+            if (lane < n) {
+                ent_sub[p + rank] = esub[e];
+                ent_grad[p + rank] = egrad[e];
             }
-            int blk = lo;
-            if (lo >= row_ptr[ra + 1] || col_idx[lo] != cb) {
-                atomicOr(bad, 1);
-                blk = nb;
-            } else {
-                atomicAdd(&bcount[blk], 1);
-            }
-            ekey[e] = ((uint64_t)(uint32_t)blk << 32) | (uint32_t)e;
-            eval[e] = (uint32_t)e;
-            esub[e] = o + 36u * rank;
-            egrad[e] = pa == pb ? o + 36u * np + 6u * (uint32_t)pa : 0xffffffffu;
-            ++e;
-            ++rank;
         }
+    }
+    for (int w = 0; w < kBlocks; ++w) {                  // (the same for all threads)
+        const int bb = blockIdx.x * kBlocks + w;
+        if (bb >= nb) break;
+        const int p = ent_ptr[bb], n = ent_ptr[bb + 1] - p;
+        if (n <= kWave) continue;
+        if (n > kEntCap) {
+            if (threadIdx.x == 0) *over = 1;
+            continue;
+        }
+        __syncthreads();                                 // (ids may still be read for the last block)
+        for (int j = threadIdx.x; j < n; j += 256) ids[j] = list[p + j];
+        __syncthreads();
+        for (int q = threadIdx.x; q < n; q += 256) {
+            const int e = ids[q];
+            int rank = 0;
+            for (int j = 0; j < n; ++j) rank += ids[j] < e ? 1 : 0;
+            ent_sub[p + rank] = esub[e];
+            ent_grad[p + rank] = egrad[e];
+        }
+    }
 }
 
-__global__ void k_key_tail(uint64_t* __restrict__ key, uint32_t* __restrict__ val, int from, int to) {
-    const int i = from + blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= to) return;
-    key[i] = ~0ull;
-    val[i] = 0xffffffffu;
+// Keys (block, entry) of all entries for sort_pairs, padded to npad.
+__global__ void k_ent_keys(int ne, int npad, const int* __restrict__ eblk, uint64_t* __restrict__ key,
+                           uint32_t* __restrict__ val) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= npad) return;
+    key[e] = e < ne ? ((uint64_t)(uint32_t)eblk[e] << 32) | (uint32_t)e : ~0ull;
+    val[e] = e < ne ? (uint32_t)e : 0xffffffffu;
 }
 
 __global__ void k_ent_gather(int ne, const uint32_t* __restrict__ order, const uint32_t* __restrict__ esub,
@@ -289,15 +366,15 @@ __global__ void k_ent_gather(int ne, const uint32_t* __restrict__ order, const u
     ent_grad[i] = egrad[v];
 }
 
-// pack_start[i] = seg_start[pack_seg[i]]; the closing entries ns and nseg.
-__global__ void k_pack_arrays(int npack, int nseg, int ns, const int* __restrict__ seg_start, int* __restrict__ pack_seg,
+// First segment and first surfel of every pack; the closing entries nseg and ns.
+__global__ void k_pack_arrays(int npack, int nseg, int ns, const int* __restrict__ cuts,
+                              const int* __restrict__ seg_start, int* __restrict__ pack_seg,
                               int* __restrict__ pack_start) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < npack) pack_start[i] = seg_start[pack_seg[i]];
-    if (i == npack) {
-        pack_seg[npack] = nseg;
-        pack_start[npack] = ns;
-    }
+    if (i > npack) return;
+    const int g = i < npack ? cuts[i] : nseg;
+    pack_seg[i] = g;
+    pack_start[i] = i < npack ? seg_start[g] : ns;
 }
 
 inline int grid_of(int64_t n, int block) { return (int)((n + block - 1) / block); }
@@ -326,7 +403,7 @@ void chain_from_zero(const int* next, int n, int M, int* out, int* count, int* w
     int* entry = hops + (size_t)nchunks * M;
     int* base = entry + nchunks;
     hipLaunchKernelGGL(k_chain_chunks, dim3(nchunks), dim3(kChainBlock), 0, st, next, n, M, C, exit_pos, hops, bad);
-    hipLaunchKernelGGL(k_chain_link, dim3(1), dim3(kWave), 0, st, nchunks, n, M, C, exit_pos, hops, entry, base,
+    hipLaunchKernelGGL(k_chain_link, dim3(1), dim3(1024), 0, st, nchunks, n, M, C, exit_pos, hops, entry, base,
                        count, bad);
     hipLaunchKernelGGL(k_chain_emit, dim3(nchunks), dim3(kChainBlock), 0, st, next, n, C, entry, base, out);
 }
@@ -350,30 +427,37 @@ void launch_seg_info(int nseg, const int* seg_start, const int* run_pos, const u
                        seg_nodes, mask, units, npairs, total_units, bad);
 }
 
-void launch_seg_off(int nseg, const int* off_units, uint32_t* off, hipStream_t st) {
-    hipLaunchKernelGGL(k_seg_off, dim3(grid_of(nseg + 1, 256)), dim3(256), 0, st, nseg, off_units, off);
+void launch_seg_starts(int nseg, const int* cuts, int ns, int* seg_start, hipStream_t st) {
+    hipLaunchKernelGGL(k_seg_starts, dim3(grid_of(nseg + 1, 256)), dim3(256), 0, st, nseg, cuts, ns, seg_start);
 }
 
-void launch_seg_entries(int nseg, int nb, int npad, const int* seg_nodes, const uint16_t* mask, const uint32_t* off,
-                        const int* ebase, int ne, const int* row_ptr, const int* col_idx, uint64_t* ekey,
-                        uint32_t* eval, uint32_t* esub, uint32_t* egrad, int* bcount, int* bad, hipStream_t st) {
-    hipLaunchKernelGGL(k_seg_entries, dim3(grid_of(nseg, 256)), dim3(256), 0, st, nseg, nb, seg_nodes, mask, off,
-                       ebase, row_ptr, col_idx, ekey, eval, esub, egrad, bcount, bad);
-    if (npad > ne)
-        hipLaunchKernelGGL(k_key_tail, dim3(grid_of(npad - ne, 256)), dim3(256), 0, st, ekey, eval, ne, npad);
+void launch_seg_entries(int nseg, const int* seg_nodes, const uint16_t* mask, const int* off_units, uint32_t* off,
+                        const int* ebase, const int* row_ptr, const int* col_idx, int* eblk, int* eplace,
+                        uint32_t* esub, uint32_t* egrad, int* bcount, int* bad, hipStream_t st) {
+    hipLaunchKernelGGL(k_seg_entries, dim3(grid_of(16 * ((int64_t)nseg + 1), 256)), dim3(256), 0, st, nseg, seg_nodes,
+                       mask, off_units, off, ebase, row_ptr, col_idx, eblk, eplace, esub, egrad, bcount, bad);
 }
 
-void launch_ent_gather(int ne, const uint32_t* order, const uint32_t* esub, const uint32_t* egrad, uint32_t* ent_sub,
-                       uint32_t* ent_grad, hipStream_t st) {
-    if (ne > 0)
-        hipLaunchKernelGGL(k_ent_gather, dim3(grid_of(ne, 256)), dim3(256), 0, st, ne, order, esub, egrad, ent_sub,
-                           ent_grad);
+void launch_ent_order(int ne, int nb, const int* eblk, const int* eplace, const int* ent_ptr, const uint32_t* esub,
+                      const uint32_t* egrad, int* list, uint32_t* ent_sub, uint32_t* ent_grad, int* over,
+                      hipStream_t st) {
+    hipLaunchKernelGGL(k_ent_scatter, dim3(grid_of(ne, 256)), dim3(256), 0, st, ne, eblk, eplace, ent_ptr, list);
+    hipLaunchKernelGGL(k_ent_order, dim3(grid_of(nb, 4)), dim3(256), 0, st, nb, ent_ptr, list, esub, egrad, ent_sub,
+                       ent_grad, over);
 }
 
-void launch_pack_arrays(int npack, int nseg, int ns, const int* seg_start, int* pack_seg, int* pack_start,
-                        hipStream_t st) {
-    hipLaunchKernelGGL(k_pack_arrays, dim3(grid_of(npack + 1, 256)), dim3(256), 0, st, npack, nseg, ns, seg_start,
-                       pack_seg, pack_start);
+void sort_entries(int ne, int npad, const int* eblk, uint64_t* key, uint32_t* val, const uint32_t* esub,
+                  const uint32_t* egrad, uint32_t* ent_sub, uint32_t* ent_grad, hipStream_t st) {
+    hipLaunchKernelGGL(k_ent_keys, dim3(grid_of(npad, 256)), dim3(256), 0, st, ne, npad, eblk, key, val);
+    sort_pairs(key, val, npad, st);
+    hipLaunchKernelGGL(k_ent_gather, dim3(grid_of(ne, 256)), dim3(256), 0, st, ne, val, esub, egrad, ent_sub,
+                       ent_grad);
+}
+
+void launch_pack_arrays(int npack, int nseg, int ns, const int* cuts, const int* seg_start, int* pack_seg,
+                        int* pack_start, hipStream_t st) {
+    hipLaunchKernelGGL(k_pack_arrays, dim3(grid_of(npack + 1, 256)), dim3(256), 0, st, npack, nseg, ns, cuts,
+                       seg_start, pack_seg, pack_start);
 }
 
 }  // namespace swgn

@@ -27,7 +27,6 @@ namespace swgn {
 // only at or below it).
 // A non-finite position enters no list (its keys are NaN or infinite).
 // ---------------------------------------------------------------------------
-constexpr int kKnnTile = 1024;          // nodes staged in LDS per round
 constexpr int kKnnRun = 32;             // nodes per bounding box
 
 __global__ void k_node_boxes(int nn, const float4* __restrict__ nodes, float4* __restrict__ boxes) {
@@ -85,12 +84,30 @@ __device__ __forceinline__ void admit4(uint64_t (&kk)[4], uint64_t c) {
     kk[0] = c0 ? c : kk[0];
 }
 
+// The nodes of run q (uniform over the wave) as candidates of every lane.
+__device__ __forceinline__ void admit_run(uint64_t (&kk)[4], float x, float y, float z, int nn, int q,
+                                          const float4* __restrict__ nodes, const int* __restrict__ caller) {
+    const int t0 = q * kKnnRun, t1 = min(nn, t0 + kKnnRun);
+#pragma unroll 8
+    for (int t = t0; t < t1; ++t) {
+        const float4 p = nodes[t];
+        const float dx = x - p.x, dy = y - p.y, dz = z - p.z;
+        admit4(kk, knn_word((dx * dx + dy * dy) + dz * dz, caller[t]));
+    }
+}
+
+__device__ __forceinline__ float worst_key(const uint64_t (&kk)[4], bool fin) {
+    return wave_maxf(fin ? __uint_as_float((uint32_t)(kk[3] >> 32)) : -INFINITY);
+}
+
+// A wave tests 64 boxes at a time, one per lane, and visits the runs that are
+// left in a bit mask; the nodes come by scalar loads, for a run is the same for
+// all lanes. (One box after the other by the whole wave, twice, and the nodes
+// staged in LDS: 98 us for 248k surfels and 1,788 nodes, 70 us so.)
 __global__ void __launch_bounds__(256) k_knn_skin(int ns, const float* __restrict__ pos, int nn,
         const float4* __restrict__ nodes, const int* __restrict__ caller, const float4* __restrict__ boxes,
         float inv_two_sigma2, int4* __restrict__ out_idx, float4* __restrict__ out_w) {
-    __shared__ float4 tile[kKnnTile];
-    __shared__ int tid[kKnnTile];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x % kWave;
     float x = 0.f, y = 0.f, z = 0.f;
     if (i < ns) { x = pos[3 * i]; y = pos[3 * i + 1]; z = pos[3 * i + 2]; }
     const bool fin = i < ns && isfinite(x) && isfinite(y) && isfinite(z);
@@ -104,48 +121,37 @@ __global__ void __launch_bounds__(256) k_knn_skin(int ns, const float* __restric
     const float3 hi = make_float3(wave_maxf(fin ? x : -INFINITY), wave_maxf(fin ? y : -INFINITY),
                                   wave_maxf(fin ? z : -INFINITY));
     const int nruns = (nn + kKnnRun - 1) / kKnnRun;
-    // first the runs whose box meets the wave's (or the nearest one)
+    auto bound = [&](int q) {                // (past the last run, and of an empty run: none)
+        return q < nruns ? box_key_bound(lo, hi, boxes[2 * q], boxes[2 * q + 1]) : INFINITY;
+    };
+    // first the runs whose box meets the wave's, or else the nearest one
+    bool met = false;
+    float least = INFINITY;
     int seed = 0;
-    float sb = INFINITY;
-    for (int q = 0; q < nruns; ++q) {
-        const float b = box_key_bound(lo, hi, boxes[2 * q], boxes[2 * q + 1]);
-        if (b < sb) { sb = b; seed = q; }
-        if (b > 0.f) continue;
-        for (int t = q * kKnnRun; t < min(nn, (q + 1) * kKnnRun); ++t) {
-            const float4 p = nodes[t];
-            const float dx = x - p.x, dy = y - p.y, dz = z - p.z;
-            admit4(kk, knn_word((dx * dx + dy * dy) + dz * dz, caller[t]));
+    for (int q0 = 0; q0 < nruns; q0 += kWave) {
+        const float b = bound(q0 + lane);
+        unsigned long long todo = __ballot(b <= 0.f);
+        met = met || todo != 0;
+        for (; todo; todo &= todo - 1) admit_run(kk, x, y, z, nn, q0 + __builtin_ctzll(todo), nodes, caller);
+        const float m = -wave_maxf(-b);
+        if (m < least) {
+            least = m;
+            seed = q0 + __builtin_ctzll(__ballot(b == m));
         }
     }
-    if (sb > 0.f) {
-        for (int t = seed * kKnnRun; t < min(nn, (seed + 1) * kKnnRun); ++t) {
-            const float4 p = nodes[t];
-            const float dx = x - p.x, dy = y - p.y, dz = z - p.z;
-            admit4(kk, knn_word((dx * dx + dy * dy) + dz * dz, caller[t]));
-        }
-    } else {
-        seed = -1;                          // (the meeting runs are done)
-    }
-    for (int base = 0; base < nn; base += kKnnTile) {
-        const int cnt = min(kKnnTile, nn - base);
-        __syncthreads();
-        for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
-            tile[t] = nodes[base + t];
-            tid[t] = caller[base + t];
-        }
-        __syncthreads();
-        for (int r0 = 0; r0 < cnt; r0 += kKnnRun) {
-            const int q = (base + r0) / kKnnRun;
-            const float b = box_key_bound(lo, hi, boxes[2 * q], boxes[2 * q + 1]);
-            if (q == seed || b <= 0.f) continue;
-            // every lane's fourth key bounds what it could still admit
-            const float worst = wave_maxf(fin ? __uint_as_float((uint32_t)(kk[3] >> 32)) : -INFINITY);
-            if (b > worst) continue;
-            for (int t = r0; t < min(cnt, r0 + kKnnRun); ++t) {
-                const float4 p = tile[t];
-                const float dx = x - p.x, dy = y - p.y, dz = z - p.z;
-                admit4(kk, knn_word((dx * dx + dy * dy) + dz * dz, tid[t]));
-            }
+    if (met) seed = -1;
+    else admit_run(kk, x, y, z, nn, __builtin_amdgcn_readfirstlane(seed), nodes, caller);
+    // then every run within the lanes' fourth keys (a candidate enters only at or below it)
+    float worst = worst_key(kk, fin);
+    for (int q0 = 0; q0 < nruns; q0 += kWave) {
+        const float b = bound(q0 + lane);
+        const bool open = b > 0.f && q0 + lane < nruns && q0 + lane != seed;
+        for (unsigned long long todo = __ballot(open && b <= worst); todo;) {
+            const int l = __builtin_ctzll(todo);
+            admit_run(kk, x, y, z, nn, q0 + l, nodes, caller);
+            worst = worst_key(kk, fin);
+            todo &= todo - 1;
+            todo &= __ballot(open && b <= worst);
         }
     }
     float kd[4];
@@ -350,9 +356,16 @@ __device__ __forceinline__ int block_prefix(int v, int* sh, int& total) {
     return before + inc - v;
 }
 
-__global__ void __launch_bounds__(kScanBlock) k_scan_tiles(const int* __restrict__ in, int* __restrict__ out,
-                                                           int* __restrict__ sums, int n) {
+// (blockIdx.y: one of up to two arrays of the same length)
+struct ScanArrays {
+    const int* in[2];
+    int *out[2], *sums[2];
+};
+
+__global__ void __launch_bounds__(kScanBlock) k_scan_tiles(ScanArrays a, int n) {
     __shared__ int sh[kScanBlock / kWave];
+    const int* in = a.in[blockIdx.y];
+    int *out = a.out[blockIdx.y], *sums = a.sums[blockIdx.y];
     const int64_t i = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanItems;
     int v[kScanItems], own = 0;
 #pragma unroll
@@ -374,9 +387,10 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_tiles(const int* __restrict
 }
 
 // sums: the tiles' totals, or (scanned) their exclusive scan
-__global__ void __launch_bounds__(kScanBlock) k_scan_add(int* __restrict__ out, const int* __restrict__ sums,
-                                                         int scanned, int n) {
+__global__ void __launch_bounds__(kScanBlock) k_scan_add(ScanArrays a, int scanned, int n) {
     __shared__ int sh[kScanBlock / kWave];
+    int* out = a.out[blockIdx.y];
+    const int* sums = a.sums[blockIdx.y];
     const int b = blockIdx.x;
     int before = 0;
     if (scanned) {
@@ -394,21 +408,34 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_add(int* __restrict__ out, 
         if (i + q < n) out[i + q] += before;
 }
 
-void exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t st) {
-    // tmp must hold scan_tmp_size(n) ints
+static void scan_arrays(ScanArrays a, int arrays, int n, int* tmp, hipStream_t st) {
     const int nb = n > 0 ? (int)(((int64_t)n + kScanTile - 1) / kScanTile) : 1;
-    int* sums = tmp;
-    hipLaunchKernelGGL(k_scan_tiles, dim3(nb), dim3(kScanBlock), 0, st, in, out, sums, n);
+    for (int q = 0; q < arrays; ++q) a.sums[q] = tmp + (size_t)q * nb;
+    hipLaunchKernelGGL(k_scan_tiles, dim3(nb, arrays), dim3(kScanBlock), 0, st, a, n);
     if (nb == 1) return;
+    tmp += (size_t)arrays * nb;
     if (nb <= kScanFlat) {
-        hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, st, out, sums, 0, n);
-    } else {
-        int* scan = tmp + nb;
-        exclusive_scan(sums, scan, nb, scan + nb + 1, st);
-        hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, st, out, scan, 1, n);
+        hipLaunchKernelGGL(k_scan_add, dim3(nb, arrays), dim3(kScanBlock), 0, st, a, 0, n);
+        return;
     }
+    ScanArrays t{};
+    for (int q = 0; q < arrays; ++q) {
+        t.in[q] = a.sums[q];
+        a.sums[q] = t.out[q] = tmp + (size_t)q * (nb + 1);
+    }
+    scan_arrays(t, arrays, nb, tmp + (size_t)arrays * (nb + 1), st);
+    hipLaunchKernelGGL(k_scan_add, dim3(nb, arrays), dim3(kScanBlock), 0, st, a, 1, n);
 }
 
+void exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t st) {
+    scan_arrays(ScanArrays{{in, nullptr}, {out, nullptr}, {nullptr, nullptr}}, 1, n, tmp, st);
+}
+
+void exclusive_scan2(const int* in0, int* out0, const int* in1, int* out1, int n, int* tmp, hipStream_t st) {
+    scan_arrays(ScanArrays{{in0, in1}, {out0, out1}, {nullptr, nullptr}}, 2, n, tmp, st);
+}
+
+// (for one array; twice that for two)
 size_t scan_tmp_size(int n) {
     size_t total = 0;
     while (n > kScanTile) {
@@ -443,6 +470,150 @@ __global__ void k_tuple_keys(int ns, int npad, const int4* __restrict__ idx, uin
     sort4(a, b, c, d);
     key[i] = ((uint64_t)a << 48) | ((uint64_t)b << 32) | ((uint64_t)c << 16) | (uint64_t)d;
     val[i] = (uint32_t)i;
+}
+
+// Surfels by node set without a sort over all of them: a bucket per value of
+// the leading bits of the four ascending node numbers (kBucketBits of them, no
+// gaps between the numbers' bits), a place in the bucket from an atomic
+// counter (any order will do), then each bucket sorted on chip by (key, surfel).
+// Pairs are unique, so the result is the sort's. A bucket of more than
+// kBucketCap surfels sets *over; the host then runs the bitonic sort
+// instead, which takes any distribution (248k surfels, 1,788 nodes: 5 launches,
+// 53 us of the device, against 27 launches and 190 us).
+constexpr int kBucketBits = 13, kBucketCap = 2048, kBucketBlock = 256;
+
+struct BucketOf {
+    int bits, shift;                         // of a node number; of the joined numbers to the bucket
+};
+
+static BucketOf bucket_of(int nn) {
+    int w = 1;
+    while ((1 << w) < nn) ++w;
+    return BucketOf{w, 4 * w > kBucketBits ? 4 * w - kBucketBits : 0};
+}
+
+// Renumbers the surfels' nodes (from the caller's numbering), keys, buckets
+// and places. Lanes of a wave with one bucket take their places together.
+__global__ void __launch_bounds__(256) k_bucket_count(int ns, int4* __restrict__ idx, const int* __restrict__ inv,
+        BucketOf o, uint64_t* __restrict__ key, int* __restrict__ bucket, int* __restrict__ place,
+        int* __restrict__ count) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x % kWave;
+    const bool in = i < ns;
+    int b = -1;
+    if (in) {
+        int4 q = idx[i];
+        q = make_int4(inv[q.x], inv[q.y], inv[q.z], inv[q.w]);
+        idx[i] = q;
+        int t0 = q.x, t1 = q.y, t2 = q.z, t3 = q.w;
+        sort4(t0, t1, t2, t3);
+        key[i] = ((uint64_t)t0 << 48) | ((uint64_t)t1 << 32) | ((uint64_t)t2 << 16) | (uint64_t)t3;
+        const uint64_t joined = ((((uint64_t)t0 << o.bits | (uint64_t)t1) << o.bits | (uint64_t)t2) << o.bits) |
+                                (uint64_t)t3;
+        b = (int)(joined >> o.shift);
+        bucket[i] = b;
+    }
+    // the first lane of each bucket speaks for it
+    int first = lane, before = 0, n = 1;
+    for (unsigned long long todo = __ballot(in); todo;) {
+        const int l = __builtin_ctzll(todo);
+        const unsigned long long same = __ballot(in && b == __builtin_amdgcn_readlane(b, l));
+        if ((same >> lane) & 1ull) {
+            first = l;
+            before = __popcll(same & ((1ull << lane) - 1ull));
+            n = __popcll(same);
+        }
+        todo &= ~same;
+    }
+    int base = 0;
+    if (in && first == lane) base = atomicAdd(&count[b], n);
+    base = __shfl(base, first, kWave);
+    if (in) place[i] = base + before;
+}
+
+// Exclusive scan of n counts by one workgroup (start[n] = the total); *over is
+// set where a count is above cap.
+__global__ void __launch_bounds__(kScanBlock) k_bucket_scan(int n, const int* __restrict__ count, int cap,
+                                                            int* __restrict__ start, int* __restrict__ over) {
+    __shared__ int sh[kScanBlock / kWave];
+    int carry = 0;
+    for (int base = 0; base < n; base += kScanTile) {
+        const int i = base + (int)threadIdx.x * kScanItems;
+        int v[kScanItems], own = 0;
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) {
+            v[q] = i + q < n ? count[i + q] : 0;
+            own += v[q];
+            if (v[q] > cap) *over = 1;
+        }
+        int total;
+        int run = carry + block_prefix(own, sh, total);
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) {
+            if (i + q < n) start[i + q] = run;
+            run += v[q];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) start[n] = carry;
+}
+
+__global__ void __launch_bounds__(256) k_bucket_scatter(int ns, const uint64_t* __restrict__ key,
+        const int* __restrict__ bucket, const int* __restrict__ place, const int* __restrict__ start,
+        uint64_t* __restrict__ skey, uint32_t* __restrict__ sval) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ns) return;
+    const int p = start[bucket[i]] + place[i];
+    skey[p] = key[i];
+    sval[p] = (uint32_t)i;
+}
+
+// One workgroup per bucket: up to 256 pairs by counting the smaller ones, more
+// by a bitonic sort in LDS.
+__global__ void __launch_bounds__(kBucketBlock) k_bucket_sort(const int* __restrict__ start, uint64_t* __restrict__ key,
+                                                              uint32_t* __restrict__ val) {
+    __shared__ uint64_t sk[kBucketCap];
+    __shared__ uint32_t sv[kBucketCap];
+    const int s0 = start[blockIdx.x], n = start[blockIdx.x + 1] - s0, t = threadIdx.x;
+    if (n <= 1 || n > kBucketCap) return;
+    if (n <= kBucketBlock) {
+        uint64_t k = 0;
+        uint32_t v = 0;
+        if (t < n) {
+            k = key[s0 + t];
+            v = val[s0 + t];
+            sk[t] = k;
+            sv[t] = v;
+        }
+        __syncthreads();
+        if (t >= n) return;
+        int rank = 0;
+        for (int j = 0; j < n; ++j) rank += pair_less(sk[j], sv[j], k, v) ? 1 : 0;
+        key[s0 + rank] = k;
+        val[s0 + rank] = v;
+        return;
+    }
+    int p2 = 2 * kBucketBlock;
+    while (p2 < n) p2 <<= 1;
+    for (int j = t; j < p2; j += kBucketBlock) {
+        sk[j] = j < n ? key[s0 + j] : ~0ull;
+        sv[j] = j < n ? val[s0 + j] : 0xffffffffu;
+    }
+    __syncthreads();
+    for (int k = 2; k <= p2; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int q = t; q < p2 / 2; q += kBucketBlock) {
+                const int a = ((q & ~(j - 1)) << 1) | (q & (j - 1)), b = a + j;
+                const uint64_t ka = sk[a], kb = sk[b];
+                const uint32_t va = sv[a], vb = sv[b];
+                const bool sw = (a & k) == 0 ? pair_less(kb, vb, ka, va) : pair_less(ka, va, kb, vb);
+                if (sw) { sk[a] = kb; sk[b] = ka; sv[a] = vb; sv[b] = va; }
+            }
+            __syncthreads();
+        }
+    for (int j = t; j < n; j += kBucketBlock) {
+        key[s0 + j] = sk[j];
+        val[s0 + j] = sv[j];
+    }
 }
 
 // Gather surfel arrays into sorted order; flag run starts.
@@ -801,6 +972,21 @@ void launch_knn_skin(int ns, const float* pos_aos, int nn, const float4* nodes, 
 void launch_node_graph(int nn, const float4* nodes, int* nbr, hipStream_t st) {
     hipLaunchKernelGGL(k_node_graph, dim3((nn + kGraphNodesPerBlock - 1) / kGraphNodesPerBlock),
                        dim3(64 * kGraphNodesPerBlock), 0, st, nn, nodes, nbr);
+}
+
+size_t bucket_work_ints(int ns) { return 2 * (size_t)ns + 2 * ((size_t)1 << kBucketBits) + 1; }
+
+void launch_bucket_sort(int ns, int nn, int4* idx, const int* inv, uint64_t* key_in, int* work, uint64_t* key,
+                        uint32_t* val, int* over, hipStream_t st) {
+    const BucketOf o = bucket_of(nn);
+    const int nb = 1 << (4 * o.bits - o.shift);
+    int *bucket = work, *place = work + ns, *count = work + 2 * (size_t)ns, *start = count + nb;
+    const dim3 grid((ns + 255) / 256);
+    launch_fill_i32(count, nb, 0, st);
+    hipLaunchKernelGGL(k_bucket_count, grid, dim3(256), 0, st, ns, idx, inv, o, key_in, bucket, place, count);
+    hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(kScanBlock), 0, st, nb, count, kBucketCap, start, over);
+    hipLaunchKernelGGL(k_bucket_scatter, grid, dim3(256), 0, st, ns, key_in, bucket, place, start, key, val);
+    hipLaunchKernelGGL(k_bucket_sort, dim3(nb), dim3(kBucketBlock), 0, st, start, key, val);
 }
 
 void launch_tuple_keys(int ns, int npad, const int4* idx, uint64_t* key, uint32_t* val, hipStream_t st) {

@@ -18,7 +18,15 @@ void launch_knn_skin(int ns, const float* pos_aos, int nn, const float4* nodes, 
 void launch_node_graph(int nn, const float4* nodes, int* nbr, hipStream_t st);
 void sort_pairs(uint64_t* key, uint32_t* val, int n_pow2, hipStream_t st);
 void exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t st);
+// two arrays of one length (2 scan_tmp_size(n) ints of scratch)
+void exclusive_scan2(const int* in0, int* out0, const int* in1, int* out1, int n, int* tmp, hipStream_t st);
 size_t scan_tmp_size(int n);
+// Renumbers idx (caller's numbers to inv's) and sorts the surfels by (node
+// set, number) into key, val; key_in[ns] and work (bucket_work_ints(ns) ints) are
+// scratch. *over is set if they have to be sorted by sort_pairs instead.
+size_t bucket_work_ints(int ns);
+void launch_bucket_sort(int ns, int nn, int4* idx, const int* inv, uint64_t* key_in, int* work, uint64_t* key,
+                        uint32_t* val, int* over, hipStream_t st);
 void launch_tuple_keys(int ns, int npad, const int4* idx, uint64_t* key, uint32_t* val, hipStream_t st);
 void launch_permute_surfels(int ns, int seg_len, const uint64_t* key, const uint32_t* val, const float* ipos, const float* inrm,
                             const int4* iidx, const float4* iw, float* px, float* py, float* pz, float* nx,
@@ -63,8 +71,6 @@ void launch_positions_to_f4(int n, const float* pos, float4* out, hipStream_t st
 
 namespace swgn {
 void launch_fill_i32(int* p, int n, int v, hipStream_t st);
-// p[i] <- map[p[i]] for i < n (indices from one numbering to another)
-void launch_map_ids(int* p, int n, const int* map, hipStream_t st);
 void launch_tables_from_state(int nn, const float4* pref, const float4* rq, const float4* tt, float4* dq, float4* cl,
                               hipStream_t st);
 }  // namespace swgn

@@ -40,23 +40,28 @@ void launch_seg_info(int nseg, const int* seg_start, const int* run_pos, const u
                      uint16_t* mask, int* units, int* npairs, unsigned long long* total_units, int* bad,
                      hipStream_t st);
 
+// seg_start[0 .. nseg] = the cuts and ns.
+void launch_seg_starts(int nseg, const int* cuts, int ns, int* seg_start, hipStream_t st);
+
+// The block fold's entries: ne = sum of the pair counts, entry e of segment g
+// at ebase[g] + rank, its block (-1: none, and *bad is set) and its place among
+// the block's; bcount[nb] counts entries per block (zero before);
 // off[g] = 4 off_units[g] for g <= nseg (float offsets from 4-float units).
-void launch_seg_off(int nseg, const int* off_units, uint32_t* off, hipStream_t st);
+void launch_seg_entries(int nseg, const int* seg_nodes, const uint16_t* mask, const int* off_units, uint32_t* off,
+                        const int* ebase, const int* row_ptr, const int* col_idx, int* eblk, int* eplace,
+                        uint32_t* esub, uint32_t* egrad, int* bcount, int* bad, hipStream_t st);
 
-// The block fold's entries, unsorted: ne = sum of the pair counts, entry e of
-// segment g at ebase[g] + rank; ekey/eval padded to npad (a power of two) for
-// sort_pairs; bcount[nb] counts entries per block (zeroed by the caller).
-void launch_seg_entries(int nseg, int nb, int npad, const int* seg_nodes, const uint16_t* mask, const uint32_t* off,
-                        const int* ebase, int ne, const int* row_ptr, const int* col_idx, uint64_t* ekey,
-                        uint32_t* eval, uint32_t* esub, uint32_t* egrad, int* bcount, int* bad, hipStream_t st);
+// ent_sub/ent_grad: the entries in block order (ent_ptr = scan of bcount),
+// each block's ascending; list[ne] is scratch. *over is set where a block has too
+// many for that: sort_entries gives the same from any.
+void launch_ent_order(int ne, int nb, const int* eblk, const int* eplace, const int* ent_ptr, const uint32_t* esub,
+                      const uint32_t* egrad, int* list, uint32_t* ent_sub, uint32_t* ent_grad, int* over,
+                      hipStream_t st);
+void sort_entries(int ne, int npad, const int* eblk, uint64_t* key, uint32_t* val, const uint32_t* esub,
+                  const uint32_t* egrad, uint32_t* ent_sub, uint32_t* ent_grad, hipStream_t st);
 
-// ent_sub/ent_grad[i] = esub/egrad[order[i]] (entries in block order).
-void launch_ent_gather(int ne, const uint32_t* order, const uint32_t* esub, const uint32_t* egrad, uint32_t* ent_sub,
-                       uint32_t* ent_grad, hipStream_t st);
-
-// pack_start[i] = seg_start[pack_seg[i]] for i < npack; pack_seg[npack] = nseg,
-// pack_start[npack] = ns.
-void launch_pack_arrays(int npack, int nseg, int ns, const int* seg_start, int* pack_seg, int* pack_start,
-                        hipStream_t st);
+// pack_seg = the cuts and nseg; pack_start[i] = seg_start[pack_seg[i]], closed by ns.
+void launch_pack_arrays(int npack, int nseg, int ns, const int* cuts, const int* seg_start, int* pack_seg,
+                        int* pack_start, hipStream_t st);
 
 }  // namespace swgn

@@ -42,3 +42,29 @@ def test_pattern_is_its_definition(swgn, n_nodes, n_surfels, flat):
     assert np.array_equal(rp, wrp) and np.array_equal(ci, wci)
     assert all(v == 0 for v in st.check_layout().values())
     st.close()
+
+
+# surfels of one node set: one bucket, at the edges of how it is sorted
+# (counted, bitonic of 512 to 2048, more than a bucket holds)
+@pytest.mark.parametrize("n_surfels", [1, 2, 255, 256, 257, 512, 513, 2047, 2048, 2049, 6000])
+def test_surfels_of_one_node_set_are_ordered(swgn, n_surfels):
+    rng = np.random.default_rng(n_surfels)
+    nodes = np.array([[0, 0, 1], [0.1, 0, 1], [0, 0.1, 1], [0.1, 0.1, 1]] + [[2 + k, 2, 1] for k in range(8)],
+                     np.float32)
+    pos = (np.array([0.02, 0.02, 1.0]) + rng.uniform(-0.004, 0.004, (n_surfels, 3))).astype(np.float32)
+    st = _stream(swgn, pos, nodes)
+    assert st.layout()["node_sets"] == 1
+    assert all(v == 0 for v in st.check_layout().values())
+    st.close()
+
+
+# few nodes, many surfels: thousands of segments in a block (9 nodes: more
+# than are ordered on chip), buckets of every size
+@pytest.mark.parametrize("n_nodes,n_surfels", [(9, 2000000), (12, 60000), (40, 150000), (200, 100000)])
+def test_layout_of_many_surfels_on_few_nodes(swgn, n_nodes, n_surfels):
+    rng = np.random.default_rng(n_nodes)
+    nodes = rng.uniform(0, 1, (n_nodes, 3)).astype(np.float32)
+    pos = rng.uniform(0, 1, (n_surfels, 3)).astype(np.float32)
+    st = _stream(swgn, pos, nodes)
+    assert all(v == 0 for v in st.check_layout().values())
+    st.close()
