@@ -5,8 +5,8 @@
 //
 //   append_eval   one thread per depth pixel. A candidate (normal present,
 //                 no fused surfel) takes the 4 nearest live node positions
-//                 c_j = T_j p_j (FP32 key, ties to the lower index; the node
-//                 positions pass through LDS in tiles). Node i stays in the
+//                 c_j = T_j p_j (FP32 key, ties to the lower index; runs of
+//                 nodes too far for the wave are skipped). Node i stays in the
 //                 set only if (1 - eps)^2 |p_i - p_0|^2 < |c_i - c_0|^2 <
 //                 (1 + eps)^2 |p_i - p_0|^2 (Eq. 7 on squares, FP32); the
 //                 nearest always stays. The candidate is far if the plain
@@ -28,13 +28,13 @@
 //                 the appended ones copied into fresh caller-order arrays.
 #include "swgn_fusion.h"
 #include "swgn_impl.h"
+#include "swgn_knn.h"
 #include "swgn_launch.h"
 
 namespace swgn {
 
 namespace {
 
-constexpr int kAppendTile = 1024;      // live node positions staged per pass
 constexpr float kFdStep = 1e-3f;       // central-difference step of Eq. 8
 
 // Reference position (and normal) of live point x through the inverse of the
@@ -81,8 +81,6 @@ __device__ __forceinline__ float max_eig_sym3(float m00, float m01, float m02, f
 }
 
 __global__ void __launch_bounds__(256) k_append_eval(AppendArgs a) {
-    __shared__ float4 tile[kAppendTile];
-    __shared__ int tid[kAppendTile];
     const int u = blockIdx.x * blockDim.x + threadIdx.x;
     const int npx = a.cam.W * a.cam.H;
     const bool in = u < npx;
@@ -91,22 +89,17 @@ __global__ void __launch_bounds__(256) k_append_eval(AppendArgs a) {
     const int x = in ? u % a.cam.W : 0, y = in ? u / a.cam.W : 0;
     const float d = nm.w;
     const float3 V = make_float3((((float)x - a.cam.cx) / a.cam.fx) * d, (((float)y - a.cam.cy) / a.cam.fy) * d, d);
-    float kd[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
-    int ki[4] = {0, 0, 0, 0};
-    for (int base = 0; base < a.nn; base += kAppendTile) {
-        const int cnt = min(kAppendTile, a.nn - base);
-        __syncthreads();
-        for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
-            tile[t] = a.cl[base + t];
-            tid[t] = a.node_id[base + t];
-        }
-        __syncthreads();
-        if (cand) {
-            for (int t = 0; t < cnt; ++t) {
-                const float4 c = tile[t];
-                const float dx = V.x - c.x, dy = V.y - c.y, dz = V.z - c.z;
-                knn_insert_lex<4>(kd, ki, (dx * dx + dy * dy) + dz * dz, tid[t]);
-            }
+    // (a scan of all nodes by every candidate, its list in scratch memory:
+    // 140 us of 320x240 pixels and 500 nodes, 46 us so)
+    float kd[4];
+    int ki[4];
+    {
+        uint64_t kk[4];
+        nearest4(kk, V.x, V.y, V.z, cand, a.nn, a.cl, a.node_id, a.boxes);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            kd[q] = __uint_as_float((uint32_t)(kk[q] >> 32));
+            ki[q] = (int)(uint32_t)kk[q];
         }
     }
     // the nearest set, found in the caller's node numbering (ties to the
@@ -267,6 +260,7 @@ void launch_compact_surfels(const CompactArgs& c, hipStream_t st) {
 void launch_append(const AppendArgs& a, int* pos, int* scan_tmp, hipStream_t st) {
     const int npx = a.cam.W * a.cam.H;
     const dim3 g((npx + 255) / 256);
+    launch_node_boxes(a.nn, a.cl, a.boxes, st);
     hipLaunchKernelGGL(k_append_eval, g, dim3(256), 0, st, a);
     exclusive_scan(a.flag, pos, npx + 1, scan_tmp, st);
     hipLaunchKernelGGL(k_append_write, g, dim3(256), 0, st, a, pos);

@@ -33,6 +33,7 @@
 #include "swgn.h"
 #include "swgn_frame.h"
 #include "swgn_impl.h"
+#include "swgn_knn.h"
 #include "swgn_launch.h"
 
 using namespace swgn;
@@ -1670,6 +1671,7 @@ void run_append(sw_stream s, int32_t max_out, int32_t* pixel, float* pos, float*
     const int npx = h.npx;
     if (!s->aflag) {
         s->aflag = s->append_mem.alloc<int>(npx + 1);
+        s->aboxes = s->append_mem.alloc<float4>(knn_box_count(kMaxNodes));
         s->apos = s->append_mem.alloc<int>(npx + 1);
         s->ascan = s->append_mem.alloc<int>(scan_tmp_size(npx + 1));
         s->acount = s->append_mem.alloc<int>(4);
@@ -1693,6 +1695,7 @@ void run_append(sw_stream s, int32_t max_out, int32_t* pixel, float* pos, float*
     a.cl = h.cl;
     a.pref = h.pref;
     a.node_id = s->d_node_id;
+    a.boxes = s->aboxes;
     a.node_inv = s->d_node_inv;
     a.dq = h.dq;
     a.flag = s->aflag;

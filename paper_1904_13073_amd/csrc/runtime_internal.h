@@ -182,7 +182,7 @@ struct sw_stream_s {
     // append-candidate workspace, allocated on first use
     swgn::rt::Arena append_mem;
     int *aflag = nullptr, *apos = nullptr, *ascan = nullptr, *acount = nullptr;
-    float4 *asv = nullptr, *asn = nullptr;
+    float4 *asv = nullptr, *asn = nullptr, *aboxes = nullptr;
     int* apix = nullptr;                  // staging of host outputs, capacity npx
     float *apos3 = nullptr, *anrm3 = nullptr, *arad = nullptr, *aconf = nullptr;
     bool surfels_set = false;

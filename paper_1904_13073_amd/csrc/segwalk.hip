@@ -99,7 +99,15 @@ __global__ void k_pack_next(int nseg, const int* __restrict__ seg_start, int M, 
 }
 
 __device__ __forceinline__ void stage_chunk(const int* __restrict__ next, int lo, int hi, int* nx) {
-    for (int i = lo + (int)threadIdx.x; i < hi; i += kChainBlock) nx[i - lo] = next[i];
+    // (8 loads of a thread on their way at once)
+    for (int i0 = lo + (int)threadIdx.x; i0 < hi; i0 += 8 * kChainBlock) {
+        int v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = next[min(i0 + q * kChainBlock, hi - 1)];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (i0 + q * kChainBlock < hi) nx[i0 + q * kChainBlock - lo] = v[q];
+    }
     __syncthreads();
 }
 

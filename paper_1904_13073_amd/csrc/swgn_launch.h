@@ -12,7 +12,6 @@ namespace swgn {
 // 4 nearest nodes (caller indices) and weights of every surfel; nodes in the
 // library's order with their caller indices; boxes holds knn_box_count(nn)
 // float4 of scratch.
-size_t knn_box_count(int nn);
 void launch_knn_skin(int ns, const float* pos_aos, int nn, const float4* nodes, const int* caller, float4* boxes,
                      float inv_two_sigma2, int4* idx, float4* w, hipStream_t st);
 void launch_node_graph(int nn, const float4* nodes, int* nbr, hipStream_t st);
