@@ -131,39 +131,6 @@ __device__ __forceinline__ void slot_step2(float& u0, float& v0, float& u1, floa
 #undef SWGN_MAC4
 #undef SWGN_MAC
 }
-// Sums over the wave of four values at once, each the butterfly sum in the
-// order 32, 16, 8, 4, 2, 1: the values share the lanes as the sums halve, so
-// 7 additions serve all four. Returns value 0, 2, 1, 3 in rows 0, 1, 2, 3 of
-// 16 lanes.
-__device__ __forceinline__ void swap32(double& a, double& b) {
-    const u64 x = (u64)__double_as_longlong(a), y = (u64)__double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane32_swap((int)(unsigned)x, (int)(unsigned)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((int)(unsigned)(x >> 32), (int)(unsigned)(y >> 32), false, false);
-    a = __longlong_as_double((long long)(((u64)(unsigned)hi[0] << 32) | (unsigned)lo[0]));
-    b = __longlong_as_double((long long)(((u64)(unsigned)hi[1] << 32) | (unsigned)lo[1]));
-}
-__device__ __forceinline__ void swap16(double& a, double& b) {
-    const u64 x = (u64)__double_as_longlong(a), y = (u64)__double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((int)(unsigned)x, (int)(unsigned)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((int)(unsigned)(x >> 32), (int)(unsigned)(y >> 32), false, false);
-    a = __longlong_as_double((long long)(((u64)(unsigned)hi[0] << 32) | (unsigned)lo[0]));
-    b = __longlong_as_double((long long)(((u64)(unsigned)hi[1] << 32) | (unsigned)lo[1]));
-}
-__device__ __forceinline__ double wave_sum4(const double (&v)[4]) {
-    double a = v[0], b = v[1], c = v[2], d = v[3];
-    swap32(a, b);
-    a += b;
-    swap32(c, d);
-    c += d;
-    swap16(a, c);
-    a += c;
-    a += xchg<8>(a);
-    a += xchg<4>(a);
-    a += xchg<2>(a);
-    a += xchg<1>(a);
-    return a;
-}
-
 // Component `sub` of a node's z and p into its vec entries (components 4 and 5
 // at two quad positions each; the lanes that have nothing to write, write the
 // node's fifth float4).

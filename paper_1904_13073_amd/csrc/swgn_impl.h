@@ -339,6 +339,39 @@ __device__ __forceinline__ int wave_sumi(int v) {
     return v;
 }
 
+// Sums over the wave of four values at once, each the butterfly sum in the
+// order 32, 16, 8, 4, 2, 1: the values share the lanes as the sums halve, so
+// 7 additions serve all four. Returns value 0, 2, 1, 3 in rows 0, 1, 2, 3 of
+// 16 lanes.
+__device__ __forceinline__ void swap32(double& a, double& b) {
+    const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((int)(unsigned)x, (int)(unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((int)(unsigned)(x >> 32), (int)(unsigned)(y >> 32), false, false);
+    a = __longlong_as_double((long long)(((unsigned long long)(unsigned)hi[0] << 32) | (unsigned)lo[0]));
+    b = __longlong_as_double((long long)(((unsigned long long)(unsigned)hi[1] << 32) | (unsigned)lo[1]));
+}
+__device__ __forceinline__ void swap16(double& a, double& b) {
+    const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((int)(unsigned)x, (int)(unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((int)(unsigned)(x >> 32), (int)(unsigned)(y >> 32), false, false);
+    a = __longlong_as_double((long long)(((unsigned long long)(unsigned)hi[0] << 32) | (unsigned)lo[0]));
+    b = __longlong_as_double((long long)(((unsigned long long)(unsigned)hi[1] << 32) | (unsigned)lo[1]));
+}
+__device__ __forceinline__ double wave_sum4(const double (&v)[4]) {
+    double a = v[0], b = v[1], c = v[2], d = v[3];
+    swap32(a, b);
+    a += b;
+    swap32(c, d);
+    c += d;
+    swap16(a, c);
+    a += c;
+    a += xchg<8>(a);
+    a += xchg<4>(a);
+    a += xchg<2>(a);
+    a += xchg<1>(a);
+    return a;
+}
+
 // Block sum over blockDim.x (multiple of 64, <= 1024) threads; result valid in thread 0.
 __device__ __forceinline__ double block_sum(double v, double* sh) {
     v = wave_sum(v);
