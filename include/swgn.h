@@ -503,11 +503,11 @@ sw_status sw_get_layout(sw_stream s, sw_layout* out);
  * successor chains); this call redoes the cut with the plain sequential walk
  * on the host, from the same sorted surfels and block pattern, and writes
  * into differ[9] the number of differing elements (plus any difference in
- * length) of: segment starts, pair masks, Gram offsets (and their total),
- * block entry pointers, entry sub-block offsets, entry J^T r offsets, pack
- * starts, pack first segments, per-surfel node positions. All zero means the
- * two agree exactly. Synchronises the stream; host memory of order the
- * surfel count. */
+ * length) of: segment starts (and surfels out of order), pair masks, Gram
+ * offsets (and their total), block entry pointers, entry sub-block offsets,
+ * entry J^T r offsets, pack starts, pack first segments, per-surfel node
+ * positions. All zero means the two agree exactly. Synchronises the stream;
+ * host memory of order the surfel count. */
 sw_status sw_check_layout(sw_stream s, int64_t* differ);
 
 /* ---- parity and debug exports (host pointers, caller's surfel order) ---- */

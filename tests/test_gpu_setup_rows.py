@@ -68,3 +68,28 @@ def test_layout_of_many_surfels_on_few_nodes(swgn, n_nodes, n_surfels):
     st = _stream(swgn, pos, nodes)
     assert all(v == 0 for v in st.check_layout().values())
     st.close()
+
+
+def test_models_in_turn_on_one_stream_equal_fresh_streams(swgn, scene_cache):
+    """A model takes over the device memory of the last one unless it is much
+    smaller or larger; either way it solves, fuses and grows as on a fresh stream."""
+    s = scene_cache("c1")
+    n = len(s.surfel_pos)
+
+    def step(st, m):
+        st.set_reference_surfels(s.surfel_pos[:m], s.surfel_nrm[:m])
+        st.set_node_graph(s.node_pos)
+        out = [st.solve_frame(s.depth)["e_data"], st.node_se3()]
+        st.fuse_frame(s.depth, 1)
+        st.update_geometry()
+        return out + list(st.reference_surfels()) + list(st.surfel_attributes()) + [st.check_layout()]
+
+    st = swgn.Stream(swgn.config_for(s))
+    for m in (n, (3 * n) // 5, n, n // 8, n // 6, n, n):
+        fresh = swgn.Stream(swgn.config_for(s))
+        got, want = step(st, m), step(fresh, m)
+        fresh.close()
+        assert all(v == 0 for v in got.pop().values()) and want.pop()
+        for k, (a, b) in enumerate(zip(got, want)):
+            assert np.array_equal(a, b), (m, k)
+    st.close()
