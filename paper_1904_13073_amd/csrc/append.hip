@@ -262,7 +262,7 @@ void launch_append(const AppendArgs& a, int* pos, int* scan_tmp, hipStream_t st)
     const dim3 g((npx + 255) / 256);
     launch_node_boxes(a.nn, a.cl, a.boxes, st);
     hipLaunchKernelGGL(k_append_eval, g, dim3(256), 0, st, a);
-    exclusive_scan(a.flag, pos, npx + 1, scan_tmp, st);
+    exclusive_scan(a.flag, pos, npx, scan_tmp, st);
     hipLaunchKernelGGL(k_append_write, g, dim3(256), 0, st, a, pos);
 }
 

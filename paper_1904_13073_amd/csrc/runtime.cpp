@@ -1670,10 +1670,10 @@ void run_append(sw_stream s, int32_t max_out, int32_t* pixel, float* pos, float*
     const FrameDesc& h = s->h;
     const int npx = h.npx;
     if (!s->aflag) {
-        s->aflag = s->append_mem.alloc<int>(npx + 1);
+        s->aflag = s->append_mem.alloc<int>(npx);
         s->aboxes = s->append_mem.alloc<float4>(knn_box_count(kMaxNodes));
         s->apos = s->append_mem.alloc<int>(npx + 1);
-        s->ascan = s->append_mem.alloc<int>(scan_tmp_size(npx + 1));
+        s->ascan = s->append_mem.alloc<int>(scan_tmp_size(npx));
         s->acount = s->append_mem.alloc<int>(4);
         s->asv = s->append_mem.alloc<float4>(npx);
         s->asn = s->append_mem.alloc<float4>(npx);
@@ -1711,7 +1711,6 @@ void run_append(sw_stream s, int32_t max_out, int32_t* pixel, float* pos, float*
         a.out_conf = s->aconf;
     }
     launch_fill_i32(s->acount, 4, 0, st);
-    launch_fill_i32(s->aflag + npx, 1, 0, st);
     launch_append(a, s->apos, s->ascan, st);
     SWGN_HIP(hipGetLastError());
     int* hc = s->fcount_host;
@@ -1776,12 +1775,11 @@ sw_status sw_update_geometry(sw_stream s, sw_geometry_stats* stats) {
         // which existing surfels stay (caller order), and where
         Arena& tmp = s->geo_mem;
         tmp.reset();
-        int* flag = tmp.alloc<int>(ns + 1);
+        int* flag = tmp.alloc<int>(ns);
         int* pos = tmp.alloc<int>(ns + 1);
-        int* scan = tmp.alloc<int>(scan_tmp_size(ns + 1));
+        int* scan = tmp.alloc<int>(scan_tmp_size(ns));
         launch_keep_mark(ns, s->in_conf, s->in_tinit, s->t_now, s->cfg.stable_conf, s->cfg.t_low_confid, flag, st);
-        launch_fill_i32(flag + ns, 1, 0, st);
-        exclusive_scan(flag, pos, ns + 1, scan, st);
+        exclusive_scan(flag, pos, ns, scan, st);
         const int nkeep = read_scalar(pos + ns, st);
         const int64_t nnew = (int64_t)nkeep + napp;
         if (nnew < 1 || nnew >= kMaxSurfels)

@@ -56,7 +56,7 @@ struct AppendArgs {
     float4* boxes;                // scratch: boxes of the live node positions
     const int* node_id;           // [nn] the caller's index of each node (ties go to the lower)
     const int* node_inv;          // [nn] the library's index of each caller index
-    int* flag;                    // [npx + 1] survivor flags (the last stays 0)
+    int* flag;                    // [npx] survivor flags
     float4 *sv, *sn;              // [npx] reference position / normal of survivors
     int* counts;                  // [0] candidates, [1] far, [2] compressive
     int* out_pixel;
