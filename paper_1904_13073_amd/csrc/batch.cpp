@@ -101,6 +101,8 @@ sw_status sw_profile_stage(sw_batch b, const sw_stream* streams, int32_t n, int3
     return guarded(b->err, [&]() -> sw_status {
         std::vector<int> its(n, 0), ev;
         b->exec.bucket = shape_bucket(ss);
+        if (stage == kStAsmFold)
+            for (sw_stream s : ss) count_folds(b->exec, s, (int64_t)reps + 1);
         run_stage(b->exec, stage, ss, its, pcg_it, nullptr, false, ev);   // warm
         hipEvent_t e0 = b->exec.event(0), e1 = b->exec.event(1);
         SWGN_HIP(hipEventRecord(e0, b->exec.st));
@@ -147,6 +149,8 @@ sw_status sw_batch_autotune(sw_batch b, const sw_stream* streams, int32_t n, int
                 ex.tuned[key] = trial;
                 ex.bucket = key;
                 const int pit = (has_wide || stage == kStPcgStep) ? 1 : 0;
+                if (stage == kStAsmFold)
+                    for (sw_stream s : ss) count_folds(ex, s, (int64_t)reps + 1);
                 run_stage(ex, stage, ss, its, pit, nullptr, false, ev);
                 hipEvent_t e0 = ex.event(0), e1 = ex.event(1);
                 SWGN_HIP(hipEventRecord(e0, ex.st));

@@ -33,12 +33,14 @@
 // The exchange. A value travels as 64-bit words, each the iteration's tag in
 // the upper half and 32 bits of payload in the lower, written and read by
 // relaxed agent-scope atomics: a word is its own flag, so no fence, no cache
-// write-back and no second round trip is needed. The fold that precedes the
-// solve counts it, and a tag is the iteration in the range of that count, so
-// nothing has to be cleared (2^32 / kPcgTags solves later a tag comes again,
-// but every word a solve reads was written by the solve before). Words are double-buffered by iteration parity: a
-// workgroup writes iteration i + 2 only after it has every part of iteration
-// i + 1, which their owners publish after they have read all of iteration i.
+// write-back and no second round trip is needed. Every fold counts (also one
+// whose solve then runs step by step, and a replayed one), and a tag is the
+// iteration in the range of that count, so nothing has to be cleared between
+// solves. A tag comes again after 2^32 / kPcgTags folds; the host clears the
+// words before that many have passed. Words are double-buffered by iteration
+// parity: a workgroup writes iteration i + 2 only after it has every part of
+// iteration i + 1, which their owners publish after they have read all of
+// iteration i.
 //
 // Every workgroup of a stream must be resident for the others to get on, so
 // the host launches no more of them than the chip holds at once (a lease on

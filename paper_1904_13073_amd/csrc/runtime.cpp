@@ -760,12 +760,12 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
         if (got[1] <= pcg_halo(4)) s->pcg_sets4 = 1 + cdiv(got[1], pcg_rows(4));
         if (got[2] <= pcg_halo(8)) s->pcg_sets8 = 1 + cdiv(got[2], pcg_rows(8));
         if (s->pcg_sets4 > 0 || s->pcg_sets8 > 0) {
-            // the exchange words and the solve count, zero
-            const size_t xwords = 2 * kPcgCopies * pcg_part_words(h) + 2 * (size_t)nn * 12 + 1;
-            h.xpart = G.alloc<unsigned long long>(xwords);
+            // the exchange words and the fold count, zero
+            h.xpart = G.alloc<unsigned long long>(pcg_words(h) + 1);
             h.xuv = h.xpart + 2 * kPcgCopies * pcg_part_words(h);
-            h.xepoch = reinterpret_cast<int*>(h.xuv + 2 * (size_t)nn * 12);
-            launch_fill_i32(reinterpret_cast<int*>(h.xpart), (int)(2 * xwords), 0, st);
+            h.xepoch = reinterpret_cast<int*>(h.xpart + pcg_words(h));
+            launch_fill_i32(reinterpret_cast<int*>(h.xpart), (int)(2 * (pcg_words(h) + 1)), 0, st);
+            s->folds = 0;
         }
     }
     h.pcg_wait = pcg_wait_limit();
@@ -911,6 +911,14 @@ void enqueue_rigid(Executor& ex, const std::vector<sw_stream>& ss, bool timing, 
     }
     for (int i = 0; i < n; ++i) its[i] = ss[i]->cfg.rigid_iters > 0 ? 0 : -1;
     run_stage(ex, kStRigidCompose, ss, its, 0, nullptr, timing, ev);
+}
+
+void count_folds(Executor& ex, sw_stream s, int64_t n) {
+    if (!s->h.xpart) return;
+    s->folds += n;
+    if (s->folds <= kPcgTagFolds / 2) return;
+    launch_fill_i32(reinterpret_cast<int*>(s->h.xpart), (int)(2 * pcg_words(s->h)), 0, ex.st);
+    s->folds = n;
 }
 
 // One Gauss-Newton iteration for every stream with its[i] >= 0 (its[i] = the
@@ -1079,6 +1087,7 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         any_capture |= ss[i]->cfg.debug_iter >= 0 && ss[i]->cfg.debug_iter < ss[i]->cfg.gn_iters;
     }
     PcgLease lease(ex, ss);
+    for (sw_stream s : ss) count_folds(ex, s, s->cfg.gn_iters);
     enqueue_depth(ex, ss, depths, on_device, timing, ev);
     enqueue_rigid(ex, ss, timing, ev);
     std::vector<char> captured(n, 0);

@@ -190,6 +190,7 @@ struct sw_stream_s {
     // sets of local nodes the whole-solve kernel needs with workgroups of 4
     // and 8 waves (0: the node set does not fit it)
     int pcg_sets4 = 0, pcg_sets8 = 0;
+    int64_t folds = 0;                    // since the exchange words were last cleared
     int pcg_sets(int waves) const { return waves == 4 ? pcg_sets4 : pcg_sets8; }
     sw_server server = nullptr;           // set while attached to a serving loop
 
@@ -237,6 +238,9 @@ void enqueue_depth(Executor& ex, const std::vector<sw_stream>& ss, const float* 
 void enqueue_rigid(Executor& ex, const std::vector<sw_stream>& ss, bool timing, std::vector<int>& ev);
 void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std::vector<int>& its, bool timing,
                        std::vector<int>& ev, std::vector<char>& captured);
+// before n folds of the stream are enqueued: clears the whole solve's exchange
+// words if their tags could come again
+void count_folds(Executor& ex, sw_stream s, int64_t n);
 void enqueue_collect(Executor& ex, const std::vector<sw_stream>& ss);
 sw_status collect_frames(Executor& ex, const std::vector<sw_stream>& ss, const float* stage_us,
                          sw_frame_stats* stats, sw_status* status, std::vector<char>* stalled = nullptr);

@@ -216,6 +216,7 @@ void sw_server_s::run() {
             for (const Active& a : active) {
                 ss.push_back(a.t->s);
                 its.push_back(a.it < a.t->s->cfg.gn_iters ? a.it : -1);
+                if (its.back() >= 0) count_folds(exec, a.t->s, 1);
             }
             captured.assign(ss.size(), 0);
             PcgLease lease(exec, ss);

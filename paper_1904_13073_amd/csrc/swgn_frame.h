@@ -62,6 +62,7 @@ constexpr int kNodeBlock = 256;
 // itself) and a stream spreads over more CUs; with 8 waves each foreign column
 // serves more rows and there are fewer workgroups to meet.
 constexpr int kPcgTags = 8192;        // tags per solve (more than kMaxPcg)
+constexpr int64_t kPcgTagFolds = ((int64_t)1 << 32) / kPcgTags;   // folds until a tag comes again
 constexpr int kPcgMaxSlots = 24;
 constexpr int kPcgFar = 16;
 constexpr int kPcgPairSets = 5;
@@ -148,7 +149,7 @@ struct FrameDesc {
     const uint16_t *loc4, *loc8;
     const int *halo4, *halo8, *halo_n4, *halo_n8;
     unsigned long long *xpart, *xuv;
-    int* xepoch;                  // solves so far (the fold before each counts it): the words' tags follow from it
+    int* xepoch;                  // folds so far: the words' tags follow from it
     long long pcg_wait;           // longest wait of a workgroup for the others, in 10 ns
     const int *slot_u, *slot_t;   // [nb] ELL slot of each upper block and of its transpose (-1: diagonal)
     // resident: capture of one iteration (null unless requested)
@@ -221,6 +222,11 @@ __host__ __device__ inline size_t pcg_part_words(const FrameDesc& d) {
 }
 __host__ __device__ inline size_t pcg_part_word(int part, int q) {
     return (size_t)(part >> 2) * 32 + (size_t)((q >> 1) * 8 + (part & 3) * 2 + (q & 1));
+}
+
+// Exchange words of a stream (xpart, then xuv).
+__host__ __device__ inline size_t pcg_words(const FrameDesc& d) {
+    return 2 * kPcgCopies * pcg_part_words(d) + 2 * (size_t)d.nn * 12;
 }
 
 // Launch variant of a stage: bit 0 = tile order (kOrderXcd), bit 1 = the
