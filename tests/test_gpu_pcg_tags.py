@@ -19,20 +19,22 @@ def swgn():
     return gpu_lib()
 
 
-# a solve's last words: the sums of its only iteration; those and u, v of its last two
-@pytest.mark.parametrize("pcg,n_nodes", [(1, 200), (10, 300)])
-def test_words_of_a_solve_long_past_are_not_taken_for_new(swgn, pcg, n_nodes):
-    s = _surface(n_nodes, n_nodes)
-    other = (s["depth"] + np.float32(0.01)).astype(np.float32)
-    want = _stream(swgn, s, pcg_iters=pcg, gn_iters=1, stage_timing=1)
-    st = _stream(swgn, s, pcg_iters=pcg, gn_iters=1, stage_timing=1)
+def test_words_of_a_solve_long_past_are_not_taken_for_new(swgn):
+    """One PCG iteration, so that a solve's first words are its last. Streams
+    of 65 workgroups, one per CU: the fourth's start at different times, and
+    the early ones look for the words of those that have not started."""
+    scenes = [_surface(4100, k) for k in range(5)]
+    first = [s["depth"] for s in scenes]
+    other = [(d + np.float32(0.01)).astype(np.float32) for d in first]
+    sides = [[_stream(swgn, s, pcg_iters=1, gn_iters=1) for s in scenes] for _ in range(2)]
     bx = swgn.Batch()
-    for x in (want, st):
-        assert x.solve_frame(s["depth"])["stage_us"][3] > 0      # (whole)
-    folds = [100001] * 5 + [TAG_FOLDS - 1 - 5 * 100001]             # (a replay is reps launches and one before)
-    for n in folds:
-        bx.profile_stage([st], FOLD, reps=n - 1)
-    _same((st.solve_frame(other), st.node_se3()), (want.solve_frame(other), want.node_se3()), pcg)
+    for sts in sides:
+        bx.solve(sts, first)
+    for n in [100001] * 5 + [TAG_FOLDS - 1 - 5 * 100001]:           # (a replay is reps launches and one before)
+        bx.profile_stage(sides[0][3:4], FOLD, reps=n - 1)
+    got, want = ([(r, st.node_se3()) for r, st in zip(bx.solve(sts, other)[0], sts)] for sts in sides)
+    for k in range(5):
+        _same(got[k], want[k], k)
     bx.close()
-    want.close()
-    st.close()
+    for st in sides[0] + sides[1]:
+        st.close()
