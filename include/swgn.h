@@ -510,6 +510,18 @@ sw_status sw_get_layout(sw_stream s, sw_layout* out);
  * host memory of order the surfel count. */
 sw_status sw_check_layout(sw_stream s, int64_t* differ);
 
+/* How the stream's linear solves (one per Gauss-Newton iteration) have run
+ * since the stream was created, by whatever executor; graph replays count as
+ * the frames they solve. */
+typedef struct sw_solve_counts {
+    int64_t whole;              /* in one launch */
+    int64_t stepwise;           /* one or two launches per PCG iteration */
+    int64_t redone;             /* frames solved again step by step (sw_set_node_graph) */
+    int64_t waits;              /* waits given up by waves of the solves of those frames */
+    int64_t captures;           /* HIP graphs captured of batches with the stream */
+} sw_solve_counts;
+sw_status sw_get_solve_counts(sw_stream s, sw_solve_counts* out);
+
 /* ---- parity and debug exports (host pointers, caller's surfel order) ---- */
 
 /* Skinning: idx4 (n_surfels x 4, nearest first) and weights w4 (n_surfels x 4). */

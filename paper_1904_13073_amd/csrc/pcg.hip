@@ -454,7 +454,7 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves == 4 && kSets > kPcgPairSe
                         if (t0 == 0) t0 = now;
                         if (now - t0 > t_limit) {
                             *(volatile int*)&stalled = 1;
-                            if (lane == 0) atomicOr(flags + 1, 1);
+                            if (lane == 0) atomicAdd(flags + 1, 1);
                         }
                     }
                     if (*(volatile int*)&stalled != 0) break;

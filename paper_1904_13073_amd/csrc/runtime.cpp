@@ -913,6 +913,36 @@ void enqueue_rigid(Executor& ex, const std::vector<sw_stream>& ss, bool timing, 
     run_stage(ex, kStRigidCompose, ss, its, 0, nullptr, timing, ev);
 }
 
+// The launch of whole solves that each stream of a Gauss-Newton iteration goes
+// into (0, 1, ...; as many streams per launch as the lease has waves for); -1:
+// its linear solve runs step by step, or it has none.
+static std::vector<int> whole_launches(const Executor& ex, const std::vector<sw_stream>& ss,
+                                       const std::vector<int>& its) {
+    const int n = (int)ss.size();
+    std::vector<int> launch(n, -1);
+    if (ex.pcg_lease == 0) return launch;
+    int at = 0, waves = 0;
+    for (int i = 0; i < n; ++i) {
+        const int w = its[i] >= 0 ? whole_solve_waves(ex, ss[i]) : 0;
+        if (w == 0) continue;
+        // (with the whole device leased, workgroups start in order as others
+        // end: the first stream that is not done always gets all of its own)
+        if (waves + w > ex.pcg_lease && ex.pcg_lease < ex.pcg_resident) {
+            ++at;
+            waves = 0;
+        }
+        waves += w;
+        launch[i] = at;
+    }
+    return launch;
+}
+
+void count_solves(const Executor& ex, const std::vector<sw_stream>& ss, const std::vector<int>& its) {
+    const std::vector<int> launch = whole_launches(ex, ss, its);
+    for (size_t i = 0; i < ss.size(); ++i)
+        if (its[i] >= 0 && ss[i]->h.pcg_iters > 0) ++(launch[i] >= 0 ? ss[i]->counts.whole : ss[i]->counts.stepwise);
+}
+
 void count_folds(Executor& ex, sw_stream s, int64_t n) {
     if (!s->h.xpart) return;
     s->folds += n;
@@ -948,24 +978,18 @@ void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std
         SWGN_HIP(hipMemcpyAsync(s->dbg_g, h.g, sizeof(float) * 6 * h.nn, hipMemcpyDeviceToDevice, st));
     }
     // (the fold also starts PCG: block-Jacobi inverses, r_0, z_0, x = 0)
-    // whole solves, as many streams per launch as the lease has waves for
+    // whole solves
     std::vector<int> steps = its;             // streams left to solve step by step
-    for (int i = 0; i < n && ex.pcg_lease > 0;) {
+    const std::vector<int> launch = whole_launches(ex, ss, its);
+    const int launches = 1 + *std::max_element(launch.begin(), launch.end());
+    for (int l = 0; l < launches; ++l) {
         std::vector<int> now(n, -1);
-        int waves = 0;
-        bool any = false;
-        for (; i < n; ++i) {
-            const int w = its[i] >= 0 ? whole_solve_waves(ex, ss[i]) : 0;
-            if (w == 0) continue;
-            // (with the whole device leased, workgroups start in order as others
-            // end: the first stream that is not done always gets all of its own)
-            if (waves + w > ex.pcg_lease && ex.pcg_lease < ex.pcg_resident) break;
-            waves += w;
-            any = true;
-            now[i] = its[i];
-            steps[i] = -1;
-        }
-        if (any) run_stage(ex, kStPcgSolve, ss, now, 0, nullptr, timing, ev, true);
+        for (int i = 0; i < n; ++i)
+            if (launch[i] == l) {
+                now[i] = its[i];
+                steps[i] = -1;
+            }
+        run_stage(ex, kStPcgSolve, ss, now, 0, nullptr, timing, ev, true);
     }
     int pmax = 0;
     int64_t rows = 0;
@@ -1029,6 +1053,7 @@ sw_status finish_frames(Executor& ex, const std::vector<sw_stream>& ss, const fl
         const int G = s->cfg.gn_iters;
         const int Rg = s->cfg.rigid_iters;
         int64_t ncorr_total = 0;
+        s->counts.waits += flags[1];
         bool bad = (flags[0] | flags[1] | flags[2] | flags[3]) != 0;
         for (int it = 0; it < G; ++it) {
             ncorr_total += is[it].n_corr;
@@ -1087,14 +1112,21 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         any_capture |= ss[i]->cfg.debug_iter >= 0 && ss[i]->cfg.debug_iter < ss[i]->cfg.gn_iters;
     }
     PcgLease lease(ex, ss);
+    std::vector<int> its(n, 0);
+    auto iteration = [&](int it) {
+        for (int i = 0; i < n; ++i) its[i] = it < ss[i]->cfg.gn_iters ? it : -1;
+    };
     for (sw_stream s : ss) count_folds(ex, s, s->cfg.gn_iters);
+    for (int it = 0; it < gmax; ++it) {
+        iteration(it);
+        count_solves(ex, ss, its);
+    }
     enqueue_depth(ex, ss, depths, on_device, timing, ev);
     enqueue_rigid(ex, ss, timing, ev);
     std::vector<char> captured(n, 0);
-    std::vector<int> its(n, 0);
     auto body = [&]() {
         for (int it = 0; it < gmax; ++it) {
-            for (int i = 0; i < n; ++i) its[i] = it < ss[i]->cfg.gn_iters ? it : -1;
+            iteration(it);
             enqueue_iteration(ex, ss, its, timing, ev, captured);
         }
         enqueue_collect(ex, ss);
@@ -1123,6 +1155,7 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
             const hipError_t e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             SWGN_HIP(e);
+            for (sw_stream s : ss) ++s->counts.captures;
             ex.graph_exec = ge;
             ex.graph_key = key;
         }
@@ -1156,6 +1189,7 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         std::vector<int> at;
         for (int i = 0; i < n; ++i)
             if (stalled[i]) {
+                ++ss[i]->counts.redone;
                 again.push_back(ss[i]);
                 again_depth.push_back(depths[i]);
                 at.push_back(i);
@@ -1939,6 +1973,13 @@ sw_status sw_check_layout(sw_stream s, int64_t* differ) {
         differ[8] = cmp(pos4, L.pos4);
         return SW_OK;
     });
+}
+
+sw_status sw_get_solve_counts(sw_stream s, sw_solve_counts* out) {
+    if (!s || !out) return SW_EINVAL;
+    if (s->server) server_quiesce(s->server, s);
+    *out = s->counts;
+    return SW_OK;
 }
 
 sw_status sw_get_footprint(sw_stream s, int64_t* resident_bytes, int64_t* workspace_bytes) {

@@ -190,6 +190,7 @@ struct sw_stream_s {
     // sets of local nodes the whole-solve kernel needs with workgroups of 4
     // and 8 waves (0: the node set does not fit it)
     int pcg_sets4 = 0, pcg_sets8 = 0;
+    sw_solve_counts counts{};
     int64_t folds = 0;                    // since the exchange words were last cleared
     int pcg_sets(int waves) const { return waves == 4 ? pcg_sets4 : pcg_sets8; }
     sw_server server = nullptr;           // set while attached to a serving loop
@@ -238,6 +239,8 @@ void enqueue_depth(Executor& ex, const std::vector<sw_stream>& ss, const float* 
 void enqueue_rigid(Executor& ex, const std::vector<sw_stream>& ss, bool timing, std::vector<int>& ev);
 void enqueue_iteration(Executor& ex, const std::vector<sw_stream>& ss, const std::vector<int>& its, bool timing,
                        std::vector<int>& ev, std::vector<char>& captured);
+// counts the linear solves of one Gauss-Newton iteration as enqueue_iteration runs them
+void count_solves(const Executor& ex, const std::vector<sw_stream>& ss, const std::vector<int>& its);
 // before n folds of the stream are enqueued: clears the whole solve's exchange
 // words if their tags could come again
 void count_folds(Executor& ex, sw_stream s, int64_t n);

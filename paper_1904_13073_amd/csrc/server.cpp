@@ -220,6 +220,7 @@ void sw_server_s::run() {
             }
             captured.assign(ss.size(), 0);
             PcgLease lease(exec, ss);
+            count_solves(exec, ss, its);
             enqueue_iteration(exec, ss, its, false, ev, captured);
             for (size_t i = 0; i < active.size(); ++i) {
                 if (captured[i]) active[i].t->s->captured = true;
@@ -242,6 +243,7 @@ void sw_server_s::run() {
                     if (stalled[i]) {
                         // from the start again, step by step, as every later frame here
                         exec.pcg_resident = 0;
+                        ++fs[i]->counts.redone;
                         again.push_back(finished[i]);
                         for (Active& a : active)
                             if (a.t == finished[i]) a.it = 0;

@@ -160,7 +160,7 @@ struct FrameDesc {
     float* depth;                 // copy of a host depth image
     float4* nmap;                 // (normal, depth) per pixel
     unsigned long long* zbuf;     // index map: (z bits << 32 | surfel) per pixel
-    int* flags;                   // [4] failure bits of the frame
+    int* flags;                   // [4] failure bits of the frame; [1] counts the waits its whole solves gave up
     IterStats* stats;             // [kMaxIters]
     float4 *rq_bak, *tt_bak;      // node state at the start of the frame
     float* part;                  // [part_floats] segment Gram sub-blocks, J^T r, r^T r

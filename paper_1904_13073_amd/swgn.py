@@ -85,6 +85,11 @@ class SwLayout(C.Structure):
                 ("ell_width", C.c_int32), ("fold_entries", C.c_int64), ("gram_floats", C.c_int64)]
 
 
+class SwSolveCounts(C.Structure):
+    _fields_ = [("whole", C.c_int64), ("stepwise", C.c_int64), ("redone", C.c_int64), ("waits", C.c_int64),
+                ("captures", C.c_int64)]
+
+
 class SwError(RuntimeError):
     def __init__(self, status: int, msg: str):
         super().__init__(f"{msg} (status {status})")
@@ -128,7 +133,7 @@ EXPORTS = ["sw_config_default", "sw_status_string", "sw_last_error", "sw_create_
            "sw_server_submit", "sw_server_poll", "sw_server_counters", "sw_get_footprint",
            "sw_batch_autotune", "sw_get_layout", "sw_check_layout", "sw_set_surfel_attributes", "sw_get_surfel_attributes",
            "sw_get_reference_surfels", "sw_set_frame_time", "sw_fuse_frame", "sw_get_last_fusion",
-           "sw_append_candidates", "sw_get_live_nodes", "sw_update_geometry"]
+           "sw_append_candidates", "sw_get_live_nodes", "sw_update_geometry", "sw_get_solve_counts"]
 
 SW_EPENDING = 1
 
@@ -195,6 +200,7 @@ def lib() -> C.CDLL:
         "sw_batch_autotune": (i32, [vp, C.POINTER(vp), i32, i32, C.POINTER(i32)]),
         "sw_get_layout": (i32, [vp, C.POINTER(SwLayout)]),
         "sw_check_layout": (i32, [vp, C.POINTER(C.c_int64)]),
+        "sw_get_solve_counts": (i32, [vp, C.POINTER(SwSolveCounts)]),
     }
     for name, (res, args) in sig.items():
         f = getattr(L, name)
@@ -651,6 +657,12 @@ class Stream:
     def layout(self) -> dict:
         out = SwLayout()
         _check(self.h, lib().sw_get_layout(self.h, C.byref(out)))
+        return {k: getattr(out, k) for k, _ in out._fields_}
+
+    def solve_counts(self) -> dict:
+        """How the stream's linear solves have run since it was created."""
+        out = SwSolveCounts()
+        _check(self.h, lib().sw_get_solve_counts(self.h, C.byref(out)))
         return {k: getattr(out, k) for k, _ in out._fields_}
 
     def check_layout(self) -> dict:

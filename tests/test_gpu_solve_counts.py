@@ -1,0 +1,103 @@
+"""Which way the linear solves run, by the stream's own counts: batches (with
+and without a HIP graph), two threads and the serving loop take whole solves,
+and where one gives up waiting its frame is done again step by step."""
+import threading
+
+import numpy as np
+import pytest
+
+from gpu_common import gpu_lib
+from test_gpu_pcg_solve import _same, _steps, _stream, _surface
+
+pytestmark = pytest.mark.gpu
+
+GN = 3                                                              # (of the scenes)
+
+
+@pytest.fixture(scope="module")
+def swgn():
+    return gpu_lib()
+
+
+def _solves(st):
+    c = st.solve_counts()
+    return c["whole"], c["stepwise"], c["redone"]
+
+
+@pytest.mark.parametrize("sizes,graph", [((4100, 33, 4100, 700), False), ((4100, 65, 4000, 9, 3900, 4100), False),
+                                         ((4100, 65, 4000, 9, 3900, 4100), True)])
+def test_a_batch_alone_on_the_device_solves_whole(swgn, sizes, graph):
+    scenes = [_surface(n, 100 + k) for k, n in enumerate(sizes)]
+    sts = [_stream(swgn, s) for s in scenes]
+    bx = swgn.Batch(graph=graph)
+    for _ in range(3):
+        bx.solve(sts, [s["depth"] for s in scenes])
+    for st in sts:
+        assert _solves(st) == (3 * GN, 0, 0)
+        assert st.solve_counts()["captures"] == (1 if graph else 0)
+        st.close()
+    bx.close()
+
+
+def test_a_fixed_schedule_and_a_node_set_that_does_not_fit_solve_in_steps(swgn):
+    st, bx = _stream(swgn, _surface(300, 300)), swgn.Batch(pcg="split")
+    bx.solve([st], [_surface(300, 300)["depth"]])
+    assert _solves(st) == (0, GN, 0)
+    s = _surface(1500, 5, volume=True)
+    big = _stream(swgn, s, damping=1.0)
+    big.solve_frame(s["depth"])
+    assert _solves(big) == (0, GN, 0)
+    for x in (bx, st, big):
+        x.close()
+
+
+def test_threads_beside_each_other_take_whole_solves(swgn):
+    scenes = [[_surface(n, 7 * k + 1) for n in (4100, 3000)] for k in range(2)]
+    counts, errors = [None, None], []
+
+    def work(k):
+        try:
+            sts = [_stream(swgn, s) for s in scenes[k]]
+            bx = swgn.Batch()
+            for _ in range(8):
+                bx.solve(sts, [s["depth"] for s in scenes[k]])
+            counts[k] = [st.solve_counts() for st in sts]
+        except Exception as e:                                      # (reported by the main thread)
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for c in (c for group in counts for c in group):
+        assert c["whole"] > 0 and c["whole"] + c["stepwise"] == 8 * GN and c["redone"] == 0
+
+
+@pytest.mark.parametrize("how", ["alone", "batch", "graph", "served"])
+def test_a_wait_given_up_redoes_the_frame(swgn, monkeypatch, how):
+    monkeypatch.setenv("SWGN_PCG_WAIT_US", "-1")
+    scenes = [_surface(n, n) for n in (300, 900)]
+    sts = [_stream(swgn, s) for s in scenes]
+    depths = [s["depth"] for s in scenes]
+    if how == "alone":
+        stats = [st.solve_frame(d) for st, d in zip(sts, depths)]
+    elif how == "served":
+        sv = swgn.Server()
+        for st in sts:
+            sv.attach(st)
+        stats = [sv.poll(t)[0] for t in [sv.submit(st, d) for st, d in zip(sts, depths)]]
+        sv.close()
+    else:
+        bx = swgn.Batch(graph=how == "graph")
+        stats, _ = bx.solve(sts, depths)
+        bx.close()
+    counts = [st.solve_counts() for st in sts]
+    for st, s, r, c in zip(sts, scenes, stats, counts):
+        _same((r, st.node_se3()), _steps(swgn, s), how)
+        assert (c["waits"] > 0) == (c["redone"] > 0)
+        assert c["stepwise"] == GN or (how == "served" and c["stepwise"] > GN)
+        st.close()
+    # (served: a frame that another's given-up wait overtakes goes on in steps, and its own is redone or not)
+    assert [c["redone"] for c in counts] == [1, 1] or (how == "served" and sum(c["redone"] for c in counts) == 1)
