@@ -187,10 +187,11 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos_xyz,
  * A repeated call reuses the device memory of the stream's previous node set
  * and so first waits for all work on the device (as freeing it would).
  * Linear solves run as one launch per Gauss-Newton iteration whose workgroups
- * wait for each other; where another process holds the device so that they
- * cannot all run, they give up after SWGN_PCG_WAIT_US microseconds
- * (environment, read here; default 100000) and the frame is solved again one
- * launch per PCG iteration, with the same results. */
+ * wait for each other; where other work holds the device so that they cannot
+ * all run, they give up after SWGN_PCG_WAIT_US microseconds (environment,
+ * read here; default 100000). From then on nothing of that frame waits, and
+ * the frame is solved again one launch per PCG iteration, with the same
+ * results. */
 sw_status sw_set_node_graph(sw_stream s, int32_t n_nodes, const float* node_pos_xyz,
                             const float* node_se3, int32_t on_device);
 

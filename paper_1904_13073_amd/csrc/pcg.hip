@@ -46,8 +46,9 @@
 // the host launches no more of them than the chip holds at once (a lease on
 // their number, taken per device for as long as they run), and every wait is
 // bounded: a workgroup that waits longer than the stream allows raises the
-// stream's stall flag and stops waiting, so the launch ends, and the host
-// solves the frame again step by step.
+// stream's stall flag and stops waiting, and so does every workgroup of the
+// frame that finds the flag raised, in this launch and in the frame's later
+// ones. The host then solves the frame again step by step.
 //
 // Arithmetic. Every value is formed by the step-wise kernels' operations in
 // their order (slot order, butterfly sums over a row's lane groups, sums of
@@ -78,6 +79,11 @@ __device__ __forceinline__ u32x4 xchg_load2(XchgBuf b, int word) {
 __device__ __forceinline__ void xchg_store(u64* p, unsigned tag, unsigned payload) {
     typedef __attribute__((address_space(1))) u64 G;
     __hip_atomic_store((G*)p, ((u64)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ int agent_load(const int* p) {
+    typedef __attribute__((address_space(1))) const int G;
+    return __hip_atomic_load((G*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ void wave_fence() {
@@ -195,7 +201,9 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves == 4 && kSets > kPcgPairSe
     const uint16_t* loc = kWaves == 4 ? a.loc4 : a.loc8;
     const int* halo = (kWaves == 4 ? a.halo4 : a.halo8) + at.tile * kHalo;
     const int part = at.tile * kWaves + wave;
-    if (tid == 0) stalled = 0;
+    // (a wait of the frame already given up: this launch waits for nothing)
+    int* const flags = a.flags;
+    const int given_up = tid == 0 ? agent_load(flags + 1) : 0;
 
     // Loads that need no other load's result first: the local columns and the
     // blocks of the wave's 8 rows (slots grp and grp + 8 in registers), the
@@ -302,7 +310,7 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves == 4 && kSets > kPcgPairSe
     const size_t part_words = pcg_part_words(a);      // of one copy
     const int copy = at.tile % kPcgCopies;
     const long long t_limit = a.pcg_wait;
-    int* const flags = a.flags;
+    if (tid == 0) stalled = given_up;
     __syncthreads();
 
     for (int i = 0; i < iters; ++i) {
@@ -449,10 +457,12 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves == 4 && kSets > kPcgPairSe
                         }
                     if (__ballot(need != 0u) == 0) break;
                     if ((spin & 15) == 15 || t_limit < 0) {
-                        // bounded: nobody waits past the limit, and nobody at all once one has
+                        // bounded: nobody waits past the limit, and nobody of the frame once one has
                         const long long now = wall_clock64();
                         if (t0 == 0) t0 = now;
-                        if (now - t0 > t_limit) {
+                        if (agent_load(flags + 1) != 0) {
+                            *(volatile int*)&stalled = 1;
+                        } else if (now - t0 > t_limit) {
                             *(volatile int*)&stalled = 1;
                             if (lane == 0) atomicAdd(flags + 1, 1);
                         }

@@ -101,3 +101,22 @@ def test_a_wait_given_up_redoes_the_frame(swgn, monkeypatch, how):
         st.close()
     # (served: a frame that another's given-up wait overtakes goes on in steps, and its own is redone or not)
     assert [c["redone"] for c in counts] == [1, 1] or (how == "served" and sum(c["redone"] for c in counts) == 1)
+
+
+@pytest.mark.parametrize("how", ["alone", "batch"])
+def test_a_frame_waits_once(swgn, monkeypatch, how):
+    """Once a wave has given up, nothing of the frame waits any more: the waits
+    given up are at most the waves of one solve, not those of every iteration."""
+    monkeypatch.setenv("SWGN_PCG_WAIT_US", "-1")
+    s = _surface(900, 900)
+    st = _stream(swgn, s, gn_iters=16)
+    if how == "alone":
+        st.solve_frame(s["depth"])
+    else:
+        bx = swgn.Batch()
+        bx.solve([st], [s["depth"]])
+        bx.close()
+    c = st.solve_counts()
+    st.close()
+    assert c["redone"] == 1 and c["whole"] == 16
+    assert 0 < c["waits"] <= -(-900 // 8)                           # (8 rows per wave)
