@@ -191,7 +191,9 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos_xyz,
  * all run, they give up after SWGN_PCG_WAIT_US microseconds (environment,
  * read here; default 100000). From then on nothing of that frame waits, and
  * the frame is solved again one launch per PCG iteration, with the same
- * results. */
+ * results; so are the executor's (stream's, batch's or server's) next 64
+ * frames, twice as many each time it happens again (at most 4096), before
+ * whole solves are tried once more. */
 sw_status sw_set_node_graph(sw_stream s, int32_t n_nodes, const float* node_pos_xyz,
                             const float* node_se3, int32_t on_device);
 

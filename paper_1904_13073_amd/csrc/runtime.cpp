@@ -119,6 +119,10 @@ static int whole_solve_waves(const Executor& ex, sw_stream s) {
 PcgLease::PcgLease(Executor& ex, const std::vector<sw_stream>& ss) : ex_(ex) {
     ex.pcg_lease = 0;
     if (ex.pcg_mode != kPcgAuto || ex.pcg_resident == 0) return;
+    if (ex.pcg_hold > 0) {
+        --ex.pcg_hold;
+        return;
+    }
     auto total = [&](int waves, int& most) {
         int all = 0, sets = 0;
         most = 0;
@@ -162,6 +166,14 @@ void PcgLease::release() {
     (void)hipStreamSynchronize(ex_.st);
     g_pcg_leased[ex_.device].fetch_sub(ex_.pcg_lease);
     ex_.pcg_lease = 0;
+    if (ex_.pcg_backoff > 0 && ex_.pcg_hold == 0 && ++ex_.pcg_good >= ex_.pcg_backoff) ex_.pcg_backoff = 0;
+}
+
+void Executor::pcg_stalled(int leases_per_frame) {
+    if (pcg_hold > 0) return;                    // (streams of the same frames)
+    pcg_backoff = std::min(kPcgHoldMost * leases_per_frame, std::max(kPcgHoldFrames * leases_per_frame, 2 * pcg_backoff));
+    pcg_hold = pcg_backoff;
+    pcg_good = 0;
 }
 
 void Executor::init(void* hip_stream) {
@@ -1180,10 +1192,10 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
     for (int i = 0; i < n; ++i)
         if (captured[i]) ss[i]->captured = true;
     if (std::find(stalled.begin(), stalled.end(), 1) != stalled.end()) {
-        // a whole solve gave up waiting for its workgroups (another process
-        // holds the chip): those frames again, step by step, as every later
-        // frame of this executor
-        ex.pcg_resident = 0;
+        // a whole solve gave up waiting for its workgroups (other work holds
+        // the chip): those frames again, step by step, as this executor's next
+        // frames
+        ex.pcg_stalled(1);
         std::vector<sw_stream> again;
         std::vector<const float*> again_depth;
         std::vector<int> at;

@@ -96,6 +96,9 @@ struct Executor {
     int pcg_resident = 0;
     int pcg_lease = 0;
     int pcg_waves = 4;
+    int pcg_hold = 0;                     // leases refused before the next one is tried (after a wait given up)
+    int pcg_backoff = 0, pcg_good = 0;    // the last such number; leases that ended well since
+    void pcg_stalled(int leases_per_frame);
     int pcg_charge = 4;                   // waves that such a workgroup counts as (8: it has a CU to itself)
     hipGraphExec_t graph_exec = nullptr;
     std::vector<std::pair<sw_stream, uint64_t>> graph_key;   // (stream, generation) it was captured for
@@ -142,6 +145,10 @@ sw_status guarded(std::string& err, F&& f) {
 
 size_t carve_workspace(FrameDesc& h, char* base);
 
+// Frames an executor solves step by step after a wait given up, doubled each
+// time it happens again up to the second number (a wait is 100 ms, a frame about
+// 1 ms: at worst 2.5% of the time), until as many have gone well.
+constexpr int kPcgHoldFrames = 64, kPcgHoldMost = 4096;
 // longest wait of a whole solve's workgroup for the others before the frame
 // is solved again step by step (100 ms, in 10 ns)
 constexpr long long kPcgWait = 10000000;

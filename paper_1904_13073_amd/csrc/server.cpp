@@ -241,8 +241,8 @@ void sw_server_s::run() {
                 std::vector<Ticket*> ended;
                 for (size_t i = 0; i < fs.size(); ++i) {
                     if (stalled[i]) {
-                        // from the start again, step by step, as every later frame here
-                        exec.pcg_resident = 0;
+                        // from the start again, step by step, as the next frames here
+                        exec.pcg_stalled(kMaxIters);
                         ++fs[i]->counts.redone;
                         again.push_back(finished[i]);
                         for (Active& a : active)

@@ -120,3 +120,55 @@ def test_a_frame_waits_once(swgn, monkeypatch, how):
     st.close()
     assert c["redone"] == 1 and c["whole"] == 16
     assert 0 < c["waits"] <= -(-900 // 8)                           # (8 rows per wave)
+
+
+@pytest.mark.parametrize("how", ["alone", "batch", "served"])
+def test_whole_solves_are_tried_again_after_a_wait_given_up(swgn, monkeypatch, how):
+    """A wait given up (forced on one node graph only) costs the next 64
+    frames the whole solve, not all that follow."""
+    s = _surface(300, 300)
+    monkeypatch.setenv("SWGN_PCG_WAIT_US", "-1")
+    bad, st = _stream(swgn, s), None
+    monkeypatch.delenv("SWGN_PCG_WAIT_US")
+    st = _stream(swgn, s)
+    if how == "alone":
+        st.close()
+        st = bad
+        solve = lambda x: x.solve_frame(s["depth"])
+        solve(bad)
+        bad.set_node_graph(s["nodes"])                              # (with patience)
+    elif how == "batch":
+        ex = swgn.Batch()
+        solve = lambda x: ex.solve([x], [s["depth"]])
+        solve(bad)
+    else:
+        ex = swgn.Server()
+        ex.attach(bad)
+        ex.attach(st)
+        solve = lambda x: ex.poll(ex.submit(x, s["depth"]))
+        solve(bad)
+    assert bad.solve_counts()["redone"] == 1
+    before = st.solve_counts()
+    for _ in range(60):
+        solve(st)
+    c = st.solve_counts()
+    assert c["whole"] == before["whole"] and c["stepwise"] == before["stepwise"] + 60 * GN
+    for _ in range(400):                                            # (served: a frame's most iterations count, not its own)
+        solve(st)
+    c = st.solve_counts()
+    assert c["whole"] > before["whole"] and c["redone"] == before["redone"]
+    if how != "alone":
+        ex.close()
+        bad.close()
+    st.close()
+
+
+def test_waits_given_up_again_and_again_become_rare(swgn, monkeypatch):
+    monkeypatch.setenv("SWGN_PCG_WAIT_US", "-1")
+    s = _surface(300, 300)
+    st = _stream(swgn, s, gn_iters=1)
+    for _ in range(500):                                            # frames 1, 65, 193, 449 (and their second solves)
+        st.solve_frame(s["depth"])
+    c = st.solve_counts()
+    st.close()
+    assert 3 <= c["redone"] <= 4
