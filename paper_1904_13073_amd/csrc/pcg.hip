@@ -43,8 +43,9 @@
 // iteration i.
 //
 // Every workgroup of a stream must be resident for the others to get on, so
-// the host launches no more of them than the chip holds at once (a lease on
-// their number, taken per device for as long as they run), and every wait is
+// the host launches no more of them than find a place on the chip however they
+// are placed (a lease on their number, taken per device for as long as they
+// run; swgn_lease.h), and every wait is
 // bounded: a workgroup that waits longer than the stream allows raises the
 // stream's stall flag and stops waiting, and so does every workgroup of the
 // frame that finds the flag raised, in this launch and in the frame's later
@@ -57,6 +58,8 @@
 #include "swgn_impl.h"
 #include "swgn_launch.h"
 #include "swgn_pcg.h"
+
+#include <initializer_list>
 
 namespace swgn {
 
@@ -564,21 +567,20 @@ void launch_pcg_solve(const Batch& b, hipStream_t st) {
     }
 }
 
-int pcg_resident_workgroups(int waves, int cus) {
-    int n = 0, m = 0;
-    const void* few = waves == 4 ? (const void*)k_pcg_solve<4, 4> : (const void*)k_pcg_solve<8, 4>;
-    const void* many = waves == 4 ? (const void*)k_pcg_solve<4, 5> : (const void*)k_pcg_solve<8, 5>;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, few, 64 * waves, 0) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, many, 64 * waves, 0) != hipSuccess)
-        return 0;
-    n = n < m ? n : m;
-    if (waves == 8) {
-        // (a workgroup of 4 waves and more than kPcgPairSets sets counts as one of 8)
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, (const void*)k_pcg_solve<4, 8>, 256, 0) != hipSuccess)
-            return 0;
-        n = n < m ? n : m;
-    }
-    return n * cus;
+void pcg_workgroups_per_cu(int& pair, int& alone) {
+    auto least = [](std::initializer_list<const void*> kernels, int threads) {
+        int n = 1 << 20;
+        for (const void* k : kernels) {
+            int m = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, k, threads, 0) != hipSuccess) m = 0;
+            n = m < n ? m : n;
+        }
+        return n;
+    };
+    pair = least({(const void*)k_pcg_solve<4, 4>, (const void*)k_pcg_solve<4, 5>}, 256);
+    const int many = least({(const void*)k_pcg_solve<4, 8>}, 256);
+    alone = least({(const void*)k_pcg_solve<8, 4>, (const void*)k_pcg_solve<8, 5>}, 512);
+    alone = many < alone ? many : alone;
 }
 
 }  // namespace swgn

@@ -14,7 +14,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstdio>
@@ -28,6 +27,7 @@
 
 #include "runtime_internal.h"
 #include "segments.h"
+#include "swgn_lease.h"
 #include "swgn_setup.h"
 #include "swgn_fusion.h"
 #include "swgn.h"
@@ -104,21 +104,23 @@ Executor::~Executor() {
     if (own_stream && st) (void)hipStreamDestroy(st);
 }
 
-// Waves of the whole-solve kernel leased on each device.
+// Workgroups of whole solves leased on each device.
 constexpr int kMaxDevices = 64;
-static std::atomic<int> g_pcg_leased[kMaxDevices];
+static std::mutex g_pcg_mu;
+static PcgHeld g_pcg_held[kMaxDevices];
 
-// waves that a whole linear solve of stream s counts as with the executor's
-// workgroups; 0: it cannot take one
-static int whole_solve_waves(const Executor& ex, sw_stream s) {
+// workgroups of a whole linear solve of stream s with the executor's kind of
+// them; 0: it cannot take one
+static int whole_solve_tiles(const Executor& ex, sw_stream s) {
     if (s->pcg_sets(ex.pcg_waves) == 0 || s->h.pcg_iters == 0) return 0;
-    const int n = pcg_tiles(s->h, ex.pcg_waves) * ex.pcg_charge;
-    return n <= ex.pcg_resident ? n : 0;
+    const int n = pcg_tiles(s->h, ex.pcg_waves);
+    return n <= (ex.pcg_alone ? ex.pcg_cus : 2 * ex.pcg_cus) ? n : 0;
 }
 
 PcgLease::PcgLease(Executor& ex, const std::vector<sw_stream>& ss) : ex_(ex) {
+    ex.pcg_whole = false;
     ex.pcg_lease = 0;
-    if (ex.pcg_mode != kPcgAuto || ex.pcg_resident == 0) return;
+    if (ex.pcg_mode != kPcgAuto || ex.pcg_cus == 0) return;
     if (ex.pcg_hold > 0) {
         --ex.pcg_hold;
         return;
@@ -128,9 +130,9 @@ PcgLease::PcgLease(Executor& ex, const std::vector<sw_stream>& ss) : ex_(ex) {
         most = 0;
         for (sw_stream s : ss) sets = std::max(sets, s->pcg_sets(waves));
         ex.pcg_waves = waves;
-        ex.pcg_charge = waves == 4 && sets > kPcgPairSets ? 8 : waves;
+        ex.pcg_alone = waves == 8 || sets > kPcgPairSets;
         for (sw_stream s : ss) {
-            const int n = whole_solve_waves(ex, s);
+            const int n = whole_solve_tiles(ex, s);
             most = std::max(most, n);
             all += n;
         }
@@ -147,25 +149,25 @@ PcgLease::PcgLease(Executor& ex, const std::vector<sw_stream>& ss) : ex_(ex) {
         return s->h.nn <= pcg_rows(8) && s->pcg_sets(8) > 0;
     });
     if (!one) all = total(4, most);
-    if (one || all / ex.pcg_charge * 4 > ex.pcg_resident / 2 || most == 0) all = total(8, most);
+    if (one || all > ex.pcg_cus || most == 0) all = total(8, most);
     if (most == 0) return;
-    std::atomic<int>& leased = g_pcg_leased[ex.device];
-    int now = leased.load();
-    for (;;) {
-        const int n = std::min(all, ex.pcg_resident - now);
-        if (n < most) return;
-        if (leased.compare_exchange_weak(now, now + n)) {
-            ex.pcg_lease = n;
-            return;
-        }
+    if (most > 1) {                            // (a workgroup that is alone in its solve waits for nobody)
+        std::lock_guard<std::mutex> lock(g_pcg_mu);
+        ex.pcg_lease = pcg_take(g_pcg_held[ex.device], ex.pcg_alone, ex.pcg_cus, most, all);
+        if (ex.pcg_lease == 0) return;
     }
+    ex.pcg_whole = true;
 }
 
 void PcgLease::release() {
-    if (ex_.pcg_lease == 0) return;
-    (void)hipStreamSynchronize(ex_.st);
-    g_pcg_leased[ex_.device].fetch_sub(ex_.pcg_lease);
-    ex_.pcg_lease = 0;
+    if (!ex_.pcg_whole) return;
+    ex_.pcg_whole = false;
+    if (ex_.pcg_lease > 0) {
+        (void)hipStreamSynchronize(ex_.st);
+        std::lock_guard<std::mutex> lock(g_pcg_mu);
+        pcg_give(g_pcg_held[ex_.device], ex_.pcg_alone, ex_.pcg_lease);
+        ex_.pcg_lease = 0;
+    }
     if (ex_.pcg_backoff > 0 && ex_.pcg_hold == 0 && ++ex_.pcg_good >= ex_.pcg_backoff) ex_.pcg_backoff = 0;
 }
 
@@ -186,8 +188,10 @@ void Executor::init(void* hip_stream) {
     SWGN_HIP(hipGetDevice(&device));
     int cus = 0;
     SWGN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
-    if (device < kMaxDevices)
-        pcg_resident = std::min(4 * pcg_resident_workgroups(4, cus), 8 * pcg_resident_workgroups(8, cus));
+    // (the leases count on two workgroups per CU of the one kind and one of the other)
+    int pair = 0, alone = 0;
+    pcg_workgroups_per_cu(pair, alone);
+    pcg_cus = device < kMaxDevices && pair >= 2 && alone >= 1 ? cus : 0;
     SWGN_HIP(hipHostMalloc(&stats_host, (size_t)kStatsOutBytes * kMaxBatch, hipHostMallocDefault));
     SWGN_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&stats_dev), stats_host, 0));
 }
@@ -926,24 +930,25 @@ void enqueue_rigid(Executor& ex, const std::vector<sw_stream>& ss, bool timing, 
 }
 
 // The launch of whole solves that each stream of a Gauss-Newton iteration goes
-// into (0, 1, ...; as many streams per launch as the lease has waves for); -1:
-// its linear solve runs step by step, or it has none.
+// into (0, 1, ...; as many streams per launch as the lease has workgroups for);
+// -1: its linear solve runs step by step, or it has none.
 static std::vector<int> whole_launches(const Executor& ex, const std::vector<sw_stream>& ss,
                                        const std::vector<int>& its) {
     const int n = (int)ss.size();
     std::vector<int> launch(n, -1);
-    if (ex.pcg_lease == 0) return launch;
-    int at = 0, waves = 0;
+    if (!ex.pcg_whole) return launch;
+    // (with the whole device leased, workgroups start in order as others end:
+    // the first stream that is not done always gets all of its own)
+    const bool bound = ex.pcg_lease > 0 && ex.pcg_lease < ex.pcg_cus;
+    int at = 0, tiles = 0;
     for (int i = 0; i < n; ++i) {
-        const int w = its[i] >= 0 ? whole_solve_waves(ex, ss[i]) : 0;
-        if (w == 0) continue;
-        // (with the whole device leased, workgroups start in order as others
-        // end: the first stream that is not done always gets all of its own)
-        if (waves + w > ex.pcg_lease && ex.pcg_lease < ex.pcg_resident) {
+        const int t = its[i] >= 0 ? whole_solve_tiles(ex, ss[i]) : 0;
+        if (t == 0) continue;
+        if (bound && tiles + t > ex.pcg_lease) {
             ++at;
-            waves = 0;
+            tiles = 0;
         }
-        waves += w;
+        tiles += t;
         launch[i] = at;
     }
     return launch;
@@ -1150,7 +1155,7 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         std::vector<std::pair<sw_stream, uint64_t>> key;
         for (sw_stream s : ss) key.emplace_back(s, s->generation);
         key.emplace_back(nullptr, ex.tune_epoch);
-        key.emplace_back(nullptr, (uint64_t)ex.pcg_lease * 256 + (uint64_t)ex.pcg_waves * 16 + (uint64_t)ex.pcg_charge);
+        key.emplace_back(nullptr, (uint64_t)ex.pcg_lease * 256 + (uint64_t)ex.pcg_waves * 16 + (uint64_t)ex.pcg_whole);
         if (!ex.graph_exec || key != ex.graph_key) {
             ex.drop_graph();
             hipGraph_t g = nullptr;

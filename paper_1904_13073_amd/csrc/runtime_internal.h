@@ -89,17 +89,20 @@ struct Executor {
     // replay of a batch's iterations as one HIP graph
     bool graphs = false;
     int pcg_mode = 0;                     // kPcgAuto, kPcgSplit, kPcgFused
-    // whole linear solves in one launch (pcg.hip): how many waves of it the
-    // device holds at once (0: never used), and how many of them a launch of
-    // the call being enqueued may take (its lease), in workgroups of how many
+    // whole linear solves in one launch (pcg.hip): the device's CUs (0: never
+    // used); whether the call being enqueued takes them, in how many
+    // workgroups per launch at most (its lease; 0: as many as it likes, for
+    // none waits for another), of how many waves, and whether one has a CU to
+    // itself
     int device = 0;
-    int pcg_resident = 0;
+    int pcg_cus = 0;
+    bool pcg_whole = false;
     int pcg_lease = 0;
     int pcg_waves = 4;
+    bool pcg_alone = false;
     int pcg_hold = 0;                     // leases refused before the next one is tried (after a wait given up)
     int pcg_backoff = 0, pcg_good = 0;    // the last such number; leases that ended well since
     void pcg_stalled(int leases_per_frame);
-    int pcg_charge = 4;                   // waves that such a workgroup counts as (8: it has a CU to itself)
     hipGraphExec_t graph_exec = nullptr;
     std::vector<std::pair<sw_stream, uint64_t>> graph_key;   // (stream, generation) it was captured for
     ~Executor();
@@ -108,10 +111,13 @@ struct Executor {
     void drop_graph();
 };
 
-// The right to have n waves of the whole-solve kernel resident on a device, held while launches that need them may run: its workgroups wait for
-// each other, so all that are in flight in this process together must fit
-// the chip. Takes what the streams can use, at least their largest solve, or
-// nothing (their linear solves then run step by step, with equal results).
+// The right to have a number of workgroups of whole solves on a device, held
+// while launches that need them may run: they wait for each other, so all that
+// are in flight in this process must find a place together (swgn_lease.h).
+// Takes what the streams can use, at least their largest solve, or nothing
+// (their linear solves then run step by step, with equal results). Other
+// kernels of the process can hold the CUs too, but end by themselves; other
+// processes are not known here: the kernel's waits are bounded.
 class PcgLease {
 public:
     PcgLease(Executor& ex, const std::vector<sw_stream>& ss);

@@ -414,8 +414,9 @@ void launch_frame_stage(int stage, const Batch& b, const DepthIn* depth, hipStre
 void launch_asm_stage(int stage, const Batch& b, hipStream_t st);
 void launch_solve_stage(int stage, const Batch& b, void* stats_out, hipStream_t st);
 void launch_pcg_solve(const Batch& b, hipStream_t st);
-// workgroups of so many waves of the whole-solve kernel that a device of so many CUs holds at once
-int pcg_resident_workgroups(int waves, int cus);
+// workgroups of the whole-solve kernel that a CU holds: of those that share one (4 waves, up to
+// kPcgPairSets sets), and of the others
+void pcg_workgroups_per_cu(int& pair, int& alone);
 
 // Bytes per stream written by the statistics copy: kMaxIters IterStats, the
 // failure flags, kMaxIters RigidStats.

@@ -172,3 +172,42 @@ def test_waits_given_up_again_and_again_become_rare(swgn, monkeypatch):
     c = st.solve_counts()
     st.close()
     assert 3 <= c["redone"] <= 4
+
+
+def test_mixed_workgroups_from_many_threads_never_wait_in_vain(swgn):
+    """Executors whose solves take a CU per workgroup (a full batch; a sheet
+    whose tiles have many foreign columns), share CUs, or are one workgroup:
+    beside each other no solve gives up waiting, and the smallest need no room."""
+    sheet = _surface(1000, 1000)
+    sheet["nodes"][:, 2] = 1.2 - np.random.default_rng(1).uniform(0, 0.1 * sheet["cfg"]["node_sigma"], 1000)
+    groups = [[_surface(4100, k) for k in range(5)], [sheet], [_surface(2000, 1)], [_surface(1700, 2), _surface(900, 3)],
+              [_surface(40, 4)], [_surface(3500, 5)]]
+    want = [[_steps(swgn, s, frames=30) for s in g] for g in groups]
+    got, counts, errors = {}, {}, []
+    start = threading.Barrier(len(groups))
+
+    def work(k):
+        try:
+            sts = [_stream(swgn, s) for s in groups[k]]
+            bx = swgn.Batch()
+            start.wait()
+            for _ in range(30):
+                stats, _ = bx.solve(sts, [s["depth"] for s in groups[k]])
+            got[k] = [(r, st.node_se3()) for r, st in zip(stats, sts)]
+            counts[k] = [st.solve_counts() for st in sts]
+        except Exception as e:                                      # (reported by the main thread)
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(groups))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k, g in enumerate(groups):
+        for i in range(len(g)):
+            _same(got[k][i], want[k][i], (k, i))
+            c = counts[k][i]
+            assert c["redone"] == c["waits"] == 0 and c["whole"] + c["stepwise"] == 30 * GN
+    assert counts[4][0]["stepwise"] == 0
+    assert sum(c["whole"] for g in counts.values() for c in g) > 0
