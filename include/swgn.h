@@ -336,7 +336,9 @@ typedef struct sw_batch_s* sw_batch;
  * HIP graph the first time a batch (the same streams in the same order) is
  * solved, and the graph is replayed while the batch and its streams'
  * buffers are unchanged (a new batch, or sw_set_reference_surfels /
- * sw_set_node_graph on a member, captures anew). Results are identical to
+ * sw_set_node_graph on a member, captures anew; so does the first time that
+ * the linear solves are launched in another way, and the last 4 such graphs
+ * are kept). Results are identical to
  * the launch-by-launch path. Not combinable with SW_BATCH_TIMING (EINVAL);
  * streams that capture an iteration (debug_iter) run launch by launch.
  * SW_BATCH_PCG_SPLIT or SW_BATCH_PCG_FUSED (not both) fix the PCG schedule.

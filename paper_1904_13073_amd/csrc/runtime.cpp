@@ -91,14 +91,14 @@ void Arena::reset() {
     bytes_ = 0;
 }
 
-void Executor::drop_graph() {
-    if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-    graph_exec = nullptr;
+void Executor::drop_graphs() {
+    for (const Graph& g : graph_execs) (void)hipGraphExecDestroy(g.exec);
+    graph_execs.clear();
     graph_key.clear();
 }
 
 Executor::~Executor() {
-    drop_graph();
+    drop_graphs();
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
     if (stats_host) (void)hipHostFree(stats_host);
     if (own_stream && st) (void)hipStreamDestroy(st);
@@ -1134,9 +1134,12 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
         for (int i = 0; i < n; ++i) its[i] = it < ss[i]->cfg.gn_iters ? it : -1;
     };
     for (sw_stream s : ss) count_folds(ex, s, s->cfg.gn_iters);
+    std::vector<int> launches{ex.pcg_waves};  // how the frame's linear solves are launched
     for (int it = 0; it < gmax; ++it) {
         iteration(it);
         count_solves(ex, ss, its);
+        const std::vector<int> l = whole_launches(ex, ss, its);
+        launches.insert(launches.end(), l.begin(), l.end());
     }
     enqueue_depth(ex, ss, depths, on_device, timing, ev);
     enqueue_rigid(ex, ss, timing, ev);
@@ -1150,14 +1153,23 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
     };
     if (ex.graphs && !timing && !any_capture) {
         // the iterations and the statistics copy of this exact batch as one
-        // graph, captured on first use and replayed while the batch and its
-        // streams' buffers are unchanged
+        // graph, captured on first use (and where the lease calls for other
+        // launches) and replayed while the batch and its streams' buffers are
+        // unchanged
         std::vector<std::pair<sw_stream, uint64_t>> key;
         for (sw_stream s : ss) key.emplace_back(s, s->generation);
         key.emplace_back(nullptr, ex.tune_epoch);
-        key.emplace_back(nullptr, (uint64_t)ex.pcg_lease * 256 + (uint64_t)ex.pcg_waves * 16 + (uint64_t)ex.pcg_whole);
-        if (!ex.graph_exec || key != ex.graph_key) {
-            ex.drop_graph();
+        if (key != ex.graph_key) {
+            ex.drop_graphs();
+            ex.graph_key = key;
+        }
+        auto at = std::find_if(ex.graph_execs.begin(), ex.graph_execs.end(),
+                               [&](const Executor::Graph& g) { return g.launches == launches; });
+        if (at == ex.graph_execs.end()) {
+            if (ex.graph_execs.size() == kGraphsKept) {
+                (void)hipGraphExecDestroy(ex.graph_execs.back().exec);
+                ex.graph_execs.pop_back();
+            }
             hipGraph_t g = nullptr;
             SWGN_HIP(hipStreamBeginCapture(ex.st, hipStreamCaptureModeThreadLocal));
             try {
@@ -1173,10 +1185,10 @@ sw_status solve_frames(Executor& ex, const std::vector<sw_stream>& ss, const flo
             (void)hipGraphDestroy(g);
             SWGN_HIP(e);
             for (sw_stream s : ss) ++s->counts.captures;
-            ex.graph_exec = ge;
-            ex.graph_key = key;
+            at = ex.graph_execs.insert(ex.graph_execs.end(), Executor::Graph{launches, ge});
         }
-        SWGN_HIP(hipGraphLaunch(ex.graph_exec, ex.st));
+        std::rotate(ex.graph_execs.begin(), at, at + 1);
+        SWGN_HIP(hipGraphLaunch(ex.graph_execs.front().exec, ex.st));
     } else {
         body();
     }

@@ -103,12 +103,18 @@ struct Executor {
     int pcg_hold = 0;                     // leases refused before the next one is tried (after a wait given up)
     int pcg_backoff = 0, pcg_good = 0;    // the last such number; leases that ended well since
     void pcg_stalled(int leases_per_frame);
-    hipGraphExec_t graph_exec = nullptr;
-    std::vector<std::pair<sw_stream, uint64_t>> graph_key;   // (stream, generation) it was captured for
+    std::vector<std::pair<sw_stream, uint64_t>> graph_key;   // (stream, generation) the graphs were captured for
+    // one graph per way the linear solves are launched in (it follows from the
+    // lease, which depends on what other executors hold), the latest first
+    struct Graph {
+        std::vector<int> launches;
+        hipGraphExec_t exec;
+    };
+    std::vector<Graph> graph_execs;
     ~Executor();
     void init(void* hip_stream);
     hipEvent_t event(size_t i);
-    void drop_graph();
+    void drop_graphs();
 };
 
 // The right to have a number of workgroups of whole solves on a device, held
@@ -155,6 +161,8 @@ size_t carve_workspace(FrameDesc& h, char* base);
 // time it happens again up to the second number (a wait is 100 ms, a frame about
 // 1 ms: at worst 2.5% of the time), until as many have gone well.
 constexpr int kPcgHoldFrames = 64, kPcgHoldMost = 4096;
+// graphs an executor keeps of one batch (all whole, all in steps, and a few between)
+constexpr size_t kGraphsKept = 4;
 // longest wait of a whole solve's workgroup for the others before the frame
 // is solved again step by step (100 ms, in 10 ns)
 constexpr long long kPcgWait = 10000000;

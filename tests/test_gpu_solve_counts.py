@@ -211,3 +211,42 @@ def test_mixed_workgroups_from_many_threads_never_wait_in_vain(swgn):
             assert c["redone"] == c["waits"] == 0 and c["whole"] + c["stepwise"] == 30 * GN
     assert counts[4][0]["stepwise"] == 0
     assert sum(c["whole"] for g in counts.values() for c in g) > 0
+
+
+def test_graphs_beside_other_executors_are_captured_once_per_way_of_launching(swgn):
+    """What a graph executor may launch at once varies with what others hold;
+    the graph follows the launches, not the number: a pair of streams has both
+    in one launch, one after the other, or in steps."""
+    scenes = [_surface(n, n) for n in (4100, 4090)]
+    want = [_steps(swgn, s, frames=60) for s in scenes]
+    sts = [_stream(swgn, s) for s in scenes]
+    done, errors = threading.Event(), []
+
+    def beside(k):
+        try:
+            s = _surface((3000, 3300, 900)[k], k)
+            st, bx = _stream(swgn, s), swgn.Batch()
+            while not done.is_set():
+                bx.solve([st], [s["depth"]])
+            bx.close()
+            st.close()
+        except Exception as e:                                      # (reported by the main thread)
+            errors.append(e)
+
+    threads = [threading.Thread(target=beside, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    bx = swgn.Batch(graph=True)
+    try:
+        for _ in range(60):
+            stats, _ = bx.solve(sts, [s["depth"] for s in scenes])
+    finally:
+        done.set()
+        for t in threads:
+            t.join()
+    assert not errors, errors
+    for st, r, w in zip(sts, stats, want):
+        _same((r, st.node_se3()), w, "graph")
+        assert 1 <= st.solve_counts()["captures"] <= 3 and st.solve_counts()["redone"] == 0
+        st.close()
+    bx.close()
