@@ -547,6 +547,12 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     // the node-set arrays and temporaries reuse their device memory: no work
     // of the device may still use it
     SWGN_HIP(hipDeviceSynchronize());
+    if (nn < s->held_nn / 4) {
+        s->held_nn = 0;
+        s->graph_mem.release();
+        s->setup_mem.release();
+    }
+    s->held_nn = std::max(s->held_nn, nn);
     s->graph_mem.reset();
     s->graph_set = false;
     s->captured = false;
@@ -1407,11 +1413,14 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos, con
         s->graph_set = false;
         s->captured = false;
         ++s->generation;
-        // a model of about the size of the last one takes over its memory (to
-        // free and allocate it anew takes longer than the rest of a model's
-        // installation); no work of the device may still use it
+        // a model takes over the memory of the last ones (to free and allocate
+        // it anew takes longer than the rest of a model's installation) unless
+        // it is much smaller than the largest of them, or larger; no work of
+        // the device may still use it
         SWGN_HIP(hipDeviceSynchronize());
-        if (!s->surfels_set || n < s->ns / 4 || n > 2 * s->ns) {
+        if (!s->surfels_set || n < s->held_ns / 4 || n > 2 * s->held_ns) {
+            s->held_ns = 0;
+            s->held_nn = 0;
             s->graph_mem.release();
             s->ws_mem.release();
             s->setup_mem.release();
@@ -1423,6 +1432,7 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos, con
         s->surf_mem.reset();
         s->surfels_set = false;
         s->ns = n;
+        s->held_ns = std::max(s->held_ns, n);
         s->fuse_mem.reset();
         s->fz4 = nullptr;
         s->fused = false;
@@ -1884,6 +1894,7 @@ sw_status sw_update_geometry(sw_stream s, sw_geometry_stats* stats) {
         // swap in the new surfels (the old arrays are the next update's spare memory) and rebuild
         s->surf_mem.swap(fresh);
         s->ns = nnew;
+        s->held_ns = std::max(s->held_ns, nnew);
         s->in_pos = c.dpos; s->in_nrm = c.dnrm; s->in_rad = c.drad; s->in_conf = c.dconf;
         s->in_tobs = c.dtobs; s->in_tinit = c.dtinit;
         build_graph(s, nn, np3, nullptr, 1, rq, tt, true);

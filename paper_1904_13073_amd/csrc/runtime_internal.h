@@ -178,6 +178,8 @@ struct sw_stream_s {
     swgn::rt::Arena frame_mem, surf_mem, graph_mem, ws_mem;
     swgn::rt::Arena setup_mem;            // temporaries of the node-set build, kept for the next one
     swgn::rt::Arena geo_mem, spare_mem;   // geometry update: temporaries, and the surfels before it (the next update's)
+    int64_t held_ns = 0;                  // the largest model since the arenas were last given back
+    int held_nn = 0;
     uint64_t generation = 0;              // bumped whenever device buffers are replaced
 
     // surfels as given

@@ -1,0 +1,67 @@
+"""Device memory that a stream keeps from one model for the next: bounded by
+the model it has, whatever came before it."""
+import numpy as np
+import pytest
+
+from gpu_common import gpu_lib
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def swgn():
+    return gpu_lib()
+
+
+def _free():
+    import torch
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _cloud(n_surfels, n_nodes, seed=0):
+    rng = np.random.default_rng(seed)
+    pos = rng.uniform(0, 1, (n_surfels, 3)).astype(np.float32)
+    nodes = rng.uniform(0, 1, (n_nodes, 3)).astype(np.float32)
+    pos[:, 2] *= 0.02
+    nodes[:, 2] *= 0.02
+    nrm = np.zeros_like(pos)
+    nrm[:, 2] = -1.0
+    return pos, nrm, nodes
+
+
+def _new_stream(swgn):
+    return swgn.Stream(swgn.sw_config_default(width=64, height=48, fx=50.0, fy=50.0, cx=32.0, cy=24.0, node_sigma=0.05))
+
+
+def _install(st, model):
+    st.set_reference_surfels(model[0], model[1])
+    st.set_node_graph(model[2])
+
+
+# surfels, nodes of models that shrink by less than four times each
+@pytest.mark.parametrize("models", [[(1200000, 600), (400000, 600), (120000, 600), (40000, 600)],
+                                    [(60000, 24000), (50000, 8000), (50000, 2500), (50000, 700)]])
+def test_a_model_after_larger_ones_holds_memory_of_its_own_size(swgn, models):
+    clouds = [_cloud(*m) for m in models]
+    one = _new_stream(swgn)
+    _install(one, clouds[-1])                       # (whatever the first install of a process allocates once)
+    before = _free()
+    fresh = _new_stream(swgn)
+    _install(fresh, clouds[-1])
+    alone = before - _free()
+    before = _free()
+    st = _new_stream(swgn)
+    for c in clouds:
+        _install(st, c)
+    held = before - _free()
+    want = fresh.skinning(), fresh.pattern()
+    got = st.skinning(), st.pattern()
+    for a, b in zip(got, want):
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
+    for x in (one, fresh, st):
+        x.close()
+    # (a model up to four times as large may still be held, and chunks are rounded up)
+    assert held <= 4 * alone + 64 * MIB, (held // MIB, alone // MIB)
