@@ -1416,8 +1416,8 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos, con
         // a model takes over the memory of the last ones (to free and allocate
         // it anew takes longer than the rest of a model's installation) unless
         // it is much smaller than the largest of them, or larger; no work of
-        // the device may still use it
-        SWGN_HIP(hipDeviceSynchronize());
+        // the device may still use it (a first model has nothing to wait for)
+        if (s->held_ns > 0) SWGN_HIP(hipDeviceSynchronize());
         if (!s->surfels_set || n < s->held_ns / 4 || n > 2 * s->held_ns) {
             s->held_ns = 0;
             s->held_nn = 0;

@@ -65,3 +65,26 @@ def test_a_model_after_larger_ones_holds_memory_of_its_own_size(swgn, models):
         x.close()
     # (a model up to four times as large may still be held, and chunks are rounded up)
     assert held <= 4 * alone + 64 * MIB, (held // MIB, alone // MIB)
+
+
+def test_a_first_model_does_not_wait_for_other_streams(swgn):
+    """Surfels set on a fresh stream reuse no memory, so they wait for no work
+    of the device but their own."""
+    import torch
+    pos, nrm, nodes = _cloud(5000, 60)
+    warm, st = _new_stream(swgn), _new_stream(swgn)
+    _install(warm, (pos, nrm, nodes))
+    side, done = torch.cuda.Stream(), torch.cuda.Event()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)                               # (loads the kernel)
+        side.synchronize()
+        torch.cuda._sleep(2_000_000_000)
+        done.record()
+    st.set_reference_surfels(pos, nrm)
+    running = not done.query()
+    side.synchronize()
+    st.set_node_graph(nodes)
+    assert running
+    assert np.array_equal(st.skinning()[0], warm.skinning()[0])
+    st.close()
+    warm.close()
