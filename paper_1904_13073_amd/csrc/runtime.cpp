@@ -817,6 +817,51 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     s->graph_set = true;
 }
 
+// Gives back all device memory of a stream's model, kept or in use.
+void release_model(sw_stream s) {
+    s->held_ns = 0;
+    s->held_nn = 0;
+    s->graph_mem.release();
+    s->ws_mem.release();
+    s->setup_mem.release();
+    s->surf_mem.release();
+    s->spare_mem.release();
+    s->geo_mem.release();
+    s->fuse_mem.release();
+}
+
+// Runs f; if the device is out of memory, once more after less() has given
+// back memory that was only kept for reuse.
+template <class F, class L>
+void retry_with_less(F&& f, L&& less) {
+    try {
+        f();
+        return;
+    } catch (const HipFail& h) {
+        if (h.e != hipErrorOutOfMemory && h.e != hipErrorMemoryAllocation) throw;
+    }
+    (void)hipGetLastError();
+    SWGN_HIP(hipDeviceSynchronize());
+    less();
+    f();
+}
+
+// build_graph, in new memory where what is kept and what it needs do not both fit.
+void build_graph_in_memory(sw_stream s, int nn, const float* node_pos, const float* node_se3, int32_t on_device,
+                           const float4* keep_rq, const float4* keep_tt, bool keep_order) {
+    retry_with_less(
+        [&]() { build_graph(s, nn, node_pos, node_se3, on_device, keep_rq, keep_tt, keep_order); },
+        [&]() {
+            // (the node state of a geometry update is in geo_mem)
+            s->graph_mem.release();
+            s->ws_mem.release();
+            s->setup_mem.release();
+            s->spare_mem.release();
+            s->fuse_mem.release();
+            if (!keep_rq) s->geo_mem.release();
+        });
+}
+
 double model_bytes(const FrameDesc& h, int gn_iters, int64_t n_corr_total) {
     // algorithmic bytes of one frame: data each kernel must read or write at least
     const double ns = h.ns, nn = h.nn, nb = h.nb, npx = h.npx;
@@ -1418,17 +1463,7 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos, con
         // it is much smaller than the largest of them, or larger; no work of
         // the device may still use it (a first model has nothing to wait for)
         if (s->held_ns > 0) SWGN_HIP(hipDeviceSynchronize());
-        if (!s->surfels_set || n < s->held_ns / 4 || n > 2 * s->held_ns) {
-            s->held_ns = 0;
-            s->held_nn = 0;
-            s->graph_mem.release();
-            s->ws_mem.release();
-            s->setup_mem.release();
-            s->surf_mem.release();
-            s->spare_mem.release();
-            s->geo_mem.release();
-            s->fuse_mem.release();
-        }
+        if (!s->surfels_set || n < s->held_ns / 4 || n > 2 * s->held_ns) release_model(s);
         s->surf_mem.reset();
         s->surfels_set = false;
         s->ns = n;
@@ -1436,15 +1471,21 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos, con
         s->fuse_mem.reset();
         s->fz4 = nullptr;
         s->fused = false;
-        s->in_pos = s->surf_mem.alloc<float>(3 * (size_t)n);
-        s->in_nrm = s->surf_mem.alloc<float>(3 * (size_t)n);
+        auto arrays = [&]() {
+            s->in_pos = s->surf_mem.alloc<float>(3 * (size_t)n);
+            s->in_nrm = s->surf_mem.alloc<float>(3 * (size_t)n);
+            s->in_rad = s->surf_mem.alloc<float>(n);
+            s->in_conf = s->surf_mem.alloc<float>(n);
+            s->in_tobs = s->surf_mem.alloc<int>(n);
+            s->in_tinit = s->surf_mem.alloc<int>(n);
+        };
+        retry_with_less(arrays, [&]() {
+            release_model(s);
+            s->held_ns = n;
+        });
         copy_in(s->in_pos, pos, sizeof(float) * 3 * n, on_device, s->exec.st);
         copy_in(s->in_nrm, nrm, sizeof(float) * 3 * n, on_device, s->exec.st);
         // attributes: radius 0, confidence 1, last observed and initialisation frame 0
-        s->in_rad = s->surf_mem.alloc<float>(n);
-        s->in_conf = s->surf_mem.alloc<float>(n);
-        s->in_tobs = s->surf_mem.alloc<int>(n);
-        s->in_tinit = s->surf_mem.alloc<int>(n);
         launch_fill_i32(reinterpret_cast<int*>(s->in_rad), (int)n, 0, s->exec.st);
         launch_fill_i32(reinterpret_cast<int*>(s->in_conf), (int)n, 0x3f800000, s->exec.st);
         launch_fill_i32(s->in_tobs, (int)n, 0, s->exec.st);
@@ -1464,7 +1505,7 @@ sw_status sw_set_node_graph(sw_stream s, int32_t n_nodes, const float* node_pos,
     if (!node_pos) return fail(s->err, SW_EINVAL, "node positions must not be NULL");
     if (on_device != 0 && on_device != 1) return fail(s->err, SW_EINVAL, "on_device must be 0 or 1");
     return guarded(s->err, [&]() -> sw_status {
-        build_graph(s, n_nodes, node_pos, node_se3, on_device, nullptr, nullptr, false);
+        build_graph_in_memory(s, n_nodes, node_pos, node_se3, on_device, nullptr, nullptr, false);
         return SW_OK;
     });
 }
@@ -1882,12 +1923,18 @@ sw_status sw_update_geometry(sw_stream s, sw_geometry_stats* stats) {
         c.spos = s->in_pos; c.snrm = s->in_nrm; c.srad = s->in_rad; c.sconf = s->in_conf;
         c.stobs = s->in_tobs; c.stinit = s->in_tinit;
         c.apos = s->apos3; c.anrm = s->anrm3; c.arad = s->arad; c.aconf = s->aconf;
-        c.dpos = fresh.alloc<float>(3 * (size_t)nnew);
-        c.dnrm = fresh.alloc<float>(3 * (size_t)nnew);
-        c.drad = fresh.alloc<float>(nnew);
-        c.dconf = fresh.alloc<float>(nnew);
-        c.dtobs = fresh.alloc<int>(nnew);
-        c.dtinit = fresh.alloc<int>(nnew);
+        auto arrays = [&]() {
+            c.dpos = fresh.alloc<float>(3 * (size_t)nnew);
+            c.dnrm = fresh.alloc<float>(3 * (size_t)nnew);
+            c.drad = fresh.alloc<float>(nnew);
+            c.dconf = fresh.alloc<float>(nnew);
+            c.dtobs = fresh.alloc<int>(nnew);
+            c.dtinit = fresh.alloc<int>(nnew);
+        };
+        retry_with_less(arrays, [&]() {
+            fresh.release();
+            s->setup_mem.release();
+        });
         launch_compact_surfels(c, st);
         SWGN_HIP(hipGetLastError());
         SWGN_HIP(hipStreamSynchronize(st));
@@ -1897,7 +1944,7 @@ sw_status sw_update_geometry(sw_stream s, sw_geometry_stats* stats) {
         s->held_ns = std::max(s->held_ns, nnew);
         s->in_pos = c.dpos; s->in_nrm = c.dnrm; s->in_rad = c.drad; s->in_conf = c.dconf;
         s->in_tobs = c.dtobs; s->in_tinit = c.dtinit;
-        build_graph(s, nn, np3, nullptr, 1, rq, tt, true);
+        build_graph_in_memory(s, nn, np3, nullptr, 1, rq, tt, true);
         SWGN_HIP(hipStreamSynchronize(st));
         if (stats) {
             stats->n_removed = ns - nkeep;

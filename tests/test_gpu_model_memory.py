@@ -88,3 +88,44 @@ def test_a_first_model_does_not_wait_for_other_streams(swgn):
     assert np.array_equal(st.skinning()[0], warm.skinning()[0])
     st.close()
     warm.close()
+
+
+def test_a_model_that_fits_without_the_kept_memory_is_installed(swgn):
+    """A model of less than twice the last one's surfels takes over its memory;
+    where the two together are more than the device has left, what was kept is
+    given back and the model still fits, as on a fresh stream."""
+    import torch
+    first, second = _cloud(1500000, 2500, 1), _cloud(2900000, 2500, 2)
+    warm = _new_stream(swgn)
+    _install(warm, _cloud(5000, 60))
+    before = _free()
+    fresh = _new_stream(swgn)
+    _install(fresh, second)
+    alone = before - _free()
+    want = fresh.skinning()[0], fresh.layout()
+    fresh.close()
+    before = _free()
+    both = _new_stream(swgn)
+    _install(both, first)
+    _install(both, second)
+    together = before - _free()
+    both.close()
+    assert together > alone + 100 * MIB
+    # fill the device so that `second` fits with half of the difference to spare
+    spare = alone + (together - alone) // 2
+    fill = []
+    for _ in range(2):
+        left = _free() - spare
+        if left > 2 * MIB:
+            fill.append(torch.empty(left // (2 * MIB) * (2 * MIB), dtype=torch.uint8, device="cuda"))
+    st = _new_stream(swgn)
+    try:
+        _install(st, first)
+        _install(st, second)
+        got = st.skinning()[0], st.layout()
+    finally:
+        st.close()
+        del fill
+        torch.cuda.empty_cache()
+        warm.close()
+    assert np.array_equal(got[0], want[0]) and got[1] == want[1]
