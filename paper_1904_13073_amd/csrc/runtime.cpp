@@ -50,7 +50,6 @@ void* Arena::raw(size_t bytes) {
         if (c.size - c.used >= bytes) {
             char* p = c.base + c.used;
             c.used += bytes;
-            bytes_ += bytes;
             return p;
         }
     }
@@ -60,7 +59,6 @@ void* Arena::raw(size_t bytes) {
     SWGN_HIP(hipMalloc(&p, size));
     chunks_.push_back(Chunk{static_cast<char*>(p), size, bytes});
     cur_ = chunks_.size() - 1;
-    bytes_ += bytes;
     return p;
 }
 
@@ -68,7 +66,6 @@ void Arena::release() {
     for (const Chunk& c : chunks_) (void)hipFree(c.base);
     chunks_.clear();
     cur_ = 0;
-    bytes_ = 0;
 }
 
 void* Arena::renew(size_t bytes) {
@@ -88,7 +85,6 @@ void* Arena::renew(size_t bytes) {
 void Arena::reset() {
     for (Chunk& c : chunks_) c.used = 0;
     cur_ = 0;
-    bytes_ = 0;
 }
 
 void Executor::drop_graphs() {
@@ -2072,9 +2068,13 @@ sw_status sw_get_solve_counts(sw_stream s, sw_solve_counts* out) {
 sw_status sw_get_footprint(sw_stream s, int64_t* resident_bytes, int64_t* workspace_bytes) {
     if (!s) return SW_EINVAL;
     if (!s->graph_set) return fail(s->err, SW_ESTATE, "node graph not set");
-    if (resident_bytes)
-        *resident_bytes = (int64_t)(s->surf_mem.bytes() + s->graph_mem.bytes() + s->frame_mem.bytes() +
-                                     s->setup_mem.bytes());
+    if (resident_bytes) {
+        size_t n = 0;
+        for (const Arena* a : {&s->frame_mem, &s->surf_mem, &s->graph_mem, &s->setup_mem, &s->geo_mem, &s->spare_mem,
+                               &s->fuse_mem, &s->append_mem, &s->ws_mem})
+            n += a->held();
+        *resident_bytes = (int64_t)(s->ws_mem.held() > 0 ? n - s->ws_bytes : n);
+    }
     if (workspace_bytes) *workspace_bytes = (int64_t)s->ws_bytes;
     return SW_OK;
 }

@@ -54,11 +54,14 @@ public:
     // if it holds that and is not much larger, else in new memory with an
     // eighth to spare (a model that grows a little each frame)
     void* renew(size_t bytes);
-    size_t bytes() const { return bytes_; }   // bytes handed out (aligned)
+    size_t held() const {                     // bytes of device memory, handed out or not
+        size_t n = 0;
+        for (const Chunk& c : chunks_) n += c.size;
+        return n;
+    }
     void swap(Arena& o) {
         chunks_.swap(o.chunks_);
         std::swap(cur_, o.cur_);
-        std::swap(bytes_, o.bytes_);
     }
 
 private:
@@ -68,7 +71,6 @@ private:
     };
     std::vector<Chunk> chunks_;
     size_t cur_ = 0;                      // chunk handed out from
-    size_t bytes_ = 0;
 };
 
 // A HIP stream plus what a solve needs besides the streams' own memory: the

@@ -129,3 +129,32 @@ def test_a_model_that_fits_without_the_kept_memory_is_installed(swgn):
         torch.cuda.empty_cache()
         warm.close()
     assert np.array_equal(got[0], want[0]) and got[1] == want[1]
+
+
+def test_the_footprint_is_the_memory_held(swgn):
+    """What the stream reports is what the device has less for it, after
+    each step that allocates (within the device's own rounding of allocations)."""
+    pos, nrm, nodes = _cloud(300000, 2000)
+    depth = np.full((48, 64), 2.0, np.float32)
+    warm = _new_stream(swgn)
+    _install(warm, _cloud(5000, 60))
+    warm.solve_frame(depth)
+    warm.fuse_frame(depth, 1)
+    warm.update_geometry()
+    before = _free()
+    st = _new_stream(swgn)
+
+    def check(what):
+        held, told = before - _free(), sum(st.footprint())
+        assert abs(held - told) <= 24 * MIB, (what, held // MIB, told // MIB)
+
+    _install(st, (pos, nrm, nodes))
+    check("a model")
+    for k in range(2):
+        st.fuse_frame(depth, 1 + k)
+        st.update_geometry()
+        check("an update")
+    _install(st, (pos[:100000], nrm[:100000], nodes))
+    check("a smaller model")
+    st.close()
+    warm.close()
