@@ -698,9 +698,8 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     SegmentChain chain{};
     const int* got = nullptr;
     for (int general = 0;; ++general) {
-        launch_permute_surfels(ns, 0, key, val, s->in_pos, s->in_nrm, idx_in, w_in, spx, spy, spz, snx, sny, snz,
+        launch_permute_surfels(ns, general ? nullptr : over, key, val, s->in_pos, s->in_nrm, idx_in, w_in, spx, spy, spz, snx, sny, snz,
                                sidx, sw, sorig, flag, st);
-        launch_fuse_gather(ns, sorig, s->in_rad, s->in_conf, s->in_tobs, h.radius, h.conf, h.t_obs, sinv, st);
         exclusive_scan(flag, fpos, ns, scan_tmp, st);
         launch_run_starts(ns, flag, fpos, key, set_start, set_key, st);
         // block pattern: every pair of a surfel's node set, every graph edge; in-edges of
@@ -718,6 +717,7 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
         launch_tuple_keys(ns, npad, idx_in, key, val, st);
         sort_pairs(key, val, npad, st);
     }
+    launch_fuse_gather(ns, sorig, s->in_rad, s->in_conf, s->in_tobs, h.radius, h.conf, h.t_obs, sinv, st);
     s->nsets = got[0];
     h.nb = got[1];
     h.ell_w = (got[2] + 7) & ~7;

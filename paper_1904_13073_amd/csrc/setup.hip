@@ -501,22 +501,30 @@ __global__ void __launch_bounds__(kBucketBlock) k_bucket_sort(const int* __restr
     }
 }
 
-// Gather surfel arrays into sorted order; flag run starts.
-__global__ void k_permute_surfels(int ns, int seg_len, const uint64_t* __restrict__ key, const uint32_t* __restrict__ val,
+// Gather surfel arrays into sorted order; flag run starts. Where *over is set
+// (given and not zero) the keys are out of order and the whole is done again
+// after another sort: nothing is gathered, and all surfels count as one run,
+// for unsorted ones would be a run each, and what lists the runs' node sets
+// would set the same few bits for every surfel (2M surfels, 9 nodes: 44 ms).
+__global__ void k_permute_surfels(int ns, const int* __restrict__ over, const uint64_t* __restrict__ key, const uint32_t* __restrict__ val,
         const float* __restrict__ ipos, const float* __restrict__ inrm, const int4* __restrict__ iidx,
         const float4* __restrict__ iw, float* __restrict__ px, float* __restrict__ py, float* __restrict__ pz,
         float* __restrict__ nx, float* __restrict__ ny, float* __restrict__ nz, int4* __restrict__ oidx,
         float4* __restrict__ ow, int* __restrict__ orig, int* __restrict__ flag) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= ns) return;
+    if (over && *over != 0) {
+        flag[i] = i == 0 ? 1 : 0;
+        return;
+    }
     int o = (int)val[i];
     px[i] = ipos[3 * o + 0]; py[i] = ipos[3 * o + 1]; pz[i] = ipos[3 * o + 2];
     nx[i] = inrm[3 * o + 0]; ny[i] = inrm[3 * o + 1]; nz[i] = inrm[3 * o + 2];
     oidx[i] = iidx[o];
     ow[i] = iw[o];
     orig[i] = o;
-    // run starts: a new node set (or, with seg_len > 0, every seg_len-th surfel)
-    flag[i] = (i == 0 || key[i] != key[i - 1] || (seg_len > 0 && (i % seg_len) == 0)) ? 1 : 0;
+    // run starts: a new node set
+    flag[i] = (i == 0 || key[i] != key[i - 1]) ? 1 : 0;
 }
 
 // First surfel and node set of every run of equal node sets; pos[ns] runs.
@@ -881,11 +889,11 @@ void launch_tuple_keys(int ns, int npad, const int4* idx, uint64_t* key, uint32_
     hipLaunchKernelGGL(k_tuple_keys, dim3((npad + 255) / 256), dim3(256), 0, st, ns, npad, idx, key, val);
 }
 
-void launch_permute_surfels(int ns, int seg_len, const uint64_t* key, const uint32_t* val, const float* ipos,
+void launch_permute_surfels(int ns, const int* over, const uint64_t* key, const uint32_t* val, const float* ipos,
                             const float* inrm, const int4* iidx, const float4* iw, float* px, float* py,
                             float* pz, float* nx, float* ny, float* nz, int4* oidx, float4* ow, int* orig,
                             int* flag, hipStream_t st) {
-    hipLaunchKernelGGL(k_permute_surfels, dim3((ns + 255) / 256), dim3(256), 0, st, ns, seg_len, key, val, ipos, inrm,
+    hipLaunchKernelGGL(k_permute_surfels, dim3((ns + 255) / 256), dim3(256), 0, st, ns, over, key, val, ipos, inrm,
                        iidx, iw, px, py, pz, nx, ny, nz, oidx, ow, orig, flag);
 }
 

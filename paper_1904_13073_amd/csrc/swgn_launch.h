@@ -28,7 +28,7 @@ size_t bucket_work_ints(int ns);
 void launch_bucket_sort(int ns, int nn, int4* idx, const int* inv, uint64_t* key_in, int* work, uint64_t* key,
                         uint32_t* val, int* over, hipStream_t st);
 void launch_tuple_keys(int ns, int npad, const int4* idx, uint64_t* key, uint32_t* val, hipStream_t st);
-void launch_permute_surfels(int ns, int seg_len, const uint64_t* key, const uint32_t* val, const float* ipos, const float* inrm,
+void launch_permute_surfels(int ns, const int* over, const uint64_t* key, const uint32_t* val, const float* ipos, const float* inrm,
                             const int4* iidx, const float4* iw, float* px, float* py, float* pz, float* nx,
                             float* ny, float* nz, int4* oidx, float4* ow, int* orig, int* flag, hipStream_t st);
 // first surfel and node set of every run of equal node sets (run_pos[ns] runs)
