@@ -342,8 +342,8 @@ typedef struct sw_batch_s* sw_batch;
  * the launch-by-launch path. Not combinable with SW_BATCH_TIMING (EINVAL);
  * streams that capture an iteration (debug_iter) run launch by launch.
  * SW_BATCH_PCG_SPLIT or SW_BATCH_PCG_FUSED (not both) fix the PCG schedule.
- * Otherwise a linear solve is one launch for all streams whose node sets it
- * can hold (while the device has room for its workgroups beside those of
+ * Otherwise a linear solve (of more than one PCG iteration) is one launch for
+ * all streams whose node sets it can hold (while the device has room for its workgroups beside those of
  * other executors' solves), and the rest run step by step in the schedule
  * chosen per batch shape (the autotuner's choice, else fused steps up to 8192
  * nodes in all); all give identical results. */

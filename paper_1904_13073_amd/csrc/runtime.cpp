@@ -106,10 +106,16 @@ static std::mutex g_pcg_mu;
 static PcgHeld g_pcg_held[kMaxDevices];
 
 // workgroups of a whole linear solve of stream s with the executor's kind of
-// them; 0: it cannot take one
+// them; 0: it cannot take one, or is better off without: a single iteration
+// by workgroups that exchange its sums takes longer than a product and a
+// finish launch (a Gauss-Newton iteration, whole and step by step: 700 nodes
+// 43.2 and 39.0 us; 1,788: 50.6, 45.8; 8,000: 81.3, 83.6; 5 x 4,100: 141, 129;
+// two PCG iterations: 47.2, 47.2; 54.8, 54.1; 87.6, 102; 155, 151; three:
+// 51.1, 54.6; 59.1, 61.6; 93.7, 120; 168, 173)
 static int whole_solve_tiles(const Executor& ex, sw_stream s) {
     if (s->pcg_sets(ex.pcg_waves) == 0 || s->h.pcg_iters == 0) return 0;
     const int n = pcg_tiles(s->h, ex.pcg_waves);
+    if (s->h.pcg_iters == 1 && n > 1) return 0;
     return n <= (ex.pcg_alone ? ex.pcg_cus : 2 * ex.pcg_cus) ? n : 0;
 }
 

@@ -20,13 +20,13 @@ def swgn():
 
 
 def test_words_of_a_solve_long_past_are_not_taken_for_new(swgn):
-    """One PCG iteration, so that a solve's first words are its last. Streams
+    """Two PCG iterations, so that a solve's first words are its last. Streams
     of 65 workgroups, one per CU: the fourth's start at different times, and
     the early ones look for the words of those that have not started."""
     scenes = [_surface(4100, k) for k in range(5)]
     first = [s["depth"] for s in scenes]
     other = [(d + np.float32(0.01)).astype(np.float32) for d in first]
-    sides = [[_stream(swgn, s, pcg_iters=1, gn_iters=1) for s in scenes] for _ in range(2)]
+    sides = [[_stream(swgn, s, pcg_iters=2, gn_iters=1) for s in scenes] for _ in range(2)]
     bx = swgn.Batch()
     for sts in sides:
         bx.solve(sts, first)

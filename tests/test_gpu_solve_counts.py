@@ -250,3 +250,14 @@ def test_graphs_beside_other_executors_are_captured_once_per_way_of_launching(sw
         assert 1 <= st.solve_counts()["captures"] <= 3 and st.solve_counts()["redone"] == 0
         st.close()
     bx.close()
+
+
+def test_a_single_pcg_iteration_runs_in_steps(swgn):
+    """(Faster than a solve whose workgroups exchange its only sums.)"""
+    s = _surface(300, 300)
+    for pcg in (1, 2):
+        st = _stream(swgn, s, pcg_iters=pcg)
+        got = st.solve_frame(s["depth"]), st.node_se3()
+        assert _solves(st) == ((0, GN, 0) if pcg == 1 else (GN, 0, 0))
+        _same(got, _steps(swgn, s, pcg_iters=pcg), pcg)
+        st.close()
