@@ -184,6 +184,8 @@ sw_status sw_set_reference_surfels(sw_stream s, int64_t n, const float* pos_xyz,
  * node's 8 nearest other nodes) and the block pattern of J^T J with its
  * segment layout, all on the device. The node order defines the node
  * indices. n_nodes in [9, 32768]; surfels must be set (SW_ESTATE otherwise).
+ * SW_EINVAL, and no node graph is set, if a node has fewer than 8 others at a
+ * finite distance (FP32 square).
  * A repeated call reuses the device memory of the stream's previous node set
  * and so first waits for all work on the device (as freeing it would).
  * Linear solves run as one launch per Gauss-Newton iteration whose workgroups

@@ -662,8 +662,10 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     const float sig = s->cfg.node_sigma;
     float4* boxes = tmp.alloc<float4>(knn_box_count(nn));
     launch_knn_skin(ns, s->in_pos, nn, pref, d_id, boxes, 1.0f / (2.0f * sig * sig), idx_in, w_in, st);
+    int* over = tmp.alloc<int>(2);                      // the surfel order's flag, the node graph's
+    launch_fill_i32(over, 2, 0, st);
     int* nbr_call = tmp.alloc<int>(8 * (size_t)nn);
-    launch_node_graph(nn, pcall, nbr_call, st);
+    launch_node_graph(nn, pcall, nbr_call, over + 1, st);
     int* nbr = G.alloc<int>(8 * (size_t)nn);
     launch_map_graph(nn, nbr_call, d_id, d_inv, nbr, st);
     h.nbr = nbr;
@@ -688,8 +690,6 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
     uint64_t* key_in = tmp.alloc<uint64_t>(ns);
     uint64_t* key = tmp.alloc<uint64_t>(ns);
     uint32_t* val = tmp.alloc<uint32_t>(ns);
-    int* over = tmp.alloc<int>(1);
-    launch_fill_i32(over, 1, 0, st);
     launch_bucket_sort(ns, nn, idx_in, d_inv, key_in, tmp.alloc<int>(bucket_work_ints(ns)), key, val, over, st);
     int* set_start = tmp.alloc<int>(ns + 1);            // runs of one node set
     uint64_t* set_key = tmp.alloc<uint64_t>(ns);
@@ -714,7 +714,8 @@ void build_graph(sw_stream s, int nn, const float* node_pos, const float* node_s
         launch_pattern(ns, key, flag, nn, nbr, bm, in_bm, words, st);
         launch_row_counts(nn, bm, in_bm, words, counts, full, counts + 2 * (size_t)nn, row_ptr, in_ptr, longest, st);
         chain = enqueue_segments(ns, set_key, set_start, fpos, tmp, st);
-        got = read_info(s, {fpos + ns, row_ptr + nn, longest, chain.count, chain.bad, over});
+        got = read_info(s, {fpos + ns, row_ptr + nn, longest, chain.count, chain.bad, over, over + 1});
+        if (got[6] != 0) throw BadInput{"a node has fewer than 8 others at a finite distance"};
         if (got[5] == 0 || general) break;
         // many surfels of few node sets: sorted by the general sort
         const int npad = pow2_at_least(ns, 1024);

@@ -28,6 +28,11 @@ struct HipFail {
     std::string what;
 };
 
+// an argument found wrong on the device
+struct BadInput {
+    std::string what;
+};
+
 #define SWGN_HIP(x)                                                         \
     do {                                                                    \
         hipError_t _e = (x);                                                \
@@ -152,6 +157,8 @@ sw_status guarded(std::string& err, F&& f) {
         const sw_status code =
             (h.e == hipErrorOutOfMemory || h.e == hipErrorMemoryAllocation) ? SW_ENOMEM : SW_EHIP;
         return fail(err, code, h.what + ": " + hipGetErrorString(h.e));
+    } catch (const BadInput& b) {
+        return fail(err, SW_EINVAL, b.what);
     } catch (const std::bad_alloc&) {
         return fail(err, SW_ENOMEM, "host allocation failed");
     }

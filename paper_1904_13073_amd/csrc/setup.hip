@@ -60,11 +60,13 @@ __global__ void __launch_bounds__(256) k_knn_skin(int ns, const float* __restric
 // One wave per node j: lane l keeps the 8 nearest of the nodes l, l + 64, ...
 // (ascending index, so equal keys keep the lower index first), then the wave
 // merges its 64 sorted lists by taking, 8 times, the smallest (key, index)
-// head: the same set and order as one sequential scan.
+// head: the same set and order as one sequential scan. A node with fewer than
+// 8 others at a finite distance sets *lone (and lists node 0 in their place).
 constexpr int kGraphNodesPerBlock = 4;
 
 __global__ void __launch_bounds__(64 * kGraphNodesPerBlock) k_node_graph(int nn, const float4* __restrict__ nodes,
-                                                                         int* __restrict__ nbr) {
+                                                                         int* __restrict__ nbr,
+                                                                         int* __restrict__ lone) {
     const int lane = threadIdx.x % kWave;
     const int j = blockIdx.x * kGraphNodesPerBlock + threadIdx.x / kWave;
     if (j >= nn) return;                     // whole waves: no barrier follows
@@ -98,7 +100,11 @@ __global__ void __launch_bounds__(64 * kGraphNodesPerBlock) k_node_graph(int nn,
             ki[7] = 0x7fffffff;
         }
     }
-    if (lane < 8) nbr[8 * j + lane] = out;
+    if (lane < 8) {
+        const bool none = out == 0x7fffffff;
+        if (none) *lone = 1;
+        nbr[8 * j + lane] = none ? 0 : out;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -865,9 +871,9 @@ void launch_knn_skin(int ns, const float* pos_aos, int nn, const float4* nodes, 
                        inv_two_sigma2, idx, w);
 }
 
-void launch_node_graph(int nn, const float4* nodes, int* nbr, hipStream_t st) {
+void launch_node_graph(int nn, const float4* nodes, int* nbr, int* lone, hipStream_t st) {
     hipLaunchKernelGGL(k_node_graph, dim3((nn + kGraphNodesPerBlock - 1) / kGraphNodesPerBlock),
-                       dim3(64 * kGraphNodesPerBlock), 0, st, nn, nodes, nbr);
+                       dim3(64 * kGraphNodesPerBlock), 0, st, nn, nodes, nbr, lone);
 }
 
 size_t bucket_work_ints(int ns) { return 2 * (size_t)ns + 2 * ((size_t)1 << kBucketBits) + 1; }

@@ -14,7 +14,8 @@ namespace swgn {
 // float4 of scratch.
 void launch_knn_skin(int ns, const float* pos_aos, int nn, const float4* nodes, const int* caller, float4* boxes,
                      float inv_two_sigma2, int4* idx, float4* w, hipStream_t st);
-void launch_node_graph(int nn, const float4* nodes, int* nbr, hipStream_t st);
+// *lone is set if some node has fewer than 8 others at a finite distance
+void launch_node_graph(int nn, const float4* nodes, int* nbr, int* lone, hipStream_t st);
 void sort_pairs(uint64_t* key, uint32_t* val, int n_pow2, hipStream_t st);
 // in[n] -> out[n + 1], out[n] = the total; tmp (scan_tmp_size(n) ints) is read until the last launch ends
 void exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t st);
