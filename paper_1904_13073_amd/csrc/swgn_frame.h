@@ -29,15 +29,18 @@ constexpr int kCorrBlock = 256;
 // Jacobian rows (28.8 KB) and the waves' output staging (10 KB) let four
 // workgroups share a CU.
 constexpr int kCorrPack = 232;
-// Where a launch has at most kCorrFewPacks packs (half of what the chip holds
-// at once), workgroups share a pack, at most kCorrSplit of them, so that each
-// takes kCorrSegs segments on average (10.7k surfels, 2,000 nodes: 47 packs of
-// 70 segments, 25.8 us alone, 11.5, 10.6 and 11.3 us with 4, 8 and 16
-// segments each). A launch that fills the chip is slower for the surfels then
-// seen twice (16 streams, 4,400 packs: 96.7 us, 132 us with 8 segments each).
+// Where a launch has at most kCorrFewPacks packs (one per CU), workgroups share
+// a pack, at most kCorrSplit of them, so that each takes kCorrSegs segments on
+// average (10.7k surfels, 2,000 nodes: 47 packs of 70 segments, 25.8 us alone,
+// 11.5, 10.6 and 11.3 us with 4, 8 and 16 segments each). With more packs the
+// launch is slower for the surfels then seen twice. Packs (segments each): us
+// alone, shared: 188 (67): 25.2, 20.6; 202 (20): 13.5, 12.0; 235 (67): 25.4,
+// 24.4; 247 (34): 16.9, 17.5; 247 (17): 12.7, 11.7; 264 (32): 18.3, 20.2; 267
+// (24): 16.0, 20.7; 329 (67): 30.6, 30.4; 376 (67): 31.1, 34.6; 470 (67): 32.2,
+// 41.4; 528 (32): 24.2, 32.0; 4,400 (16 streams): 96.7, 132.
 constexpr int kCorrSegs = 8;
 constexpr int kCorrSplit = 16;
-constexpr int kCorrFewPacks = 512;
+constexpr int kCorrFewPacks = 256;
 constexpr int kFoldGroups = 16;       // diagonal blocks per fold workgroup (16 lanes each)
 constexpr int kFoldOffLanes = 4;      // lanes per off-diagonal block
 constexpr int kFoldOffGroups = 256 / kFoldOffLanes;   // off-diagonal blocks per fold workgroup
