@@ -389,6 +389,9 @@ sw_status sw_profile_stage(sw_batch b, const sw_stream* streams, int32_t n, int3
  * (1 warp, 2 correspondence, 8 fold, 5 product, 6 finish, 13 fused step)
  * reps times back to back in each launch variant and keep the
  * fastest for later solves of batches in that bucket on this executor.
+ * Products, finishes and fused steps serve the streams whose linear solves
+ * run step by step; whole solves, and the sharing of packs in the
+ * correspondence launch, follow size rules that are not tuned.
  * Variants: the tile order — linear, or XCD-contiguous (the workgroups an XCD
  * runs take one contiguous range of tiles, keeping a stream's data in few L2
  * caches) — and, for the product and the finish, 1 or 2 block rows per wave

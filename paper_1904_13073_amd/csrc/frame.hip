@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(kWarpBlock) k_warp_zbuf(Batch b) {
 // ---------------------------------------------------------------------------
 // Correspondence, residual, Jacobian and the segment Gram matrices.
 //
-// A tile is a pack of whole segments (consecutive surfels, at most 256; a
+// A tile is a pack of whole segments (consecutive surfels, at most kCorrPack; a
 // segment is a run of surfels whose nodes number at most 5 in all). Each
 // thread forms its surfel's row [J | r] in LDS: node block k at the position
 // of its node in the segment's ascending node list (pos4), r in column 30.

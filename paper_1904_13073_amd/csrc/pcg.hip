@@ -156,7 +156,8 @@ __device__ __forceinline__ float2 get_vec(const float4* node, int sub) {
     return f[sub < 4 ? 2 * sub : 2 * (sub & 1) + 1];
 }
 
-// The same for two values: value 0 in lanes 0-31, value 1 in lanes 32-63.
+// Sums over the wave of two values at once, as wave_sum4 forms four: value 0
+// in lanes 0-31, value 1 in lanes 32-63.
 __device__ __forceinline__ double wave_sum2(double a, double b) {
     swap32(a, b);
     a += b;

@@ -371,7 +371,7 @@ long long pcg_wait_limit() {
 // A segment is a run of consecutive surfels (sorted by node set), at most
 // kCorrPack long, whose nodes together number at most 5: its Gram matrix
 // [J | r]^T [J | r] (30 Jacobian columns, node blocks by position in the
-// segment's ascending node list, r in column 30) fits one 32x32 MFMA tile.
+// segment's ascending node list, r in column 30) is 31 x 31.
 // It keeps the 6x6 sub-blocks of the node pairs that share a surfel (bit
 // first(pa) + pb - pa of its 15-bit mask, pa <= pb), then J^T r (30) and
 // r^T r: 36 x pairs + 32 floats from offset seg_off. A pack is a greedy run

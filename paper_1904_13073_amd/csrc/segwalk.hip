@@ -3,7 +3,7 @@
 //
 // Surfels sorted by node set are cut into segments: greedy runs of at most M
 // consecutive surfels whose node sets together name at most 5 nodes, so that
-// a segment's Gram matrix fits one 32x32 MFMA tile; packs are greedy runs of
+// a segment's Gram matrix is at most 31 x 31 (three 16x16 MFMA tiles); packs are greedy runs of
 // whole segments with at most M surfels. A greedy cut is a chain: a segment
 // that opens at surfel s always starts with the node set of s's run, so the
 // next opening after s is a function next(s) of s alone, with

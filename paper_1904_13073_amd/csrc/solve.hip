@@ -1,4 +1,5 @@
-// Linear solve and node update of one Gauss-Newton iteration (Sec. 7, Sec. 8):
+// Linear solve and node update of one Gauss-Newton iteration (Sec. 7, Sec. 8),
+// step by step (pcg.hip does all of it in one launch, where it can):
 //
 //   PCG start    block-Jacobi preconditioner (FP64 inverses of H_kk + mu I) and
 //                the start of preconditioned conjugate gradients on

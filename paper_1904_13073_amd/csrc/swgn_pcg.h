@@ -85,8 +85,8 @@ __device__ __forceinline__ float quad_bcast(float v) {
 
 // The finish of iteration k for one component of one node (8 lanes per node,
 // component c = lane & 7 < 6, lanes 6 and 7 carry zeros): p_k, r_{k+1},
-// z_{k+1} = M r_{k+1} (FP64 sum of the node's 6 entries, read by shuffles
-// within the lane group) and x_{k+1}. A fused step repeats the same
+// z_{k+1} = M r_{k+1} (FP64 sum of the node's 6 entries, read by DPP within
+// the lane group) and x_{k+1}. A fused step repeats the same
 // operations for the nodes of its rows' columns, so both agree bit for bit.
 struct Finished {
     float p, r, z, x;

@@ -114,10 +114,11 @@ def test_a_model_that_fits_without_the_kept_memory_is_installed(swgn):
     # fill the device so that `second` fits with half of the difference to spare
     spare = alone + (together - alone) // 2
     fill = []
-    for _ in range(2):
-        left = _free() - spare
-        if left > 2 * MIB:
-            fill.append(torch.empty(left // (2 * MIB) * (2 * MIB), dtype=torch.uint8, device="cuda"))
+    while (left := _free() - spare) > 2 * MIB:
+        try:
+            fill.append(torch.empty(min(left, 32 << 30) // (2 * MIB) * (2 * MIB), dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:                         # (what is left is in pieces)
+            break
     st = _new_stream(swgn)
     try:
         _install(st, first)
