@@ -436,6 +436,9 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves == 4 && kSets > kPcgPairSe
                     if (p0 == 0 && !last && word[m] >= 0) need |= 1u << m;
                 for (int spin = 0;; ++spin) {
                     asm volatile("" ::: "memory");   // (every round reads anew)
+                    // (the flag's load goes out with the words')
+                    const bool look = (spin & 15) == 15 || t_limit < 0;
+                    const int raised = look ? agent_load(flags + 1) : 0;
 #pragma unroll
                     for (int g = 0; g < kLeafParts; ++g)
                         if (need & (kPartBit << g)) {
@@ -460,11 +463,11 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves == 4 && kSets > kPcgPairSe
                             if (((wuv[m].y ^ tag) | (wuv[m].w ^ tag)) == 0u) need &= ~(1u << m);
                         }
                     if (__ballot(need != 0u) == 0) break;
-                    if ((spin & 15) == 15 || t_limit < 0) {
+                    if (look) {
                         // bounded: nobody waits past the limit, and nobody of the frame once one has
                         const long long now = wall_clock64();
                         if (t0 == 0) t0 = now;
-                        if (agent_load(flags + 1) != 0) {
+                        if (raised != 0) {
                             *(volatile int*)&stalled = 1;
                         } else if (now - t0 > t_limit) {
                             *(volatile int*)&stalled = 1;
